@@ -10,6 +10,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -17,7 +18,7 @@ LIB = os.path.join(HERE, "libsvmi.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", os.path.join(ROCM, "bin", "hipcc"))
 
-SOURCES = ["kernels.hip", "mlp.hip", "api.cpp", "plan.cpp", "jit.cpp", "qasm.cpp"]
+SOURCES = ["block.hip", "kernels.hip", "readout.hip", "mlp.hip", "api.cpp", "plan.cpp", "jit.cpp", "qasm.cpp"]
 # headers embedded as text for the pass kernels compiled at run time
 JIT_HEADERS = [("kJitAbiH", "k2_abi.h"), ("kJitDeviceH", "k2_device.h")]
 
@@ -43,7 +44,7 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-f
 
 def build(verbose: bool = False) -> str:
     write_jit_sources()
-    objs = []
+    objs, cmds = [], []
     for src in SOURCES:
         path = os.path.join(CSRC, src)
         obj = os.path.join(CSRC, src + ".o")
@@ -57,8 +58,11 @@ def build(verbose: bool = False) -> str:
                    "-Wno-unused-result", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include"]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
+        cmds.append(cmd)
         objs.append(obj)
+    # block.hip takes minutes (every register tile of the interpreter), the rest seconds
+    with ThreadPoolExecutor(4) as pool:
+        list(pool.map(lambda c: subprocess.run(c, check=True), cmds))
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs + \
         [f"-L{ROCM}/lib", "-lhiprtc", f"-Wl,-rpath,{ROCM}/lib"]

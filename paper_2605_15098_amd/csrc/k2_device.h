@@ -1,4 +1,4 @@
-// Device code shared by the compiled kernels (kernels.hip) and the pass
+// Device code shared by the compiled kernels (kernels.hip, block.hip) and the pass
 // kernels generated at run time (jit.cpp): complex arithmetic, the block-pass
 // op handlers, the persistent block-pass skeleton and the op interpreter.
 // Every gate's arithmetic lives here once, so the plain sweep, the

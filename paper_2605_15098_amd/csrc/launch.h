@@ -1,4 +1,4 @@
-// Host-side launchers of the gfx950 kernels (defined in kernels.hip).
+// Host-side launchers of the gfx950 kernels (kernels.hip, block.hip, readout.hip).
 // Every launcher enqueues on `stream` and returns the hipError_t of the
 // launch (hipSuccess on success).
 #pragma once
@@ -12,6 +12,13 @@
 namespace svk {
 
 using K2Args = svp::K2Args;
+
+// Work-groups for `work` threads' worth of work, at most cap, at least one.
+inline unsigned grid_for(uint64_t work, unsigned block, unsigned cap)
+{
+    const uint64_t g = (work + block - 1) / block;
+    return g > cap ? cap : (g < 1 ? 1u : (unsigned)g);
+}
 
 hipError_t init_zero_state(void *S, int n, int dtype, hipStream_t st);
 // The state's storage order (sto in k2_device.h): every kernel addresses
