@@ -972,6 +972,42 @@ static sv_status check_measured(sv_handle h, const int *qubits, int nq)
     return SV_OK;
 }
 
+// Scratch of a call that draws shots, and how it draws them: through the
+// cumulative table of every outcome, or without one (few shots of many
+// outcomes); then a full register in the identity layout needs no array of
+// probabilities either (direct).
+struct ShotLayout {
+    uint64_t M;
+    bool table, direct;
+    size_t o_p = 0, o_c, o_w, bytes;  // probabilities, table or tile sums, work
+    ShotLayout(sv_handle h, int nq, uint64_t shots) : M(1ull << (nq == 0 ? h->n : nq))
+    {
+        auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+        table = !svk::shots_without_table(M, shots);
+        direct = !table && nq == 0 && identity(h->l2p);
+        o_c = direct ? 0 : up(M * 8);
+        o_w = o_c + up(table ? M * 8 : svk::shot_scratch_bytes(M));
+        bytes = o_w + up(std::max(outcome_work_bytes(h, nq), table ? svk::scan_scratch_bytes(M) : size_t(0)));
+    }
+};
+
+static sv_status shots_begin(sv_handle h, const int *qubits, int nq, const ShotLayout &L, char *base)
+{
+    double *P = L.direct ? nullptr : (double *)(base + L.o_p);
+    if (P)
+        if (sv_status st = outcome_probs(h, qubits, nq, P, base + L.o_w)) return st;
+    if (L.table) SV_HIP(svk::scan_inclusive(P, (double *)(base + L.o_c), L.M, base + L.o_w, h->stream), "scan");
+    else SV_HIP(svk::shot_prepare(P, h->buf, h->dtype, L.M, base + L.o_c, h->stream), "scan");
+    return SV_OK;
+}
+
+static hipError_t shots_draw(sv_handle h, const ShotLayout &L, char *base, const double *u, uint64_t shots, uint64_t *out)
+{
+    if (L.table) return svk::sample_outcomes((const double *)(base + L.o_c), L.M, u, shots, out, h->stream);
+    return svk::shot_outcomes(L.direct ? nullptr : (const double *)(base + L.o_p), h->buf, h->dtype, L.M, base + L.o_c, u,
+                              shots, out, h->stream);
+}
+
 sv_status sv_sample(sv_handle h, const int *qubits, int nq, const double *uniforms, size_t shots, uint64_t *out)
 {
     if (sv_status s = check_handle(h)) return s;
@@ -979,17 +1015,13 @@ sv_status sv_sample(sv_handle h, const int *qubits, int nq, const double *unifor
     if (shots > 0 && (!uniforms || !out)) return fail(SV_ERR_INVALID_ARG, "null uniforms or output");
     if (shots == 0) return SV_OK;
     const bool du = is_device_ptr(uniforms), dout = is_device_ptr(out);
-    const uint64_t M = 1ull << (nq == 0 ? h->n : nq);
     const size_t chunk = std::min<size_t>(shots, size_t(1) << 22);
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t o_p = 0, o_c = up(M * 8), o_w = o_c + up(M * 8);
-    const size_t o_u = o_w + up(std::max(outcome_work_bytes(h, nq), svk::scan_scratch_bytes(M)));
-    const size_t o_o = o_u + up(chunk * 8), need = o_o + up(chunk * 8);
+    const ShotLayout L(h, nq, shots);
+    const size_t o_u = L.bytes, o_o = o_u + up(chunk * 8), need = o_o + up(chunk * 8);
     if (sv_status st = ensure_scratch(h, need)) return st;
     char *base = (char *)h->scratch;
-    double *P = (double *)(base + o_p), *cdf = (double *)(base + o_c);
-    if (sv_status st = outcome_probs(h, qubits, nq, P, base + o_w)) return st;
-    SV_HIP(svk::scan_inclusive(P, cdf, M, base + o_w, h->stream), "scan");
+    if (sv_status st = shots_begin(h, qubits, nq, L, base)) return st;
     for (size_t off = 0; off < shots; off += chunk) {
         const size_t c = std::min(chunk, shots - off);
         const double *u = uniforms + off;
@@ -998,7 +1030,7 @@ sv_status sv_sample(sv_handle h, const int *qubits, int nq, const double *unifor
             u = (const double *)(base + o_u);
         }
         uint64_t *o = dout ? out + off : (uint64_t *)(base + o_o);
-        SV_HIP(svk::sample_outcomes(cdf, M, u, c, o, h->stream), "sample");
+        SV_HIP(shots_draw(h, L, base, u, c, o), "sample");
         if (!dout) {
             SV_HIP(hipMemcpyAsync(out + off, o, c * 8, hipMemcpyDeviceToHost, h->stream), "copy");
             SV_HIP(hipStreamSynchronize(h->stream), "sync");
@@ -1013,24 +1045,24 @@ sv_status sv_measure(sv_handle h, const int *qubits, int nq, double u, uint64_t 
     if (sv_status s = check_measured(h, qubits, nq)) return s;
     if (!outcome || !prob) return fail(SV_ERR_INVALID_ARG, "null output");
     if (!(u >= 0.0 && u < 1.0)) return fail(SV_ERR_INVALID_ARG, "u must be in [0, 1)");
-    const uint64_t M = 1ull << (nq == 0 ? h->n : nq);
-    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    const size_t o_p = 0, o_c = up(M * 8), o_w = o_c + up(M * 8);
-    const size_t o_u = o_w + up(std::max(outcome_work_bytes(h, nq), svk::scan_scratch_bytes(M)));
-    const size_t need = o_u + 256;
+    const ShotLayout L(h, nq, 1);
+    const size_t o_u = L.bytes, need = o_u + 256;
     if (sv_status st = ensure_scratch(h, need)) return st;
     char *base = (char *)h->scratch;
-    double *P = (double *)(base + o_p), *cdf = (double *)(base + o_c);
-    if (sv_status st = outcome_probs(h, qubits, nq, P, base + o_w)) return st;
-    SV_HIP(svk::scan_inclusive(P, cdf, M, base + o_w, h->stream), "scan");
+    if (sv_status st = shots_begin(h, qubits, nq, L, base)) return st;
     SV_HIP(hipMemcpyAsync(base + o_u, &u, 8, hipMemcpyHostToDevice, h->stream), "copy");
     uint64_t *dm = (uint64_t *)(base + o_u + 64);
-    SV_HIP(svk::sample_outcomes(cdf, M, (const double *)(base + o_u), 1, dm, h->stream), "sample");
+    SV_HIP(shots_draw(h, L, base, (const double *)(base + o_u), 1, dm), "sample");
     uint64_t m = 0;
     SV_HIP(hipMemcpyAsync(&m, dm, 8, hipMemcpyDeviceToHost, h->stream), "copy");
     SV_HIP(hipStreamSynchronize(h->stream), "sync");
     double pm = 0.0;
-    SV_HIP(hipMemcpyAsync(&pm, P + m, 8, hipMemcpyDeviceToHost, h->stream), "copy");
+    const double *dp = (const double *)(base + L.o_p) + m;
+    if (L.direct) {
+        dp = (const double *)(base + o_u + 128);
+        SV_HIP(svk::probabilities(h->buf, h->n, h->dtype, h->l2p.data(), (double *)(base + o_u + 128), m, 1, h->stream), "probs");
+    }
+    SV_HIP(hipMemcpyAsync(&pm, dp, 8, hipMemcpyDeviceToHost, h->stream), "copy");
     SV_HIP(hipStreamSynchronize(h->stream), "sync");
     if (!(pm > 0.0)) return fail(SV_ERR_INVALID_ARG, "the drawn outcome has zero probability (state is zero)");
     // the measured qubits' physical bits must equal m's bits

@@ -64,6 +64,14 @@ size_t scan_scratch_bytes(uint64_t m);
 hipError_t scan_inclusive(const double *in, double *out, uint64_t m, void *scratch, hipStream_t st);
 hipError_t sample_outcomes(const double *cdf, uint64_t M, const double *u, uint64_t shots, uint64_t *out,
                            hipStream_t st);
+// The same without a table of M sums (readout.hip): shot_prepare sums and scans
+// tiles into scratch (shot_scratch_bytes(M)), shot_outcomes draws. p: the M
+// probabilities (device), or null for those of state S in the identity layout.
+bool shots_without_table(uint64_t M, uint64_t shots);
+size_t shot_scratch_bytes(uint64_t M);
+hipError_t shot_prepare(const double *p, const void *S, int dtype, uint64_t M, void *scratch, hipStream_t st);
+hipError_t shot_outcomes(const double *p, const void *S, int dtype, uint64_t M, const void *scratch, const double *u,
+                         uint64_t shots, uint64_t *out, hipStream_t st);
 hipError_t collapse(void *S, int n, int dtype, uint64_t mask, uint64_t val, double scale, hipStream_t st);
 
 // Plain HBM stream (bandwidth reference): mode 0 copy, 1 in place.

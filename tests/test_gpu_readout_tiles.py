@@ -1,5 +1,5 @@
-"""GPU readouts in permuted layouts: export, import, probabilities and
-marginals through the tiled kernels against plain numpy.
+"""GPU readouts in permuted layouts: export, import, probabilities, marginals
+and shots through the tiled kernels against plain numpy.
 
 A circuit of SWAP gates relabels the qubits without touching an amplitude, so
 export and import have to return the imported bits, and probabilities are
@@ -11,6 +11,7 @@ complex128), below and above the storage order's first size, 2^20 outputs.
 import numpy as np
 import pytest
 
+from oracle import measure as M
 from paper_2605_15098_amd import sv
 from paper_2605_15098_amd import workloads as W
 
@@ -90,5 +91,41 @@ def test_probabilities_and_marginals(n, dtype):
             sv.sv_probabilities(s.h, qs, n, out=out)
             assert np.max(np.abs(out.cpu().numpy() - want)) <= 1e-12, qs
             assert np.array_equal(sv.sv_probabilities(s.h, qs, n), out.cpu().numpy()) or qs is None
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n,shots", [(5, 3), (9, 4), (9, 9), (10, 15), (16, 1000), (17, 100), (20, 5000)])
+@pytest.mark.parametrize("layout", ["identity", "permuted"])
+def test_shots_with_and_without_table(n, shots, layout, dtype):
+    """Around the M / 64 shots where the table of cumulative sums takes over; half of the outcomes impossible."""
+    s, a, rng = permuted(n, dtype, "random", 33)
+    try:
+        if layout == "identity":
+            s.reset()
+        a[rng.random(1 << n) < 0.5] = 0
+        a[: (1 << n) // 4] = 0           # whole tiles of impossible outcomes
+        a[-1] = 0
+        s.set_state(a)
+        p = np.abs(a.astype(np.complex128)) ** 2
+        u = rng.random(shots)
+        u[0] = 0.0
+        if shots > 1:
+            u[1] = np.nextafter(1.0, 0.0)
+        print(f"case shots n={n} shots={shots} {layout} {dtype}", flush=True)
+        for qs in (None, list(range(n))[::-1]):
+            got = sv.sv_sample(s.h, qs, u)
+            q = p if qs is None else numpy_marginal(p, n, qs)
+            want = M.sample_from(q, u)
+            c, t = M.cdf(q), u * M.cdf(q)[-1]
+            assert np.all(q[got.astype(np.int64)] > 0)
+            for g, w, x in zip(got.tolist(), want.tolist(), t.tolist()):
+                # equal, or the uniform within the sums' rounding of the CDF between the two
+                assert g == w or abs(c[min(g, w)] - x) <= 1e-12 * c[-1], (g, w)
+        m, pm = sv.sv_measure(s.h, None, float(u[-1]))
+        assert abs(pm - p[m]) <= 1e-15 and p[m] > 0
+        after = s.state()
+        assert np.count_nonzero(after) == 1 and abs(abs(after[m]) - 1.0) <= 1e-6
     finally:
         s.close()
