@@ -10,6 +10,7 @@ namespace svk {
 
 constexpr int kMlpHidden = 64;
 constexpr int kMlpMaxIn = 32;
+constexpr int kMlpArgminMax = 64;  // most predictions of a call that also returns their argmin
 
 // Offsets (in floats) of each tensor in the flat parameter array.
 struct MlpLayout {
