@@ -218,10 +218,131 @@ __global__ void __launch_bounds__(128) kq_kernel(C *__restrict__ S, uint64_t ngr
     }
 }
 
+// The same for k = 4..6 on the matrix cores: the gate is a contraction of 2^k
+// complex products per amplitude, and a thread per group can hold neither 2^6
+// amplitudes in registers nor the matrix in the scalar cache. A wave takes NB
+// batches of 16 groups, the columns of the 16x16x4 products: lane 16 q + n
+// loads amplitudes 4 s + q of group n (both components), and all of a wave's
+// inputs are in registers before its first store (the gate is in place).
+// With PAIR (complex64, memory bit 0 neither target nor control) a lane's two
+// batches are neighbouring groups, 16 bytes per access: half the accesses,
+// runs of 256 bytes. The matrix is staged once per work-group in operand
+// order as (re, im) pairs: one LDS read feeds four products, re and im rows
+// against re and im inputs. Lane 16 q + n gets rows 4 q + r (FP32) or 4 r + q
+// (FP64) of group n. Up to k = 5 this is bound by HBM; k = 6 needs 512 flop
+// per amplitude, about as long on the matrix cores as the memory takes.
+// One gate on scattered targets, a thread per group -> this: 26 qubits
+// complex64 k = 5 280-336 -> 211-257 us, k = 6 1122 -> 355-384 us; 25 qubits
+// complex128 k = 5 262-341 -> 205-220 us, k = 6 2619 -> 306-332 us.
+template <typename C, int K, int NB, bool PAIR>
+__global__ void __launch_bounds__(256, K == 6 && PAIR ? 4 : 1) kq_mfma_kernel(C *__restrict__ S, uint64_t nbatch, KqArg a, const C *__restrict__ U)
+{
+    using T = decltype(C::x);
+    using V = typename K2Mfma<T>::V;
+    constexpr int D = 1 << K, TILES = D / 16, STEPS = D / 4;
+    constexpr bool F32 = sizeof(T) == 4;
+    __shared__ C ul[D * D];
+    for (int e = threadIdx.x; e < D * D; e += 256) {
+        const int l = e & 63, s = (e >> 6) % STEPS, t = (e >> 6) / STEPS;
+        ul[e] = U[(16 * t + (l & 15)) * D + 4 * s + (l >> 4)];
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+    // storage offsets of the lane's part of the input and output amplitudes (the order is linear, offsets XOR)
+    const uint64_t qin = ((q & 1) ? a.toff[0] : 0ull) ^ ((q & 2) ? a.toff[1] : 0ull);
+    const uint64_t qout = F32 ? ((q & 1) ? a.toff[2] : 0ull) ^ ((q & 2) ? a.toff[3] : 0ull) : qin;
+    auto off = [&](int x, int first, int bits) {
+        uint64_t o = 0;
+#pragma unroll
+        for (int b = 0; b < bits; ++b)
+            if ((x >> b) & 1) o ^= a.toff[first + b];
+        return o;
+    };
+    const uint64_t stride = (uint64_t)gridDim.x * 4;
+    for (uint64_t b = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); b < nbatch; b += stride) {
+        uint64_t base[NB];
+        C v[NB][STEPS];
+        if constexpr (PAIR) {
+            uint64_t j = (b * 16 + n) * 2;
+            for (int f = 0; f < a.nfixed; ++f) j = insert0(j, a.fixed[f]);
+            base[0] = sto<C>(j | a.cmask);
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                const float4 p = *reinterpret_cast<const float4 *>(S + (base[0] ^ qin ^ off(s, 2, K - 2)));
+                v[0][s] = mk<C>(p.x, p.y);
+                v[1][s] = mk<C>(p.z, p.w);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                uint64_t j = (b * NB + i) * 16 + n;
+                for (int f = 0; f < a.nfixed; ++f) j = insert0(j, a.fixed[f]);
+                base[i] = sto<C>(j | a.cmask);
+#pragma unroll
+                for (int s = 0; s < STEPS; ++s) v[i][s] = S[base[i] ^ qin ^ off(s, 2, K - 2)];
+            }
+        }
+        // (not unrolled: the operand reads of all tiles together would take the registers of two more waves)
+#pragma unroll 1
+        for (int t = 0; t < TILES; ++t) {
+            V re[NB], im[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) re[i] = im[i] = V{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                const C u = ul[(t * STEPS + s) * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    re[i] = K2Mfma<T>::mma(u.x, v[i][s].x, re[i]);
+                    im[i] = K2Mfma<T>::mma(u.y, v[i][s].x, im[i]);
+                    re[i] = K2Mfma<T>::mma(-u.y, v[i][s].y, re[i]);
+                    im[i] = K2Mfma<T>::mma(u.x, v[i][s].y, im[i]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint64_t o = qout ^ off(r, F32 ? 0 : 2, 2) ^ off(t, 4, K - 4);
+                if constexpr (PAIR) {
+                    *reinterpret_cast<float4 *>(S + (base[0] ^ o)) =
+                        make_float4((float)re[0][r], (float)im[0][r], (float)re[1][r], (float)im[1][r]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        C z;
+                        z.x = re[i][r];
+                        z.y = im[i][r];
+                        S[base[i] ^ o] = z;
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <typename C, int K> static hipError_t kq_mfma_launch(C *S, uint64_t ngroups, const KqArg &a, const C *U, hipStream_t st)
+{
+    constexpr int NB = sizeof(C) == 8 ? 2 : 1;
+    const uint64_t nbatch = ngroups / (16 * NB);
+    const unsigned grid = grid_for(nbatch, 4, 1024);
+    if (NB == 2 && a.fixed[0] > 0) kq_mfma_kernel<C, K, NB, NB == 2><<<grid, 256, 0, st>>>(S, nbatch, a, U);
+    else kq_mfma_kernel<C, K, NB, false><<<grid, 256, 0, st>>>(S, nbatch, a, U);
+    return hipGetLastError();
+}
+
+// ngroups is a power of two, so from 32 on there is a whole number of batches;
+// smaller states keep the thread per group. k = 4 takes the matrix cores too:
+// no difference on scattered targets (212 and 208 us at 26 qubits complex64),
+// but 335 against 476 us on the lowest ones, where a thread's amplitudes are
+// neighbours and its accesses touch a line each. k <= 3 stays with the threads
+// (at the memory's rate, 180-205 us).
 template <typename C> static hipError_t kq_launch(void *S, int n, const KqArg &a, const void *U, hipStream_t st)
 {
     const uint64_t ngroups = 1ull << (n - a.nfixed);
     const unsigned grid = (unsigned)((ngroups + 127) / 128);
+    const bool mfma = ngroups >= 32;
+    if (mfma && a.k == 4) return kq_mfma_launch<C, 4>((C *)S, ngroups, a, (const C *)U, st);
+    if (mfma && a.k == 5) return kq_mfma_launch<C, 5>((C *)S, ngroups, a, (const C *)U, st);
+    if (mfma && a.k == 6) return kq_mfma_launch<C, 6>((C *)S, ngroups, a, (const C *)U, st);
     switch (a.k) {
     case 1: kq_kernel<C, 1><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
     case 2: kq_kernel<C, 2><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
