@@ -163,7 +163,7 @@ static std::string generate_pass(const svp::Step &s, const svp::Plan &plan, int 
             const std::string tpred =
                 op.b == svp::CK_MEM ? "code_bit(cx.tloc, cx.base, " + std::to_string(op.c) + ")" : "true";
             o << "k2_pairs<" << op.a << ", R>(a, " << op.kind << ", v, " << tpred << ", " << op.b << ", "
-              << (op.b == svp::CK_SLOT ? op.c : 0) << "); }\n";
+              << (op.b == svp::CK_SLOT ? op.c : 0) << ", " << op.m0 << "); }\n";
             break;
         }
         }

@@ -25,7 +25,7 @@ enum K2Kind {
                      // after; 32 + x in two halves by local bit x, a
                      // thread-id bit at the same position before and after
     K2_DENSE = 1,    // a: slot; b: control kind; c: control slot or bit code;
-                     // v[0..7]: row-major 2x2 (re, im)
+                     // v[0..7]: row-major 2x2 (re, im); m0: DenseForm
     K2_H = 2,        // as K2_DENSE, Hadamard
     K2_X = 3,        // as K2_DENSE, exchange
     K2_PHASE = 4,    // a: slot mask; m0: local-bit mask; m1: block-base mask;
@@ -40,6 +40,10 @@ enum K2Kind {
                      // b: window qubits (4 or 5); c: packed window local bits
                      // (5 bits each, ascending); m0: window local-bit mask
 };
+// Form of a dense 2x2 matrix: general; real (RY); real diagonal and imaginary
+// off-diagonal (RX). The last two take half the arithmetic: the terms left out
+// are products with zero, so finite amplitudes get the same bits.
+enum DenseForm { DF_FULL = 0, DF_REAL = 1, DF_CROSS = 2 };
 // Control of a dense op: none, a register slot, or a bit code (0..l-1 =
 // local bit tested on the thread's local index, 64 + p = memory bit p of the
 // block base).

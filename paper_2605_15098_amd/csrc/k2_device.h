@@ -46,6 +46,33 @@ template <typename C> __device__ __forceinline__ C cmad2(C u0, C a, C u1, C b)
     return r;
 }
 
+// u0 * a + u1 * b for real u0, u1
+template <typename C, typename T> __device__ __forceinline__ C cmad2_rr(T u0, C a, T u1, C b)
+{
+    C r;
+    r.x = xfma(u0, a.x, u1 * b.x);
+    r.y = xfma(u0, a.y, u1 * b.y);
+    return r;
+}
+
+// u0 * a + i u1 * b for real u0, u1
+template <typename C, typename T> __device__ __forceinline__ C cmad2_ri(T u0, C a, T u1, C b)
+{
+    C r;
+    r.x = xfma(u0, a.x, -(u1 * b.y));
+    r.y = xfma(u0, a.y, u1 * b.x);
+    return r;
+}
+
+// i u0 * a + u1 * b for real u0, u1
+template <typename C, typename T> __device__ __forceinline__ C cmad2_ir(T u0, C a, T u1, C b)
+{
+    C r;
+    r.x = xfma(-u0, a.y, u1 * b.x);
+    r.y = xfma(u0, a.x, u1 * b.y);
+    return r;
+}
+
 // Component-wise select (a whole-struct ?: on double2 is lowered through
 // scratch memory).
 template <typename C> __device__ __forceinline__ C csel(bool p, C x, C y)
@@ -138,8 +165,11 @@ __device__ __forceinline__ void lds_barrier()
 
 // Dense, Hadamard or exchange gate on register slot J, optionally controlled
 // by another slot (ckind CK_SLOT) or a per-thread predicate (tpred).
+// The forms of cmad2 with zero halves keep its order of operations, so they
+// give its bits (24 qubits complex128, layers of RX and RY and CNOT: half of the pass
+// arithmetic is products with zero otherwise).
 template <int J, int R, typename C>
-__device__ __forceinline__ void k2_pairs(C *a, int kind, const double *v, bool tpred, int ckind, int cslot)
+__device__ __forceinline__ void k2_pairs(C *a, int kind, const double *v, bool tpred, int ckind, int cslot, int form)
 {
     const C u00 = mk<C>(v[0], v[1]), u01 = mk<C>(v[2], v[3]);
     const C u10 = mk<C>(v[4], v[5]), u11 = mk<C>(v[6], v[7]);
@@ -156,6 +186,12 @@ __device__ __forceinline__ void k2_pairs(C *a, int kind, const double *v, bool t
         } else if (kind == svp::K2_X) {
             nx = y;
             ny = x;
+        } else if (form == svp::DF_REAL) {
+            nx = cmad2_rr(u00.x, x, u01.x, y);
+            ny = cmad2_rr(u10.x, x, u11.x, y);
+        } else if (form == svp::DF_CROSS) {
+            nx = cmad2_ri(u00.x, x, u01.y, y);
+            ny = cmad2_ir(u10.y, x, u11.x, y);
         } else {
             nx = cmad2(u00, x, u01, y);
             ny = cmad2(u10, x, u11, y);
@@ -921,12 +957,13 @@ struct K2Interp {
                 const int ckind = op.b;
                 const bool tpred = (ckind == svp::CK_MEM) ? code_bit(cx.tloc, cx.base, op.c) : true;
                 const int cslot = op.c;
+                const int form = (int)op.m0;
                 switch (op.a) {
-                case 0: k2_pairs<0, R>(a, kind, op.v, tpred, ckind, cslot); break;
-                case 1: if constexpr (LOGR > 1) k2_pairs<1, R>(a, kind, op.v, tpred, ckind, cslot); break;
-                case 2: if constexpr (LOGR > 2) k2_pairs<2, R>(a, kind, op.v, tpred, ckind, cslot); break;
-                case 3: if constexpr (LOGR > 3) k2_pairs<3, R>(a, kind, op.v, tpred, ckind, cslot); break;
-                case 4: if constexpr (LOGR > 4) k2_pairs<4, R>(a, kind, op.v, tpred, ckind, cslot); break;
+                case 0: k2_pairs<0, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
+                case 1: if constexpr (LOGR > 1) k2_pairs<1, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
+                case 2: if constexpr (LOGR > 2) k2_pairs<2, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
+                case 3: if constexpr (LOGR > 3) k2_pairs<3, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
+                case 4: if constexpr (LOGR > 4) k2_pairs<4, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
                 default: break;
                 }
             }

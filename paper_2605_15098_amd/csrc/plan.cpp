@@ -339,6 +339,14 @@ struct Builder {
         plan.ops.push_back(op);
     }
 
+    // Which halves of a 2x2 matrix are zero (K2_DENSE's m0).
+    static uint64_t dense_form(const double *u)
+    {
+        if (u[1] == 0.0 && u[3] == 0.0 && u[5] == 0.0 && u[7] == 0.0) return DF_REAL;
+        if (u[1] == 0.0 && u[2] == 0.0 && u[4] == 0.0 && u[7] == 0.0) return DF_CROSS;
+        return DF_FULL;
+    }
+
     // LDS of one work-group on gfx950.
     static constexpr uint32_t kLdsLimit = 160 * 1024;
     // blocks above this many bytes stage half at a time (one 2^14 complex64
@@ -765,6 +773,7 @@ struct Builder {
                 else { op.b = CK_MEM; op.c = code_of(g.c); }
             }
             for (int k = 0; k < 8; ++k) op.v[k] = g.u[k];
+            if (op.kind == K2_DENSE) op.m0 = dense_form(g.u);
             plan.ops.push_back(op);
         }
         flush_diag();
