@@ -124,7 +124,11 @@ typedef struct {
     int32_t mode;         /* SV_PLAIN: one sweep per gate (Algorithm 1);
                              SV_PARTITIONED: Section III-B                     */
     int32_t block_qubits; /* l, local qubits per on-chip block; 0 = default
-                             (14 for complex64, 13 for complex128)           */
+                             (14 for complex64, 13 for complex128; with
+                             SV_SWAP_GRAPH and block_qubits, reg_qubits and
+                             pin_qubits all 0 the three are chosen by the
+                             state's size: smaller blocks and tiles below 23
+                             (22) qubits, and the pins that cost least)      */
     int32_t outer_qubits; /* l2 (0 = off): outer tier. Consecutive block
                              passes whose local qubits together number at
                              most l2 run outer block by outer block (2^l2

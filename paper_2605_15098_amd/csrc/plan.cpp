@@ -827,35 +827,40 @@ struct Builder {
 // of the ready gate with the longest chain of dependent local-target gates
 // is added, everything that the bits chosen so far let run is run on a copy
 // of the graph, and this repeats until the block is full.
-std::string schedule_graph(const PlanConfig &cfg, const RawGate *gates, size_t m, int l, int pin, Plan &plan, std::vector<int> &l2p, std::vector<int> &slot_mem,
-                           std::vector<int> &mem_slot, std::vector<MGate> &queue,
-                           const std::function<void()> &flush)
-{
-    std::vector<MGate> G;
-    G.reserve(m);
-    for (size_t i = 0; i < m; ++i) {
-        const RawGate &x = gates[i];
-        if (x.op == OP_SWAP) {
-            std::swap(l2p[x.target], l2p[x.target2]);
-            continue;
-        }
-        MGate g;
-        g.op = x.op;
-        gate_matrix(x.op, x.theta, x.u, g.u, &g.cls);
-        g.t = l2p[x.target];
-        g.c = x.control >= 0 ? l2p[x.control] : -1;
-        diag_angles(x, g);
-        G.push_back(g);
-    }
-    const int M = (int)G.size();
-    std::vector<int> indeg(M, 0), prio(M, 0);
-    std::vector<std::vector<int>> succ(M);
-    std::vector<char> blocking(M);
+class GraphSchedule {
+public:
+    // One block pass: its gates (indices into gates()) in order, its local bits by slot.
+    struct Pass {
+        std::vector<int> gates, local;
+    };
+
+    // l2p is updated by the circuit's SWAPs.
+    GraphSchedule(const PlanConfig &cfg, const RawGate *gates, size_t m, std::vector<int> &l2p)
     {
+        G.reserve(m);
+        for (size_t i = 0; i < m; ++i) {
+            const RawGate &x = gates[i];
+            if (x.op == OP_SWAP) {
+                std::swap(l2p[x.target], l2p[x.target2]);
+                continue;
+            }
+            MGate g;
+            g.op = x.op;
+            gate_matrix(x.op, x.theta, x.u, g.u, &g.cls);
+            g.t = l2p[x.target];
+            g.c = x.control >= 0 ? l2p[x.control] : -1;
+            diag_angles(x, g);
+            G.push_back(g);
+        }
+        M = (int)G.size();
+        indeg.assign(M, 0);
+        prio.assign(M, 0);
+        succ.resize(M);
+        blocking.resize(M);
         std::vector<int> last_nd(64, -1);
         std::vector<std::vector<int>> diag_since(64);
-        auto edge = [&](int a, int c) {
-            succ[a].push_back(c);
+        auto edge = [&](int x, int c) {
+            succ[x].push_back(c);
             ++indeg[c];
         };
         for (int i = 0; i < M; ++i) {
@@ -876,97 +881,158 @@ std::string schedule_graph(const PlanConfig &cfg, const RawGate *gates, size_t m
                 }
             }
         }
+        // longest chain of local-target gates starting at each gate
+        for (int i = M - 1; i >= 0; --i) {
+            int best = 0;
+            for (int s : succ[i]) best = std::max(best, prio[s]);
+            prio[i] = best + blocking[i];
+        }
     }
-    // longest chain of local-target gates starting at each gate
-    for (int i = M - 1; i >= 0; --i) {
-        int best = 0;
-        for (int s : succ[i]) best = std::max(best, prio[s]);
-        prio[i] = best + blocking[i];
-    }
-    auto runnable = [&](int i, const std::vector<char> &local) { return !blocking[i] || local[G[i].t]; };
 
-    // look-ahead choice of the next block's free local bits from the ready set
-    auto choose = [&](const std::vector<int> &ready) {
-        std::vector<char> in(64, 0);
-        for (int p = 0; p < pin; ++p) in[p] = 1;
-        std::vector<int> want, work = ready, held, undo;
+    const std::vector<MGate> &gates() const { return G; }
+
+    // The passes with blocks of l qubits that keep the low `pin` memory bits;
+    // *swaps counts the qubits gathered into a block.
+    std::vector<Pass> run(int l, int pin, int64_t *swaps)
+    {
+        std::vector<Pass> out;
+        *swaps = 0;
+        std::vector<int> slot_mem(l), mem_slot(64, -1);
+        for (int v = 0; v < l; ++v) slot_mem[v] = v, mem_slot[v] = v;
+        const std::vector<int> indeg0 = indeg;
+        auto runnable = [&](int i, const std::vector<char> &local) { return !blocking[i] || local[G[i].t]; };
+
+        // look-ahead choice of the next block's free local bits from the ready set
+        auto choose = [&](const std::vector<int> &ready) {
+            std::vector<char> in(64, 0);
+            for (int p = 0; p < pin; ++p) in[p] = 1;
+            std::vector<int> want, work = ready, held, undo;
+            for (;;) {
+                while (!work.empty()) {
+                    const int i = work.back();
+                    work.pop_back();
+                    if (!runnable(i, in)) {
+                        held.push_back(i);
+                        continue;
+                    }
+                    for (int s : succ[i]) {
+                        undo.push_back(s);
+                        if (--indeg[s] == 0) work.push_back(s);
+                    }
+                }
+                if (held.empty() || pin + (int)want.size() >= l) break;
+                int best = -1;
+                for (int i : held)
+                    if (best < 0 || prio[i] > prio[best] || (prio[i] == prio[best] && i < best)) best = i;
+                in[G[best].t] = 1;
+                want.push_back(G[best].t);
+                work.swap(held);
+            }
+            for (int s : undo) ++indeg[s];
+            return want;
+        };
+        // gather the chosen bits, keeping the pinned bits and, in the places left,
+        // the bits already local; new bits take the freed slots in slot order
+        auto gather = [&](const std::vector<int> &want) {
+            std::vector<char> keep(64, 0);
+            int kept = 0;
+            for (int p = 0; p < pin; ++p) keep[p] = 1, ++kept;
+            for (int p : want) keep[p] = 1, ++kept;
+            for (int v = 0; v < l && kept < l; ++v)
+                if (!keep[slot_mem[v]]) keep[slot_mem[v]] = 1, ++kept;
+            std::vector<int> incoming;
+            for (int p : want)
+                if (mem_slot[p] < 0) incoming.push_back(p);
+            size_t next = 0;
+            for (int v = 0; v < l && next < incoming.size(); ++v) {
+                if (keep[slot_mem[v]]) continue;
+                mem_slot[slot_mem[v]] = -1;
+                slot_mem[v] = incoming[next++];
+                mem_slot[slot_mem[v]] = v;
+                *swaps += 1;
+            }
+            std::vector<char> local(64, 0);
+            for (int v = 0; v < l; ++v) local[slot_mem[v]] = 1;
+            return local;
+        };
+
+        std::priority_queue<int, std::vector<int>, std::greater<int>> ready;
+        std::vector<int> held;
+        for (int i = 0; i < M; ++i)
+            if (indeg[i] == 0) held.push_back(i);
+        // the first block costs nothing to choose either
+        std::vector<char> local = gather(choose(held));
         for (;;) {
-            while (!work.empty()) {
-                const int i = work.back();
-                work.pop_back();
-                if (!runnable(i, in)) {
+            Pass pass;
+            for (int i : held) ready.push(i);
+            held.clear();
+            while (!ready.empty()) {
+                const int i = ready.top();
+                ready.pop();
+                if (!runnable(i, local)) {
                     held.push_back(i);
                     continue;
                 }
-                for (int s : succ[i]) {
-                    undo.push_back(s);
-                    if (--indeg[s] == 0) work.push_back(s);
-                }
+                pass.gates.push_back(i);
+                for (int s : succ[i])
+                    if (--indeg[s] == 0) ready.push(s);
             }
-            if (held.empty() || pin + (int)want.size() >= l) break;
-            int best = -1;
-            for (int i : held)
-                if (best < 0 || prio[i] > prio[best] || (prio[i] == prio[best] && i < best)) best = i;
-            in[G[best].t] = 1;
-            want.push_back(G[best].t);
-            work.swap(held);
-        }
-        for (int s : undo) ++indeg[s];
-        return want;
-    };
-    // gather the chosen bits, keeping the pinned bits and, in the places left,
-    // the bits already local; new bits take the freed slots in slot order
-    auto gather = [&](const std::vector<int> &want) {
-        std::vector<char> keep(64, 0);
-        int kept = 0;
-        for (int p = 0; p < pin; ++p) keep[p] = 1, ++kept;
-        for (int p : want) keep[p] = 1, ++kept;
-        for (int v = 0; v < l && kept < l; ++v)
-            if (!keep[slot_mem[v]]) keep[slot_mem[v]] = 1, ++kept;
-        std::vector<int> incoming;
-        for (int p : want)
-            if (mem_slot[p] < 0) incoming.push_back(p);
-        size_t next = 0;
-        for (int v = 0; v < l && next < incoming.size(); ++v) {
-            if (keep[slot_mem[v]]) continue;
-            mem_slot[slot_mem[v]] = -1;
-            slot_mem[v] = incoming[next++];
-            mem_slot[slot_mem[v]] = v;
-            plan.stats.swaps += 1;
-        }
-        std::vector<char> local(64, 0);
-        for (int v = 0; v < l; ++v) local[slot_mem[v]] = 1;
-        return local;
-    };
-
-    std::priority_queue<int, std::vector<int>, std::greater<int>> ready;
-    std::vector<int> held;
-    for (int i = 0; i < M; ++i)
-        if (indeg[i] == 0) held.push_back(i);
-    // the first block costs nothing to choose either
-    std::vector<char> local = gather(choose(held));
-    for (;;) {
-        for (int i : held) ready.push(i);
-        held.clear();
-        while (!ready.empty()) {
-            const int i = ready.top();
-            ready.pop();
-            if (!runnable(i, local)) {
-                held.push_back(i);
-                continue;
+            if (!pass.gates.empty()) {
+                pass.local = slot_mem;
+                out.push_back(std::move(pass));
             }
-            queue.push_back(G[i]);
-            plan.stats.gates += 1;
-            for (int s : succ[i])
-                if (--indeg[s] == 0) ready.push(s);
+            if (held.empty()) break;
+            local = gather(choose(held));
         }
-        if (held.empty()) break;
-        flush();
-        local = gather(choose(held));
+        indeg = indeg0;
+        return out;
     }
-    flush();
-    plan.l2p_after = l2p;
-    return "";
+
+private:
+    std::vector<MGate> G;
+    std::vector<std::vector<int>> succ;
+    std::vector<int> indeg, prio;
+    std::vector<char> blocking;
+    int M = 0;
+};
+
+// Blocks of the default schedule, by size. A pass of a large state streams
+// HBM and wants the largest block (fewest passes); below about 2^21
+// amplitudes there are fewer of those than CUs and a pass takes as long as one
+// work-group needs for one block, so smaller blocks with fewer amplitudes per
+// thread are faster although a circuit may need a pass more. Device us, the
+// largest block -> this: complex64 phase estimation 17 qubits 33.9 -> 21.5, 20
+// qubits 44.7 -> 31.6, 200 random gates on 17 qubits 91.9 -> 49.7, 22 qubits 128
+// -> 116; complex128 phase estimation 16 qubits 37.6 -> 21.1, 20 qubits 59.5 ->
+// 42.6, 200 random gates on 18 qubits 115 -> 59.
+// Fewer pinned low qubits leave more free ones, so maybe a pass less, at
+// shorter runs: cost[] is what a pass with pins[] costs relative to the longest
+// runs (measured at 22-30 qubits: complex64 128-byte runs 1.03-1.08, 64-byte
+// runs 1.3; complex128 128-byte runs 1.05-1.13, 64-byte runs 1.3-1.4); the
+// cheapest product with the number of passes is taken (complex64 phase
+// estimation 24 qubits 172 -> 136, 25 qubits 327 -> 283, complex128 24 qubits
+// 395 -> 309, 28 qubits 6706 -> 5896).
+struct AutoBlock {
+    int l, logr, npins;
+    int pins[3];
+    double cost[3];
+};
+
+AutoBlock auto_block(int dtype, int n)
+{
+    AutoBlock b;
+    if (dtype == 0) {
+        if (n <= 20) b = {12, 3, 2, {4, 3}, {1.0, 1.15}};
+        else if (n <= 22) b = {13, 4, 2, {4, 3}, {1.0, 1.2}};
+        else b = {14, 5, 3, {5, 4, 3}, {1.0, 1.06, 1.3}};
+    } else {
+        if (n <= 18) b = {10, 2, 2, {3, 2}, {1.0, 1.05}};
+        else if (n <= 21) b = {12, 3, 3, {4, 3, 2}, {1.0, 1.1, 1.2}};
+        else b = {13, 4, 3, {4, 3, 2}, {1.0, 1.1, 1.4}};
+    }
+    b.l = std::min(b.l, n);
+    if (b.l <= default_reg_qubits(dtype)) b.logr = b.l;  // one thread's registers hold the block
+    return b;
 }
 
 }  // namespace
@@ -1013,8 +1079,15 @@ std::string make_plan(const PlanConfig &cfg, const RawGate *gates, size_t m,
         return "";
     }
     if (l > max_block_qubits(cfg.dtype)) return "block_qubits above the on-chip maximum";
+    // the default schedule as a whole: block, tile and pins by size
+    const bool by_size = cfg.policy == 2 && cfg.remap == 0 && cfg.l <= 0 && cfg.logr <= 0 && cfg.pin_low < 0;
+    AutoBlock ab{};
+    if (by_size) {
+        ab = auto_block(cfg.dtype, n);
+        l = ab.l;
+    }
     b.l = l;
-    b.logr = std::min(cfg.logr > 0 ? cfg.logr : default_reg_qubits(cfg.dtype), l);
+    b.logr = by_size ? ab.logr : std::min(cfg.logr > 0 ? cfg.logr : default_reg_qubits(cfg.dtype), l);
     if (l - b.logr > 10) b.logr = l - 10;  // at most 1024 threads per block
     plan.l = l;
     const bool explicit_remap = cfg.remap == 1;
@@ -1047,7 +1120,37 @@ std::string make_plan(const PlanConfig &cfg, const RawGate *gates, size_t m,
 
     if (cfg.policy == 2) {
         if (explicit_remap) return "the dependence-graph schedule needs virtual remap";
-        return schedule_graph(cfg, gates, m, l, pin, plan, l2p, slot_mem, mem_slot, queue, flush);
+        GraphSchedule graph(cfg, gates, m, l2p);
+        int64_t swaps = 0;
+        std::vector<GraphSchedule::Pass> passes;
+        if (by_size) {
+            double best = 0.0;
+            for (int k = 0; k < ab.npins; ++k) {
+                const int p = std::max(0, std::min(ab.pins[k], l - 1));
+                int64_t sw = 0;
+                std::vector<GraphSchedule::Pass> ps = graph.run(l, p, &sw);
+                const double c = (double)ps.size() * ab.cost[k];
+                if (k == 0 || c < best) {
+                    best = c;
+                    pin = p;
+                    swaps = sw;
+                    passes.swap(ps);
+                }
+                if (passes.size() <= 1) break;  // one pass: longer runs only
+            }
+        } else {
+            passes = graph.run(l, pin, &swaps);
+        }
+        plan.pin = pin;
+        plan.stats.swaps += swaps;
+        for (const GraphSchedule::Pass &ps : passes) {
+            for (int i : ps.gates) queue.push_back(graph.gates()[i]);
+            plan.stats.gates += (int64_t)ps.gates.size();
+            slot_mem = ps.local;
+            flush();
+        }
+        plan.l2p_after = l2p;
+        return "";
     }
 
     // next time (gate index > i) the data now at memory bit p is the target of

@@ -99,6 +99,7 @@ struct Plan {
     PlanStats stats;
     std::vector<int> l2p_after;      // layout after the plan
     int l = 0;
+    int pin = -1;                    // pinned low bits (dependence-graph schedule)
 };
 
 // Default block size for a dtype (complex64 / complex128).
