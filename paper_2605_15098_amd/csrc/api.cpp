@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -68,6 +69,38 @@ size_t amp_bytes(int dtype) { return dtype == SV_COMPLEX64 ? 8 : 16; }
 
 }  // namespace
 
+// A planned circuit with what its launches need on the device. A handle keeps
+// the last few, so a program that applies the same circuits again (a step of a
+// loop, a circuit whose SWAPs alternate between two layouts) does not plan,
+// write out, look up and upload them again: 23-qubit phase estimation spends
+// 420 us of host time on that and 80 us on the device. The key is the whole
+// input of the planner, compared byte by byte.
+struct PreparedPlan {
+    bool valid = false;
+    uint64_t last_use = 0;
+    svp::PlanConfig cfg;
+    bool jit = false, fuse_all = false;
+    std::vector<int> l2p;
+    std::vector<svp::RawGate> gates;
+    svp::Plan plan;
+    std::shared_ptr<const void> module;  // keeps the kernels below loaded
+    std::vector<const void *> kernels;
+    svp::K2Op *dops = nullptr;           // device copies, reused by the next plan of this entry
+    size_t dops_cap = 0;
+    uint8_t *dtab = nullptr;
+    size_t dtab_cap = 0;
+    PreparedPlan() = default;
+    PreparedPlan(const PreparedPlan &) = delete;
+    PreparedPlan &operator=(const PreparedPlan &) = delete;
+    ~PreparedPlan()
+    {
+        if (dops) hipFree(dops);
+        if (dtab) hipFree(dtab);
+    }
+};
+constexpr size_t kMaxPrepared = 8;
+constexpr size_t kMaxPreparedGates = 1 << 16;  // larger circuits are planned on every call (key memory)
+
 struct sv_handle_s {
     int n = 0;
     int dtype = 0;
@@ -76,10 +109,8 @@ struct sv_handle_s {
     bool owns = false;
     hipStream_t stream = nullptr;
     std::vector<int> l2p;
-    svp::K2Op *dops = nullptr;
-    size_t dops_cap = 0;
-    uint8_t *dtab = nullptr;
-    size_t dtab_cap = 0;
+    std::vector<std::unique_ptr<PreparedPlan>> plans;  // at most kMaxPrepared
+    uint64_t plan_clock = 0;
     void *scratch = nullptr;
     size_t scratch_cap = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -155,8 +186,7 @@ void free_handle(sv_handle_s *h)
     for (hipEvent_t e : h->kev) hipEventDestroy(e);
     if (h->ev0) hipEventDestroy(h->ev0);
     if (h->ev1) hipEventDestroy(h->ev1);
-    if (h->dops) hipFree(h->dops);
-    if (h->dtab) hipFree(h->dtab);
+    h->plans.clear();
     if (h->scratch) hipFree(h->scratch);
     if (h->owns && h->buf) hipFree(h->buf);
     delete h;
@@ -237,62 +267,96 @@ sv_status check_schedule(const sv_schedule *s, int dtype)
     return SV_OK;
 }
 
-sv_status run_plan(sv_handle h, const svp::Plan &plan, int outer_qubits, bool record = true)
+bool env_is(const char *name, char c)
 {
-    const auto tu0 = std::chrono::steady_clock::now();
-    if (!plan.ops.empty()) {
-        const size_t need = plan.ops.size();
-        if (need > h->dops_cap) {
-            if (h->dops) {
-                hipStreamSynchronize(h->stream);
-                hipFree(h->dops);
-                h->dops = nullptr;
-                h->dops_cap = 0;
-            }
-            size_t cap = std::max<size_t>(need, 1024);
-            void *p = nullptr;
-            if (dev_alloc(&p, cap * sizeof(svp::K2Op)) != hipSuccess)
-                return fail(SV_ERR_OUT_OF_MEMORY, "program buffer allocation failed");
-            h->dops = (svp::K2Op *)p;
-            h->dops_cap = cap;
+    const char *e = std::getenv(name);
+    return e && e[0] == c;
+}
+
+bool same_config(const svp::PlanConfig &a, const svp::PlanConfig &b)
+{
+    return a.n == b.n && a.dtype == b.dtype && a.mode == b.mode && a.l == b.l && a.logr == b.logr &&
+           a.policy == b.policy && a.remap == b.remap && a.diag_free == b.diag_free && a.pin_low == b.pin_low &&
+           a.fuse_k == b.fuse_k && a.half_lds == b.half_lds;
+}
+
+// Copy n bytes to a device buffer that grows.
+template <typename T> sv_status upload(sv_handle h, T **buf, size_t *cap, const void *src, size_t count, size_t least)
+{
+    if (count > *cap) {
+        if (*buf) {
+            hipStreamSynchronize(h->stream);
+            hipFree(*buf);
+            *buf = nullptr;
+            *cap = 0;
         }
-        SV_HIP(hipMemcpyAsync(h->dops, plan.ops.data(), need * sizeof(svp::K2Op), hipMemcpyHostToDevice,
-                              h->stream),
-               "program upload");
+        const size_t c = std::max(count, least);
+        void *p = nullptr;
+        if (dev_alloc(&p, c * sizeof(T)) != hipSuccess) return fail(SV_ERR_OUT_OF_MEMORY, "program buffer allocation failed");
+        *buf = (T *)p;
+        *cap = c;
     }
-    if (!plan.table.empty()) {
-        const size_t need = plan.table.size();
-        if (need > h->dtab_cap) {
-            if (h->dtab) {
-                hipStreamSynchronize(h->stream);
-                hipFree(h->dtab);
-                h->dtab = nullptr;
-                h->dtab_cap = 0;
-            }
-            size_t cap = std::max<size_t>(need, 1 << 16);
-            void *p = nullptr;
-            if (dev_alloc(&p, cap) != hipSuccess) return fail(SV_ERR_OUT_OF_MEMORY, "table allocation failed");
-            h->dtab = (uint8_t *)p;
-            h->dtab_cap = cap;
-        }
-        SV_HIP(hipMemcpyAsync(h->dtab, plan.table.data(), need, hipMemcpyHostToDevice, h->stream), "table upload");
-    }
+    SV_HIP(hipMemcpyAsync(*buf, src, count * sizeof(T), hipMemcpyHostToDevice, h->stream), "program upload");
+    return SV_OK;
+}
+
+// The plan of this circuit from the handle's current layout, planned, compiled
+// and uploaded unless the handle still holds it.
+sv_status prepared(sv_handle h, const svp::PlanConfig &c, const svp::RawGate *gates, size_t m, PreparedPlan **out)
+{
     // Block passes run as kernels compiled for their op lists (cached), unless
-    // SV_JIT=0 selects the op interpreter. Compilation happens before the
-    // first event so device time covers only the kernels.
-    const char *jenv = std::getenv("SV_JIT");
-    const bool use_jit = !(jenv && jenv[0] == '0');
-    const bool trace = std::getenv("SV_TRACE_HOST") != nullptr;
-    const auto tp0 = std::chrono::steady_clock::now();
-    if (trace)
-        std::fprintf(stderr, "[sv] upload %.3f ms\n", std::chrono::duration<double, std::milli>(tp0 - tu0).count());
-    std::vector<const void *> jit(plan.steps.size(), nullptr);
-    if (use_jit) {
-        std::string err;
-        hipError_t e = svj::prepare_plan(plan, h->dtype, jit, &err);
+    // SV_JIT=0 selects the op interpreter.
+    const bool jit = !env_is("SV_JIT", '0'), fuse_all = env_is("SV_FUSE_ALL", '1');
+    for (auto &p : h->plans)
+        if (p->valid && p->gates.size() == m && p->jit == jit && p->fuse_all == fuse_all && same_config(p->cfg, c) &&
+            p->l2p == h->l2p && (m == 0 || std::memcmp(p->gates.data(), gates, m * sizeof(svp::RawGate)) == 0)) {
+            p->last_use = ++h->plan_clock;
+            *out = p.get();
+            return SV_OK;
+        }
+    PreparedPlan *p = nullptr;
+    if (h->plans.size() < kMaxPrepared) {
+        h->plans.emplace_back(new PreparedPlan());
+        p = h->plans.back().get();
+    } else {
+        for (auto &x : h->plans)
+            if (!p || !x->valid || (p->valid && x->last_use < p->last_use)) p = x.get();
+    }
+    p->valid = false;
+    std::string err = svp::make_plan(c, gates, m, h->l2p, p->plan);
+    if (!err.empty()) return fail(SV_ERR_INVALID_ARG, err);
+    p->kernels.assign(p->plan.steps.size(), nullptr);
+    p->module.reset();
+    bool interp = false;
+    for (const svp::Step &s : p->plan.steps) interp = interp || (!jit && s.kind == svp::ST_K2);
+    if (interp && !p->plan.ops.empty())
+        if (sv_status st = upload(h, &p->dops, &p->dops_cap, p->plan.ops.data(), p->plan.ops.size(), 1024)) return st;
+    if (!p->plan.table.empty())
+        if (sv_status st = upload(h, &p->dtab, &p->dtab_cap, p->plan.table.data(), p->plan.table.size(), 1 << 16)) return st;
+    if (jit) {
+        hipError_t e = svj::prepare_plan(p->plan, h->dtype, p->kernels, &p->module, &err);
         if (e != hipSuccess)
             return fail(SV_ERR_DEVICE, err.empty() ? std::string("pass compilation: ") + hipGetErrorString(e) : err);
     }
+    p->cfg = c;
+    p->jit = jit;
+    p->fuse_all = fuse_all;
+    p->l2p = h->l2p;
+    p->gates.clear();
+    if (m <= kMaxPreparedGates) {
+        p->gates.assign(gates, gates + m);
+        p->valid = true;
+    }
+    p->last_use = ++h->plan_clock;
+    *out = p;
+    return SV_OK;
+}
+
+sv_status run_plan(sv_handle h, const PreparedPlan &prep, int outer_qubits, bool record = true)
+{
+    const svp::Plan &plan = prep.plan;
+    const std::vector<const void *> &jit = prep.kernels;
+    const bool trace = std::getenv("SV_TRACE_HOST") != nullptr;
     const auto tp1 = std::chrono::steady_clock::now();
     h->kev_kind.clear();
     // One launch of block pass si over 2^nblk blocks: the bits of the block
@@ -309,7 +373,7 @@ sv_status run_plan(sv_handle h, const svp::Plan &plan, int outer_qubits, bool re
         a.tab_count = s.tab_count;
         a.ut_off = s.ut_off;
         a.nut = s.nut;
-        a.table = h->dtab;
+        a.table = prep.dtab;
         a.vec2 = (s.l >= 2 && s.logr >= 2 && s.bits[0] == 0) ? 1 : 0;
         a.half_lds = s.half_lds;
         for (int i = 0; i < s.l; ++i) a.bits[i] = (int8_t)s.bits[i];
@@ -319,7 +383,7 @@ sv_status run_plan(sv_handle h, const svp::Plan &plan, int outer_qubits, bool re
         if (jit[si]) return svj::launch(jit[si], h->buf, a, h->stream);
         bool mf = false;
         for (int i = 0; i < s.op_count && !mf; ++i) mf = plan.ops[s.op_begin + i].kind == svp::K2_MFMA;
-        return svk::k2_pass(h->buf, h->n, h->dtype, s.logr, a, h->dops + s.op_begin, mf, h->stream);
+        return svk::k2_pass(h->buf, h->n, h->dtype, s.logr, a, prep.dops + s.op_begin, mf, h->stream);
     };
     auto local_mask = [&](const svp::Step &s) {
         uint64_t m = 0;
@@ -408,8 +472,7 @@ sv_status run_plan(sv_handle h, const svp::Plan &plan, int outer_qubits, bool re
     }
     if (trace) {
         const auto tp2 = std::chrono::steady_clock::now();
-        std::fprintf(stderr, "[sv] prepare %.3f ms, launch %.3f ms, %zu steps\n",
-                     std::chrono::duration<double, std::milli>(tp1 - tp0).count(),
+        std::fprintf(stderr, "[sv] launch %.3f ms, %zu steps\n",
                      std::chrono::duration<double, std::milli>(tp2 - tp1).count(), plan.steps.size());
     }
     return SV_OK;
@@ -587,15 +650,14 @@ sv_status sv_apply_circuit(sv_handle h, const sv_gate *gates, size_t m, const sv
         s = &tuned;
     }
     const auto t0 = std::chrono::steady_clock::now();
-    svp::PlanConfig c = config_from(h, s);
-    svp::Plan plan;
-    std::string err = svp::make_plan(c, reinterpret_cast<const svp::RawGate *>(gates), m, h->l2p, plan);
-    if (!err.empty()) return fail(SV_ERR_INVALID_ARG, err);
+    const svp::PlanConfig c = config_from(h, s);
+    PreparedPlan *p = nullptr;
+    if (sv_status st = prepared(h, c, reinterpret_cast<const svp::RawGate *>(gates), m, &p)) return st;
     const auto t1 = std::chrono::steady_clock::now();
-    if (sv_status st = run_plan(h, plan, s ? s->outer_qubits : 0)) return st;
-    h->l2p = plan.l2p_after;
+    if (sv_status st = run_plan(h, *p, s ? s->outer_qubits : 0)) return st;
+    h->l2p = p->plan.l2p_after;
     std::memset(&h->st, 0, sizeof(h->st));
-    fill_stats(&h->st, c, plan);
+    fill_stats(&h->st, c, p->plan);
     h->st.plan_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     return SV_OK;
 }
@@ -661,14 +723,13 @@ sv_status sv_apply_circuit_ex(sv_handle h, const sv_gate_ex *gates, size_t m, co
     auto flush = [&]() -> sv_status {
         if (seg.empty()) return SV_OK;
         const auto p0 = std::chrono::steady_clock::now();
-        svp::Plan plan;
-        std::string err = svp::make_plan(c, seg.data(), seg.size(), h->l2p, plan);
-        if (!err.empty()) return fail(SV_ERR_INVALID_ARG, err);
+        PreparedPlan *p = nullptr;
+        if (sv_status st = prepared(h, c, seg.data(), seg.size(), &p)) return st;
         plan_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - p0).count();
-        if (sv_status st = run_plan(h, plan, s ? s->outer_qubits : 0, false)) return st;
-        h->l2p = plan.l2p_after;
+        if (sv_status st = run_plan(h, *p, s ? s->outer_qubits : 0, false)) return st;
+        h->l2p = p->plan.l2p_after;
         sv_stats one{};
-        fill_stats(&one, c, plan);
+        fill_stats(&one, c, p->plan);
         tot.gates += one.gates;
         tot.swaps += one.swaps;
         tot.phases += one.phases;
@@ -781,7 +842,7 @@ sv_status sv_prepare(sv_handle h, const sv_gate *gates, size_t m, const sv_sched
         std::string err = svp::make_plan(c, reinterpret_cast<const svp::RawGate *>(gates), m, l2p, plan);
         if (!err.empty()) return fail(SV_ERR_INVALID_ARG, err);
         std::vector<const void *> handles;
-        hipError_t e = svj::prepare_plan(plan, h->dtype, handles, &err);
+        hipError_t e = svj::prepare_plan(plan, h->dtype, handles, nullptr, &err);
         if (e != hipSuccess)
             return fail(SV_ERR_DEVICE, err.empty() ? std::string("pass compilation: ") + hipGetErrorString(e) : err);
         l2p = plan.l2p_after;
@@ -886,6 +947,17 @@ sv_status sv_probabilities(sv_handle h, const int *qubits, int nq, double *out)
     return SV_OK;
 }
 
+// The argmax kernels' result: the index, then its value.
+static sv_status fetch_argmax(sv_handle h, const uint64_t *res, uint64_t *m, double *p)
+{
+    uint64_t r[2] = {0, 0};
+    SV_HIP(hipMemcpyAsync(r, res, sizeof r, hipMemcpyDeviceToHost, h->stream), "copy");
+    SV_HIP(hipStreamSynchronize(h->stream), "sync");
+    *m = r[0];
+    std::memcpy(p, &r[1], sizeof *p);
+    return SV_OK;
+}
+
 sv_status sv_qpe_readout(sv_handle h, int t, uint64_t *m, double *phi, double *pmax)
 {
     if (sv_status s = check_handle(h)) return s;
@@ -903,13 +975,7 @@ sv_status sv_qpe_readout(sv_handle h, int t, uint64_t *m, double *phi, double *p
         double *rv = (double *)(base + am + 8);
         SV_HIP(svk::marginal_argmax(h->buf, h->n, h->dtype, qb.data(), t, ob.data(), h->scratch, ri, rv, h->stream),
                "qpe readout");
-        uint64_t hi = 0;
-        double hv = 0;
-        SV_HIP(hipMemcpyAsync(&hi, ri, 8, hipMemcpyDeviceToHost, h->stream), "copy");
-        SV_HIP(hipMemcpyAsync(&hv, rv, 8, hipMemcpyDeviceToHost, h->stream), "copy");
-        SV_HIP(hipStreamSynchronize(h->stream), "sync");
-        *m = hi;
-        *pmax = hv;
+        if (sv_status s = fetch_argmax(h, ri, m, pmax)) return s;
     } else {
         const uint64_t M = 1ull << t;
         if (h->n - t > 12 && M > 65535) return fail(SV_ERR_UNSUPPORTED, "marginal shape not supported");
@@ -923,13 +989,7 @@ sv_status sv_qpe_readout(sv_handle h, int t, uint64_t *m, double *phi, double *p
         double *rv = (double *)(base + sb + mb + am + 8);
         SV_HIP(svk::marginal(h->buf, h->n, h->dtype, qb.data(), t, ob.data(), marg, base, h->stream), "marginal");
         SV_HIP(svk::argmax(marg, M, ams, ri, rv, h->stream), "argmax");
-        uint64_t hi = 0;
-        double hv = 0;
-        SV_HIP(hipMemcpyAsync(&hi, ri, 8, hipMemcpyDeviceToHost, h->stream), "copy");
-        SV_HIP(hipMemcpyAsync(&hv, rv, 8, hipMemcpyDeviceToHost, h->stream), "copy");
-        SV_HIP(hipStreamSynchronize(h->stream), "sync");
-        *m = hi;
-        *pmax = hv;
+        if (sv_status s = fetch_argmax(h, ri, m, pmax)) return s;
     }
     *phi = std::ldexp((double)*m, -t);
     return SV_OK;
@@ -1105,14 +1165,8 @@ sv_status sv_qpe_readout_noalloc(sv_handle h, int t, uint64_t *m, double *phi, d
     uint64_t *ri = (uint64_t *)((char *)base + am);
     double *rv = (double *)((char *)base + am + 8);
     SV_HIP(svk::marginal_argmax(h->buf, h->n, h->dtype, qb, t, ob, base, ri, rv, h->stream), "qpe readout");
-    uint64_t hi = 0;
-    double hv = 0;
-    SV_HIP(hipMemcpyAsync(&hi, ri, 8, hipMemcpyDeviceToHost, h->stream), "copy");
-    SV_HIP(hipMemcpyAsync(&hv, rv, 8, hipMemcpyDeviceToHost, h->stream), "copy");
-    SV_HIP(hipStreamSynchronize(h->stream), "sync");
-    *m = hi;
-    *pmax = hv;
-    *phi = std::ldexp((double)hi, -t);
+    if (sv_status s = fetch_argmax(h, ri, m, pmax)) return s;
+    *phi = std::ldexp((double)*m, -t);
     return SV_OK;
 }
 
@@ -1350,9 +1404,7 @@ sv_status sv_tune_time(sv_handle h, const sv_gate *gates, size_t m, const sv_sch
                                          h->l2p, probe);
         if (!err.empty()) return fail(SV_ERR_INVALID_ARG, err);
     }
-    if (svj::cache_size() > 256) {
-        if (hipError_t e = svj::trim_cache(128); e != hipSuccess) return hip_fail(e, "kernel cache trim");
-    }
+    if (svj::cache_size() > 256) svj::trim_cache(128);
     const size_t nb = amp_bytes(h->dtype) << h->n;
     void *scratch = nullptr;
     if (dev_alloc(&scratch, nb) != hipSuccess) {
@@ -1374,7 +1426,7 @@ sv_status sv_tune_time(sv_handle h, const sv_gate *gates, size_t m, const sv_sch
         const char *jenv = std::getenv("SV_JIT");
         if (!(jenv && jenv[0] == '0')) {
             std::vector<const void *> handles;
-            if (svj::prepare_plan(plan, h->dtype, handles, &err, &cms) != hipSuccess) {
+            if (svj::prepare_plan(plan, h->dtype, handles, nullptr, &err, &cms) != hipSuccess) {
                 rc = fail(SV_ERR_DEVICE, err.empty() ? std::string("pass compilation failed") : err);
                 break;
             }

@@ -19,6 +19,7 @@
 #include <unistd.h>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <sstream>
 #include <string>
@@ -34,14 +35,29 @@ struct Kernel {
     int per_cu = 0;
     unsigned threads = 0;
 };
-struct Entry {
+// A loaded module, unloaded with its last reference (the cache's or a
+// prepared plan's); its kernels may still be queued on some stream then.
+struct Module {
     hipModule_t mod = nullptr;
     std::vector<Kernel> kernels;
+    Module() = default;
+    Module(const Module &) = delete;
+    Module &operator=(const Module &) = delete;
+    ~Module()
+    {
+        if (!mod) return;
+        (void)hipDeviceSynchronize();
+        (void)hipModuleUnload(mod);
+    }
+};
+struct Entry {
+    std::shared_ptr<const Module> mod;
     uint64_t last_use = 0;
 };
 
 std::mutex g_mu;
-std::unordered_map<std::string, Entry> g_cache;
+// (never destroyed: the runtime may be gone when static objects are)
+std::unordered_map<std::string, Entry> &g_cache = *new std::unordered_map<std::string, Entry>();
 uint64_t g_clock = 0;
 int g_cus = 0;
 
@@ -324,8 +340,8 @@ std::string compile_check(const std::string &src)
     return out;
 }
 
-hipError_t prepare_plan(const svp::Plan &plan, int dtype, std::vector<const void *> &handles, std::string *err,
-                        double *compile_ms)
+hipError_t prepare_plan(const svp::Plan &plan, int dtype, std::vector<const void *> &handles,
+                        std::shared_ptr<const void> *keep, std::string *err, double *compile_ms)
 {
     if (compile_ms) *compile_ms = 0.0;
     handles.assign(plan.steps.size(), nullptr);
@@ -348,28 +364,29 @@ hipError_t prepare_plan(const svp::Plan &plan, int dtype, std::vector<const void
         if (compile_ms)
             *compile_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         if (he != hipSuccess) return he;
-        Entry e;
-        he = hipModuleLoadData(&e.mod, code.data());
+        auto mod = std::make_shared<Module>();
+        he = hipModuleLoadData(&mod->mod, code.data());
         if (he != hipSuccess) return he;
         int idx = 0;
         for (const svp::Step &s : plan.steps) {
             if (s.kind != svp::ST_K2) continue;
             Kernel k;
             const std::string name = "svk2_pass_" + std::to_string(idx++);
-            he = hipModuleGetFunction(&k.fn, e.mod, name.c_str());
+            he = hipModuleGetFunction(&k.fn, mod->mod, name.c_str());
             if (he != hipSuccess) return he;
             k.threads = 1u << (s.l - s.logr);
             he = hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&k.per_cu, k.fn, (int)k.threads, 0);
             if (he != hipSuccess) return he;
             if (k.per_cu < 1) return hipErrorInvalidConfiguration;
-            e.kernels.push_back(k);
+            mod->kernels.push_back(k);
         }
-        it = g_cache.emplace(src, std::move(e)).first;
+        it = g_cache.emplace(src, Entry{std::move(mod), 0}).first;
     }
     it->second.last_use = ++g_clock;
     size_t k = 0;
     for (size_t i = 0; i < plan.steps.size(); ++i)
-        if (plan.steps[i].kind == svp::ST_K2) handles[i] = &it->second.kernels[k++];
+        if (plan.steps[i].kind == svp::ST_K2) handles[i] = &it->second.mod->kernels[k++];
+    if (keep) *keep = it->second.mod;
     return hipSuccess;
 }
 
@@ -392,13 +409,11 @@ hipError_t precompile(const svp::Plan &plan, int dtype, std::string *err)
     return compile(generate_plan(plan, dtype), code, err);
 }
 
-hipError_t trim_cache(size_t keep)
+void trim_cache(size_t keep)
 {
+    std::vector<Entry> dropped;  // released after the lock: unloading synchronizes the device
     std::lock_guard<std::mutex> lk(g_mu);
-    if (g_cache.size() <= keep) return hipSuccess;
-    // kernels of an evicted module may still be queued on some stream
-    hipError_t e = hipDeviceSynchronize();
-    if (e != hipSuccess) return e;
+    if (g_cache.size() <= keep) return;
     std::vector<std::pair<uint64_t, const std::string *>> order;
     for (auto &kv : g_cache) order.emplace_back(kv.second.last_use, &kv.first);
     std::sort(order.begin(), order.end());
@@ -407,11 +422,9 @@ hipError_t trim_cache(size_t keep)
     for (size_t i = 0; i < drop; ++i) victims.push_back(*order[i].second);
     for (const std::string &v : victims) {
         auto it = g_cache.find(v);
-        if (it->second.mod) e = hipModuleUnload(it->second.mod);
+        dropped.push_back(std::move(it->second));
         g_cache.erase(it);
-        if (e != hipSuccess) return e;
     }
-    return hipSuccess;
 }
 
 size_t cache_size()

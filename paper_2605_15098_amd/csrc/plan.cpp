@@ -264,19 +264,17 @@ struct Builder {
         auto build_table = [&](const std::vector<std::pair<uint64_t, uint64_t>> &ts, int first, int nbits) {
             const int N = 1 << nbits;
             std::vector<double> tab(2 * std::max(N, 1));
-            for (int x = 0; x < N; ++x) {
-                uint64_t acc = 0;
-                for (auto &pr : ts) {
-                    bool on = true;
-                    for (int p = 0; p < 64; ++p)
-                        if ((pr.first >> p) & 1ull) {
-                            const int tb = tbit[rank[p]] - first;
-                            if (!((x >> tb) & 1)) on = false;
-                        }
-                    if (on) acc += pr.second;
-                }
-                cexp(acc, &tab[2 * x]);
+            // the angle at x is the sum over the terms whose bits lie within x
+            std::vector<uint64_t> acc(N, 0);
+            for (auto &pr : ts) {
+                uint32_t t = 0;
+                for (uint64_t v = pr.first; v != 0; v &= v - 1) t |= 1u << (tbit[rank[__builtin_ctzll(v)]] - first);
+                acc[t] += pr.second;
             }
+            for (int b = 0; b < nbits; ++b)
+                for (int x = 0; x < N; ++x)
+                    if ((x >> b) & 1) acc[x] += acc[x ^ (1 << b)];
+            for (int x = 0; x < N; ++x) cexp(acc[x], &tab[2 * x]);
             const int idx = (int)(ptab.size() / 2);
             ptab.insert(ptab.end(), tab.begin(), tab.end());
             return idx;
