@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <cstring>
 #include <mutex>
 
 #include "k2_device.h"
@@ -29,24 +30,38 @@ namespace svk {
 
 // ---------------------------------------------------------------- init
 
-template <typename C> __global__ void __launch_bounds__(256) init_kernel(C *S, uint64_t N)
+// |0...0>: 16-byte stores, 16 KiB per work-group (8-byte stores in a
+// grid-stride loop: 3.0 TB/s at 64 MiB, 5.3 at 4 GiB; a fill reaches 6.9).
+constexpr int INIT_PER = 4;
+
+template <typename V> __global__ void __launch_bounds__(256) init_kernel(V *S, uint64_t count, V first)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride) {
-        C z;
-        z.x = (i == 0) ? 1 : 0;
-        z.y = 0;
-        S[i] = z;
+    const uint64_t base = (uint64_t)blockIdx.x * (256 * INIT_PER) + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < INIT_PER; ++k) {
+        const uint64_t i = base + k * 256;
+        if (i < count) S[i] = i == 0 ? first : V{};
     }
+}
+
+template <typename V> static hipError_t init_launch(void *S, uint64_t bytes, int dtype, hipStream_t st)
+{
+    V first{};
+    const float one32 = 1.0f;
+    const double one64 = 1.0;
+    if (dtype == 0) std::memcpy(&first, &one32, sizeof one32);
+    else std::memcpy(&first, &one64, sizeof one64);
+    const uint64_t count = bytes / sizeof(V);
+    init_kernel<V><<<(unsigned)((count + 256 * INIT_PER - 1) / (256 * INIT_PER)), 256, 0, st>>>((V *)S, count, first);
+    return hipGetLastError();
 }
 
 hipError_t init_zero_state(void *S, int n, int dtype, hipStream_t st)
 {
-    const uint64_t N = 1ull << n;
-    const unsigned g = grid_for(N, 256, 8192);
-    if (dtype == 0) init_kernel<float2><<<g, 256, 0, st>>>((float2 *)S, N);
-    else init_kernel<double2><<<g, 256, 0, st>>>((double2 *)S, N);
-    return hipGetLastError();
+    const uint64_t bytes = (dtype == 0 ? 8ull : 16ull) << n;  // 16 or more
+    // (a borrowed buffer may start between two 16-byte units)
+    if ((uintptr_t)S % 16 == 0) return init_launch<float4>(S, bytes, dtype, st);
+    return init_launch<float2>(S, bytes, dtype, st);
 }
 
 // Logical-to-storage order in place (sto is its own inverse, so each pair
@@ -324,7 +339,7 @@ template <typename C, int K> static hipError_t kq_mfma_launch(C *S, uint64_t ngr
     constexpr int NB = sizeof(C) == 8 ? 2 : 1;
     const uint64_t nbatch = ngroups / (16 * NB);
     const unsigned grid = grid_for(nbatch, 4, 1024);
-    if (NB == 2 && a.fixed[0] > 0) kq_mfma_kernel<C, K, NB, NB == 2><<<grid, 256, 0, st>>>(S, nbatch, a, U);
+    if (NB == 2 && a.fixed[0] > 0 && (uintptr_t)S % 16 == 0) kq_mfma_kernel<C, K, NB, NB == 2><<<grid, 256, 0, st>>>(S, nbatch, a, U);
     else kq_mfma_kernel<C, K, NB, false><<<grid, 256, 0, st>>>(S, nbatch, a, U);
     return hipGetLastError();
 }
