@@ -80,6 +80,7 @@ struct PreparedPlan {
     uint64_t last_use = 0;
     svp::PlanConfig cfg;
     bool jit = false, fuse_all = false;
+    bool small = false;                  // a plain circuit that runs as one launch
     std::vector<int> l2p;
     std::vector<svp::RawGate> gates;
     svp::Plan plan;
@@ -329,7 +330,12 @@ sv_status prepared(sv_handle h, const svp::PlanConfig &c, const svp::RawGate *ga
     p->module.reset();
     bool interp = false;
     for (const svp::Step &s : p->plan.steps) interp = interp || (!jit && s.kind == svp::ST_K2);
-    if (interp && !p->plan.ops.empty())
+    p->small = c.mode == SV_PLAIN && h->n <= svk::k1_small_max(h->dtype) && p->plan.steps.size() > 1;
+    if (p->small) {
+        p->plan.ops.clear();
+        for (const svp::Step &s : p->plan.steps) p->plan.ops.push_back(svk::k1_small_op(s.g));
+    }
+    if ((interp || p->small) && !p->plan.ops.empty())
         if (sv_status st = upload(h, &p->dops, &p->dops_cap, p->plan.ops.data(), p->plan.ops.size(), 1024)) return st;
     if (!p->plan.table.empty())
         if (sv_status st = upload(h, &p->dtab, &p->dtab_cap, p->plan.table.data(), p->plan.table.size(), 1 << 16)) return st;
@@ -409,7 +415,12 @@ sv_status run_plan(sv_handle h, const PreparedPlan &prep, int outer_qubits, bool
         return SV_OK;
     };
     if (record) SV_HIP(hipEventRecord(h->ev0, h->stream), "hipEventRecord");
-    for (size_t si = 0; si < plan.steps.size();) {
+    // (with kernel timing on, every gate keeps a launch and a time of its own)
+    const bool small = prep.small && !h->kernel_timing;
+    if (small)
+        if (sv_status st = timed(0, [&] { return svk::k1_small(h->buf, h->n, h->dtype, prep.dops, (int)plan.ops.size(), h->stream); }))
+            return st;
+    for (size_t si = small ? plan.steps.size() : 0; si < plan.steps.size();) {
         const svp::Step &s = plan.steps[si];
         if (s.kind == svp::ST_K1) {
             if (sv_status st = timed(0, [&] { return svk::k1_gate(h->buf, h->n, h->dtype, s.g, h->stream); })) return st;

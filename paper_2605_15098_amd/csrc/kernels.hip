@@ -190,6 +190,109 @@ hipError_t k1_gate(void *S, int n, int dtype, const svp::MGate &g, hipStream_t s
     return dtype == 0 ? k1_launch<float>(S, n, g, st) : k1_launch<double>(S, n, g, st);
 }
 
+// ---------------------------------------------------------------- plain circuits of small states
+
+// Every gate of a plain circuit on a state that fits in LDS, in one launch: one
+// work-group holds the state and applies the gates in order, a barrier
+// after each, with k1_pair_kernel's and k1_diag_kernel's arithmetic (the same
+// bits). A launch per gate is bound by the launches: 3.2 us each against less
+// than a microsecond of work on up to 2^14 amplitudes (10 qubits complex128,
+// 64 gates of a phase estimation: 205 us in launches). ops: K2_PHASE /
+// K2_DIAG / K2_H / K2_X / K2_DENSE records with a: target, b: control or -1, v:
+// the matrix (uniform, read through the scalar unit).
+template <typename C>
+__global__ void __launch_bounds__(1024) k1_small_kernel(C *__restrict__ S, int n, const svp::K2Op *ops, int nops)
+{
+    extern __shared__ unsigned char small_lds[];
+    C *st = reinterpret_cast<C *>(small_lds);
+    const uint32_t N = 1u << n, nt = blockDim.x;
+    for (uint32_t i = threadIdx.x; i < N; i += nt) st[i] = S[i];
+    __syncthreads();
+    k2_const<int32_t> op = as_const<int32_t>(ops);
+    for (int g = 0; g < nops; ++g, op += (int)(sizeof(svp::K2Op) / 4)) {
+        const int kind = op[0], t = op[1], c = op[2];
+        const k2_const<double> v = (k2_const<double>)(op + 8);
+        if (kind == svp::K2_PHASE || kind == svp::K2_DIAG) {
+            // amplitudes with every condition bit set: the control, and for a phase the target
+            const C d0 = mk<C>(v[0], v[1]), d1 = mk<C>(v[6], v[7]);
+            const bool phase = kind == svp::K2_PHASE;
+            int lo = phase ? t : c, hi = phase ? c : -1;
+            if (lo < 0) lo = hi, hi = -1;
+            if (hi >= 0 && hi < lo) {
+                const int x = lo;
+                lo = hi;
+                hi = x;
+            }
+            const uint32_t ones = (lo >= 0 ? 1u << lo : 0u) | (hi >= 0 ? 1u << hi : 0u);
+            const uint32_t cnt = N >> ((lo >= 0) + (hi >= 0));
+            for (uint32_t p = threadIdx.x; p < cnt; p += nt) {
+                uint32_t j = p;
+                if (lo >= 0) j = insert0_32(j, lo);
+                if (hi >= 0) j = insert0_32(j, hi);
+                j |= ones;
+                const C d = csel(!phase && !((j >> t) & 1u), d0, d1);
+                st[j] = cmul(d, st[j]);
+            }
+        } else {
+            const C u00 = mk<C>(v[0], v[1]), u01 = mk<C>(v[2], v[3]), u10 = mk<C>(v[4], v[5]), u11 = mk<C>(v[6], v[7]);
+            const int lo = (c >= 0 && c < t) ? c : t, hi = (c >= 0 && c > t) ? c : t;
+            const uint32_t cbit = c >= 0 ? 1u << c : 0u, pairs = N >> (c >= 0 ? 2 : 1);
+            for (uint32_t p = threadIdx.x; p < pairs; p += nt) {
+                uint32_t j = insert0_32(p, lo);
+                if (c >= 0) j = insert0_32(j, hi);
+                j |= cbit;
+                const uint32_t k = j | (1u << t);
+                C a = st[j], b = st[k];
+                if (kind == svp::K2_H) {
+                    hbfly(a, b);
+                    st[j] = a;
+                    st[k] = b;
+                } else if (kind == svp::K2_X) {
+                    st[j] = b;
+                    st[k] = a;
+                } else {
+                    st[j] = cmad2(u00, a, u01, b);
+                    st[k] = cmad2(u10, a, u11, b);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = threadIdx.x; i < N; i += nt) S[i] = st[i];
+}
+
+int k1_small_max(int dtype) { return dtype == 0 ? 14 : 13; }
+
+svp::K2Op k1_small_op(const svp::MGate &g)
+{
+    svp::K2Op op{};
+    if (g.cls == svp::GC_DIAG) op.kind = (g.u[0] == 1.0 && g.u[1] == 0.0) ? svp::K2_PHASE : svp::K2_DIAG;
+    else op.kind = g.op == 0 ? svp::K2_H : (g.cls == svp::GC_PERM ? svp::K2_X : svp::K2_DENSE);
+    op.a = g.t;
+    op.b = g.c;
+    for (int k = 0; k < 8; ++k) op.v[k] = g.u[k];
+    return op;
+}
+
+template <typename C> static hipError_t k1_small_launch(void *S, int n, const svp::K2Op *ops, int nops, hipStream_t st)
+{
+    const size_t lds = sizeof(C) << n;
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)k1_small_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    // a thread per pair, whole waves
+    const unsigned threads = n >= 11 ? 1024u : (n <= 7 ? 64u : 1u << (n - 1));
+    k1_small_kernel<C><<<1, threads, lds, st>>>((C *)S, n, ops, nops);
+    return hipGetLastError();
+}
+
+hipError_t k1_small(void *S, int n, int dtype, const svp::K2Op *dev_ops, int nops, hipStream_t st)
+{
+    if (n > k1_small_max(dtype)) return hipErrorInvalidValue;
+    return dtype == 0 ? k1_small_launch<float2>(S, n, dev_ops, nops, st) : k1_small_launch<double2>(S, n, dev_ops, nops, st);
+}
+
 // ---------------------------------------------------------------- extended gates
 
 // A k-qubit unitary (2^k x 2^k, row-major, the state's precision; bit b of

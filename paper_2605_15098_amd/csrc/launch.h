@@ -40,6 +40,11 @@ hipError_t k6_batch(int dtype, int lmax, unsigned grid, unsigned threads, size_t
                     unsigned *ctrs, int *err, unsigned limit, bool mfma, hipStream_t st);
 hipError_t zero_u32(unsigned *p, uint32_t n, hipStream_t st);
 hipError_t k1_gate(void *S, int n, int dtype, const svp::MGate &g, hipStream_t st);
+// A plain circuit on a state of at most k1_small_max qubits in one launch:
+// k1_small_op's records in device memory, in order.
+int k1_small_max(int dtype);
+svp::K2Op k1_small_op(const svp::MGate &g);
+hipError_t k1_small(void *S, int n, int dtype, const svp::K2Op *dev_ops, int nops, hipStream_t st);
 hipError_t k3_swap(void *S, int n, int dtype, int p, int v, hipStream_t st);
 // Extended gate: a k-qubit unitary U (device, 4^k amplitudes of the state's
 // type, row-major, bit b of the row index = target b) on physical target bits
