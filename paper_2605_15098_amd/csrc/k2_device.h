@@ -146,6 +146,14 @@ __device__ __forceinline__ bool code_bit(uint32_t tloc, uint64_t base, int code)
     return code >= 64 ? (bool)((base >> (code - 64)) & 1ull) : (bool)((tloc >> code) & 1u);
 }
 
+// Read-only device memory at uniform addresses: pointers to the constant
+// address space, whose loads go through the scalar unit.
+template <typename T> using k2_const = const T __attribute__((address_space(4))) *;
+template <typename T> __device__ __forceinline__ k2_const<T> as_const(const void *p)
+{
+    return (k2_const<T>)(uint64_t)p;
+}
+
 __device__ __forceinline__ uint64_t uniform64(uint64_t x)
 {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
