@@ -284,21 +284,20 @@ sv_status sv_qasm_parse(const char *text, sv_gate_ex *gates, size_t cap, size_t 
 sv_status sv_prepare(sv_handle h, const sv_gate *gates, size_t m, const sv_schedule *s, int repeats);
 
 /* Many independent circuits, one per handle (all of one dtype, distinct
- * handles, one device), in one persistent kernel launch captured in a HIP
- * graph. The launch has one work-group size, 2^t threads with t = min(L - r,
- * n_min - 3) for the schedule's block size L and register tile r (defaults:
- * the dtype's block size and a tile one below the dtype's, 4 for complex64
- * and 3 for complex128, which keeps two work-groups per CU); instance i is planned with the partitioned schedule at its
- * own block size l_i = min(n_i, t + r) and tile l_i - t (at least 3), so
- * large states use the full block and small ones shrink only their tile. An
- * instance carrying at least two work-groups' share of the work gets that
- * many work-groups (at most one per block), which meet at a device-scope
- * counter barrier between passes; smaller instances are packed, largest
- * first, onto the least loaded remaining work-groups and run there one after
- * another. The graph is cached by a hash of the gate lists, layouts, buffers
- * and schedule, so the same batch applied again replays it. Runs on the
- * first handle's stream and synchronizes it (the barrier's error flag is
- * checked: SV_ERR_DEVICE if a barrier wait timed out). Schedules that are not
+ * handles, one device), in one kernel launch per block pass (pass p of every
+ * instance that has one), captured in a HIP graph. The launches have one
+ * work-group size, 2^t threads with t = min(L - r, n_min - 3) for the schedule's
+ * block size L and register tile r (defaults: the dtype's block size and a tile
+ * one below the dtype's, 4 for complex64 and 3 for complex128, which keeps two
+ * work-groups per CU); instance i is planned with the partitioned schedule at
+ * its own block size l_i = min(n_i, t + r) and tile l_i - t (at least 3), so
+ * large states use the full block and small ones shrink only their tile. When
+ * the schedule leaves block, tile and pins to the library, an instance pins fewer low
+ * qubits than the dtype's default where that saves passes. The work-groups of a
+ * launch take chunks of an instance's blocks from a counter, the most expensive
+ * chunks first. The graph is cached by a hash of the gate lists, layouts,
+ * buffers and schedule, so the same batch applied again replays it. Runs on the
+ * first handle's stream and synchronizes it. Schedules that are not
  * partitioned with virtual remap, or a register tile outside 3..5 (3..4 for
  * complex128), are applied one circuit after another. Each handle's stats
  * receive its own counts, its block size and the batch's device time. */

@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libsvmi.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", os.path.join(ROCM, "bin", "hipcc"))
 
-SOURCES = ["block.hip", "kernels.hip", "readout.hip", "mlp.hip", "api.cpp", "plan.cpp", "jit.cpp", "qasm.cpp"]
+SOURCES = ["block.hip", "batch.hip", "kernels.hip", "readout.hip", "mlp.hip", "api.cpp", "plan.cpp", "jit.cpp", "qasm.cpp"]
 # headers embedded as text for the pass kernels compiled at run time
 JIT_HEADERS = [("kJitAbiH", "k2_abi.h"), ("kJitDeviceH", "k2_device.h")]
 
@@ -42,6 +42,14 @@ def write_jit_sources() -> None:
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-ffp-contract=off"]
 
 
+# The interpreters' op loop branches only on uniform values. Structurizing it
+# merges the paths of all handlers through copies of the thread's whole register
+# tile, twice an op (289 vector instructions per amplitude and pass of the
+# batched phase estimations); uniform regions are left as they are.
+INTERP_FLAGS = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
+INTERP_SOURCES = ("block.hip", "batch.hip")
+
+
 def build(verbose: bool = False) -> str:
     write_jit_sources()
     objs, cmds = [], []
@@ -51,7 +59,7 @@ def build(verbose: bool = False) -> str:
         cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-c", path, "-o", obj,
                "-Wall", "-Wno-unused-function"]
         if src.endswith(".hip"):
-            cmd += DEVICE_FLAGS
+            cmd += DEVICE_FLAGS + (INTERP_FLAGS if src in INTERP_SOURCES else [])
         else:
             # host-only translation units: plain g++ against the HIP runtime headers
             cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-c", path, "-o", obj, "-Wall",
@@ -60,8 +68,8 @@ def build(verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         cmds.append(cmd)
         objs.append(obj)
-    # block.hip takes minutes (every register tile of the interpreter), the rest seconds
-    with ThreadPoolExecutor(4) as pool:
+    # block.hip and batch.hip take minutes (every register tile of the interpreter), the rest seconds
+    with ThreadPoolExecutor(5) as pool:
         list(pool.map(lambda c: subprocess.run(c, check=True), cmds))
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs + \

@@ -278,7 +278,7 @@ bool same_config(const svp::PlanConfig &a, const svp::PlanConfig &b)
 {
     return a.n == b.n && a.dtype == b.dtype && a.mode == b.mode && a.l == b.l && a.logr == b.logr &&
            a.policy == b.policy && a.remap == b.remap && a.diag_free == b.diag_free && a.pin_low == b.pin_low &&
-           a.fuse_k == b.fuse_k && a.half_lds == b.half_lds;
+           a.fuse_k == b.fuse_k && a.half_lds == b.half_lds && a.auto_pins == b.auto_pins;
 }
 
 // Copy n bytes to a device buffer that grows.
@@ -1594,11 +1594,8 @@ namespace {
 // of everything its plans depend on.
 struct BatchEntry {
     uint64_t key = 0;
-    int dtype = 0, lmax = 4, count = 0;
-    unsigned grid = 0, threads = 0;
-    size_t lds = 0;
+    int count = 0;
     void *dbuf = nullptr;
-    unsigned *ctrs = nullptr;  // count barrier counters, then the error flag
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<std::vector<int>> l2p_after;
@@ -1613,8 +1610,7 @@ struct BatchEntry {
 };
 
 std::mutex g_batch_mu;
-std::vector<BatchEntry *> g_batches;  // most recent last
-int *g_err_host = nullptr;
+std::vector<std::shared_ptr<BatchEntry>> g_batches;  // most recent last, at most 8
 
 uint64_t mix64(uint64_t h, uint64_t x)
 {
@@ -1641,12 +1637,15 @@ size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
 // Build (or fetch) the batch for these handles; nullptr + message on failure.
 // *sequential is set when the schedule does not run as one launch.
-BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m, const sv_schedule *s,
+std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m, const sv_schedule *s,
                       bool *sequential, std::string *err)
 {
     *sequential = false;
     const int dtype = hs[0]->dtype;
     svp::PlanConfig base = config_from(hs[0], s);
+    // a schedule that leaves the sizes to the library leaves it the pins too: 22
+    // qubits in blocks of 13 take two passes with 128-byte runs, three with 256
+    base.auto_pins = base.l <= 0 && base.logr <= 0 && base.pin_low < 0;
     int min_n = 64;
     for (int i = 0; i < count; ++i) min_n = std::min(min_n, hs[i]->n);
     // One work-group size for the launch, 2^tbits threads; instance i runs
@@ -1684,7 +1683,7 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
         std::lock_guard<std::mutex> lk(g_batch_mu);
         for (size_t k = 0; k < g_batches.size(); ++k)
             if (g_batches[k]->key == key && g_batches[k]->count == count) {
-                BatchEntry *e = g_batches[k];
+                std::shared_ptr<BatchEntry> e = g_batches[k];
                 g_batches.erase(g_batches.begin() + k);
                 g_batches.push_back(e);
                 return e;
@@ -1696,6 +1695,7 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
         svp::PlanConfig c = config_from(hs[i], s);
         c.l = li[i];
         c.logr = ri[i];
+        c.auto_pins = base.auto_pins;
         std::string e = svp::make_plan(c, reinterpret_cast<const svp::RawGate *>(gates[i]), m[i], hs[i]->l2p, plans[i]);
         if (!e.empty()) {
             *err = "instance " + std::to_string(i) + ": " + e;
@@ -1711,8 +1711,12 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
     std::vector<svp::K2Op> ops;
     std::vector<uint8_t> table;
     std::vector<svp::BatchPass> passes;
-    std::vector<svp::BatchInst> insts(count);
-    std::vector<double> work(count);
+    // the launches: chunks of pass 0 of every instance, of pass 1, ...
+    struct InstPass {
+        int pass, logr;
+        double blocks, cost;  // blocks, and their cost in instructions per amplitude times amplitudes
+    };
+    std::vector<std::vector<InstPass>> launches;
     size_t max_lds = 0;
     bool all_half = true;
     const size_t amp = dtype == 0 ? 8 : 16;
@@ -1730,12 +1734,7 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
             }
             ops.push_back(op);
         }
-        insts[i].S = hs[i]->buf;
-        insts[i].pass_off = (int)passes.size();
-        insts[i].npass = 0;
-        insts[i].logr = ri[i];
-        insts[i].l = li[i];
-        insts[i].ctr = i;
+        size_t ip = 0;
         for (const svp::Step &st : P.steps) {
             svp::BatchPass bp{};
             bp.args.n = hs[i]->n;
@@ -1763,11 +1762,20 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
             bp.args.nblk_bits = hs[i]->n - st.l;
             bp.args.base_or = 0;
             bp.op_begin = ob + st.op_begin;
+            bp.S = hs[i]->buf;
+            // vector instructions per amplitude of the load, the store and each op
+            double per_amp = 16.0;
+            for (int k = 0; k < st.op_count; ++k) {
+                const int kind = P.ops[st.op_begin + k].kind;
+                per_amp += kind == svp::K2_HU || kind == svp::K2_SCALE ? 2.0
+                           : kind == svp::K2_MFMA                      ? (double)(6 << P.ops[st.op_begin + k].b)
+                                                                       : 8.0;
+            }
+            if (launches.size() <= ip) launches.emplace_back();
+            launches[ip++].push_back({(int)passes.size(), st.logr, std::ldexp(1.0, hs[i]->n - st.l),
+                                      per_amp * std::ldexp(1.0, hs[i]->n)});
             passes.push_back(bp);
-            insts[i].npass += 1;
         }
-        // work in amplitudes moved: every pass reads and writes the state
-        work[i] = (double)insts[i].npass * std::ldexp(1.0, hs[i]->n);
     }
     // resident capacity
     const unsigned threads = 1u << tbits;
@@ -1788,92 +1796,37 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
         const long v = std::atol(env);
         if (v > 0) cap = std::min(cap, v);
     }
-    // Work-groups: an instance with more than one work-group's share of the
-    // work gets ceil(share) of its own (at most one per block; the largest
-    // groups shrink until everything fits the resident capacity); the
-    // others are packed, largest first, onto the least loaded of the
-    // remaining work-groups, one after another without barriers.
-    double wsum = 0;
-    for (double w : work) wsum += w;
-    const double target = wsum > 0 ? wsum / (double)cap : 1.0;
-    std::vector<int> gsz(count, 1);
-    for (int i = 0; i < count; ++i) {
-        const double blocks = std::ldexp(1.0, hs[i]->n - li[i]);
-        const double share = work[i] / target;
-        gsz[i] = share > 1.0 ? (int)std::min(std::ceil(share), blocks) : 1;
-    }
-    auto packing = [&](long *ded, long *bins, double *single_work, long *nsingle) {
-        *ded = 0;
-        *single_work = 0;
-        *nsingle = 0;
-        for (int i = 0; i < count; ++i) {
-            if (gsz[i] > 1) {
-                *ded += gsz[i];
-            } else {
-                *single_work += work[i];
-                *nsingle += 1;
-            }
+    // Chunks: an eighth of a work-group's share of its launch or a block,
+    // whichever is more (a chunk's own cost, the staging of its tables, is about
+    // a tenth of a block's; a work-group ends within one chunk of the others),
+    // the most expensive first.
+    std::vector<svp::BatchChunk> chunks;
+    std::vector<unsigned> chunk_end;
+    for (const std::vector<InstPass> &L : launches) {
+        double sum = 0;
+        for (const InstPass &x : L) sum += x.cost;
+        const double target = sum / (8.0 * (double)cap);
+        std::vector<std::pair<double, svp::BatchChunk>> cs;
+        for (const InstPass &x : L) {
+            const int k = (int)std::max(1.0, std::min(x.blocks, std::ceil(x.cost / target)));
+            for (int f = 0; f < k; ++f) cs.push_back({std::ceil((x.blocks - f) / k) * x.cost / x.blocks, {x.pass, x.logr, f, k}});
         }
-        *bins = *nsingle == 0 ? 0 : std::min(*nsingle, std::max(1L, (long)std::ceil(*single_work / target)));
-    };
-    long ded, bins, nsingle;
-    double single_work;
-    packing(&ded, &bins, &single_work, &nsingle);
-    while (ded + bins > cap) {
-        const int big = (int)(std::max_element(gsz.begin(), gsz.end()) - gsz.begin());
-        if (gsz[big] <= 1) break;
-        gsz[big] -= 1;
-        packing(&ded, &bins, &single_work, &nsingle);
+        std::stable_sort(cs.begin(), cs.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        for (const auto &c : cs) chunks.push_back(c.second);
+        chunk_end.push_back((unsigned)chunks.size());
     }
-    if (ded + bins > cap) bins = cap - ded;
-    if (nsingle > 0 && bins < 1) {
-        *sequential = true;
-        return nullptr;
-    }
-    std::vector<std::vector<std::pair<int, int>>> wg;  // per work-group: (instance, rank)
-    for (int i = 0; i < count; ++i) {
-        insts[i].group_size = gsz[i];
-        if (gsz[i] > 1)
-            for (int r = 0; r < gsz[i]; ++r) wg.push_back({{i, r}});
-    }
-    {
-        std::vector<int> order;
-        for (int i = 0; i < count; ++i)
-            if (gsz[i] == 1) order.push_back(i);
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
-        std::vector<double> load(bins, 0.0);
-        const size_t first = wg.size();
-        wg.resize(first + bins);
-        for (int i : order) {
-            const size_t b = (size_t)(std::min_element(load.begin(), load.end()) - load.begin());
-            load[b] += work[i];
-            wg[first + b].push_back({i, 0});
-        }
-    }
-    std::vector<int32_t> wg_off(1, 0);
-    std::vector<int32_t> jobs;  // int2 pairs
-    for (const auto &w : wg) {
-        for (const auto &j : w) {
-            jobs.push_back(j.first);
-            jobs.push_back(j.second);
-        }
-        wg_off.push_back((int32_t)(jobs.size() / 2));
-    }
-    // one device buffer: insts | wg_off | jobs | passes | ops | table | counters
-    BatchEntry *e = new (std::nothrow) BatchEntry();
+    // one device buffer: chunks | passes | ops | table | a counter per launch
+    std::shared_ptr<BatchEntry> e(new (std::nothrow) BatchEntry());
     if (!e) {
         *err = "host allocation failed";
         return nullptr;
     }
-    const size_t o_inst = 0, o_wg = align16(o_inst + insts.size() * sizeof(svp::BatchInst));
-    const size_t o_jobs = align16(o_wg + wg_off.size() * sizeof(int32_t));
-    const size_t o_pass = align16(o_jobs + jobs.size() * sizeof(int32_t));
+    const size_t o_chunk = 0, o_pass = align16(o_chunk + chunks.size() * sizeof(svp::BatchChunk));
     const size_t o_ops = align16(o_pass + passes.size() * sizeof(svp::BatchPass));
     const size_t o_tab = align16(o_ops + ops.size() * sizeof(svp::K2Op));
     const size_t o_ctr = align16(o_tab + table.size());
-    const size_t bytes = o_ctr + (size_t)(count + 1) * sizeof(unsigned);
+    const size_t bytes = o_ctr + (launches.size() + 1) * sizeof(unsigned);
     if (dev_alloc(&e->dbuf, bytes) != hipSuccess) {
-        delete e;
         *err = "batch buffer allocation failed";
         return nullptr;
     }
@@ -1884,21 +1837,13 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
     auto up = [&](size_t off, const void *src, size_t n) {
         if (he == hipSuccess && n) he = hipMemcpyAsync(d + off, src, n, hipMemcpyHostToDevice, st);
     };
-    up(o_inst, insts.data(), insts.size() * sizeof(svp::BatchInst));
-    up(o_wg, wg_off.data(), wg_off.size() * sizeof(int32_t));
-    up(o_jobs, jobs.data(), jobs.size() * sizeof(int32_t));
+    up(o_chunk, chunks.data(), chunks.size() * sizeof(svp::BatchChunk));
     up(o_pass, passes.data(), passes.size() * sizeof(svp::BatchPass));
     up(o_ops, ops.data(), ops.size() * sizeof(svp::K2Op));
     up(o_tab, table.data(), table.size());
     if (he == hipSuccess) he = hipStreamSynchronize(st);
-    e->ctrs = reinterpret_cast<unsigned *>(d + o_ctr);
     e->key = key;
-    e->dtype = dtype;
-    e->lmax = lmax_tile;
     e->count = count;
-    e->grid = (unsigned)wg.size();
-    e->threads = threads;
-    e->lds = lds;
     e->l = li;
     for (int i = 0; i < count; ++i) {
         e->l2p_after.push_back(plans[i].l2p_after);
@@ -1906,34 +1851,32 @@ BatchEntry *get_batch(sv_handle *hs, int count, const sv_gate *const *gates, con
     }
     // capture on a private stream (the handle's stream may be the legacy
     // default stream, which cannot be captured); the graph is then launched on
-    // the handle's stream. Counters and the error flag are cleared by a kernel.
+    // the handle's stream. The counters are cleared by a kernel.
     hipStream_t cap_st = nullptr;
     if (he == hipSuccess) he = hipStreamCreateWithFlags(&cap_st, hipStreamNonBlocking);
     if (he == hipSuccess) he = hipStreamBeginCapture(cap_st, hipStreamCaptureModeThreadLocal);
     if (he == hipSuccess) {
-        hipError_t h1 = svk::zero_u32(e->ctrs, (uint32_t)(count + 1), cap_st);
-        hipError_t h2 = svk::k6_batch(dtype, lmax_tile, e->grid, threads, lds,
-                                      reinterpret_cast<const svp::BatchInst *>(d + o_inst),
-                                      reinterpret_cast<const int32_t *>(d + o_wg), d + o_jobs,
-                                      reinterpret_cast<const svp::BatchPass *>(d + o_pass),
-                                      reinterpret_cast<const svp::K2Op *>(d + o_ops), e->ctrs,
-                                      reinterpret_cast<int *>(e->ctrs + count), 1u << 24, mfma, cap_st);
+        unsigned *ctrs = reinterpret_cast<unsigned *>(d + o_ctr);
+        hipError_t h1 = svk::zero_u32(ctrs, (uint32_t)launches.size() + 1, cap_st);
+        for (size_t p = 0; p < launches.size() && h1 == hipSuccess; ++p) {
+            const unsigned c0 = p == 0 ? 0u : chunk_end[p - 1], nc = chunk_end[p] - c0;
+            h1 = svk::k6_batch(dtype, lmax_tile, (unsigned)std::min<long>(cap, nc), threads, lds,
+                               reinterpret_cast<const svp::BatchPass *>(d + o_pass),
+                               reinterpret_cast<const svp::BatchChunk *>(d + o_chunk) + c0, nc,
+                               reinterpret_cast<const svp::K2Op *>(d + o_ops), ctrs + p, mfma, cap_st);
+        }
         he = hipStreamEndCapture(cap_st, &e->graph);
-        if (he == hipSuccess) he = h1 != hipSuccess ? h1 : h2;
+        if (he == hipSuccess) he = h1;
     }
     if (cap_st) hipStreamDestroy(cap_st);
     if (he == hipSuccess) he = hipGraphInstantiate(&e->exec, e->graph, nullptr, nullptr, 0);
     if (he != hipSuccess) {
         *err = std::string("batch graph: ") + hipGetErrorString(he);
-        delete e;
         return nullptr;
     }
     std::lock_guard<std::mutex> lk(g_batch_mu);
     g_batches.push_back(e);
-    while (g_batches.size() > 8) {
-        delete g_batches.front();
-        g_batches.erase(g_batches.begin());
-    }
+    if (g_batches.size() > 8) g_batches.erase(g_batches.begin());
     return e;
 }
 
@@ -1966,27 +1909,20 @@ sv_status sv_apply_batch(sv_handle *hs, int count, const sv_gate *const *gates, 
         return fail(SV_ERR_UNSUPPORTED, "batches are tuned with sv_tune_batch, not through the schedule");
     bool sequential = false;
     std::string err;
-    BatchEntry *e = get_batch(hs, count, gates, m, s, &sequential, &err);
+    std::shared_ptr<BatchEntry> e = get_batch(hs, count, gates, m, s, &sequential, &err);
     if (sequential) {
         for (int i = 0; i < count; ++i)
             if (sv_status st = sv_apply_circuit(hs[i], gates[i], m[i], s)) return st;
         return SV_OK;
     }
     if (!e) return fail(SV_ERR_DEVICE, err);
-    if (!g_err_host) {
-        void *p = nullptr;
-        if (hipHostMalloc(&p, sizeof(int), 0) != hipSuccess) return fail(SV_ERR_OUT_OF_MEMORY, "pinned flag");
-        g_err_host = static_cast<int *>(p);
-    }
     sv_handle h0 = hs[0];
     hipStream_t st = h0->stream;
     if (launch_fault()) return fail(SV_ERR_DEVICE, "injected launch failure");
     SV_HIP(hipEventRecord(h0->ev0, st), "hipEventRecord");
     SV_HIP(hipGraphLaunch(e->exec, st), "hipGraphLaunch");
     SV_HIP(hipEventRecord(h0->ev1, st), "hipEventRecord");
-    SV_HIP(hipMemcpyAsync(g_err_host, e->ctrs + count, sizeof(int), hipMemcpyDeviceToHost, st), "copy");
     SV_HIP(hipStreamSynchronize(st), "sync");
-    if (*g_err_host != 0) return fail(SV_ERR_DEVICE, "batch pass barrier did not complete (timed out)");
     float ms = 0.f;
     SV_HIP(hipEventElapsedTime(&ms, h0->ev0, h0->ev1), "hipEventElapsedTime");
     for (int i = 0; i < count; ++i) {

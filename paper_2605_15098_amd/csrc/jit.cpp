@@ -136,7 +136,7 @@ static std::string generate_pass(const svp::Step &s, const svp::Plan &plan, int 
             std::function<void(int, const std::string &)> visit = [&](int k, const std::string &tk) {
                 if ((rec->kmask >> k) & 1u) {
                     const bool q = (rec->qmask >> k) & 1u;
-                    o << "      k2_diag_apply(a[" << k << "], " << (q ? "true" : "false") << ", make_double2("
+                    o << "      k2_diag_apply(a[" << k << "], " << (q ? "true" : "false") << ", mk<C>("
                       << hexd(qt[2 * k]) << ", " << hexd(qt[2 * k + 1]) << "), " << (tk.empty() ? "false" : "true")
                       << ", " << (tk.empty() ? std::string("mk<C>(1.0, 0.0)") : tk) << ");\n";
                 }

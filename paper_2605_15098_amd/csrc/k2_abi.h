@@ -71,7 +71,8 @@ struct DiagGroup {
 // A run of diagonal gates as one multiply per register slot. Followed in the
 // table by ngroups DiagGroup records (sorted by the highest bit of rmask,
 // groups with rmask = 0 first) and then 2^r complex doubles Q[k], the
-// constant factor of register pattern k. Register slot k is multiplied (when
+// constant factor of register pattern k (for complex64 followed by the same in
+// single precision, which the interpreter reads). Register slot k is multiplied (when
 // k is in kmask) by F(k) = Q[k] * T(k) if k is in qmask, else T(k), where the
 // thread factor T(k) folds, in this order, the groups with rmask = 0 and then,
 // for each set bit b of k ascending, the groups whose highest rmask bit is b
@@ -83,7 +84,7 @@ struct DiagRun {
     uint32_t kmask;
     uint32_t qmask;
     int32_t ngroups;
-    int32_t pad;
+    int32_t same;       // 1: ngroups >= 1 and all groups have the same rmask
 };
 
 // Block-uniform factor: e^{2 pi i sum angle_j [base covers tmask_j]} with
@@ -161,22 +162,19 @@ constexpr int k2_canon_bit(int j, int l, int r)
     return j == 0 ? 0 : (l == r ? j : l - r - 1 + j);
 }
 
-// Batched passes (one persistent launch over many states). Instance i is
-// served by group_size work-groups (ranks 0 .. group_size-1), which run its
-// passes in order and meet at a counter barrier between passes.
-struct BatchInst {
-    void *S;             // the instance's state
-    int32_t npass;
-    int32_t pass_off;    // first BatchPass of this instance
-    int32_t logr;        // register tile (2^logr amplitudes per thread)
-    int32_t group_size;  // work-groups sharing the instance
-    int32_t ctr;         // barrier counter index (group_size > 1)
-    int32_t l;           // block qubits of its passes
-};
+// Batched passes: pass p of every instance that has one runs in one launch,
+// whose work-groups take chunks (blocks first, first + stride, ... of one
+// instance's pass) from a counter.
 struct BatchPass {
     K2Args args;         // args.table points to the batch table
+    void *S;             // the instance's state
     int32_t op_begin;    // first op in the batch op array
-    int32_t pad[3];
+    int32_t pad;
+};
+struct BatchChunk {
+    int32_t pass;        // index of the BatchPass
+    int32_t logr;        // register tile (2^logr amplitudes per thread)
+    int32_t first, stride;
 };
 
 }  // namespace svp

@@ -1,4 +1,4 @@
-// Device code shared by the compiled kernels (kernels.hip, block.hip) and the pass
+// Device code shared by the compiled kernels (kernels.hip, block.hip, batch.hip) and the pass
 // kernels generated at run time (jit.cpp): complex arithmetic, the block-pass
 // op handlers, the persistent block-pass skeleton and the op interpreter.
 // Every gate's arithmetic lives here once, so the plain sweep, the
@@ -176,8 +176,8 @@ __device__ __forceinline__ void lds_barrier()
 // The forms of cmad2 with zero halves keep its order of operations, so they
 // give its bits (24 qubits complex128, layers of RX and RY and CNOT: half of the pass
 // arithmetic is products with zero otherwise).
-template <int J, int R, typename C>
-__device__ __forceinline__ void k2_pairs(C *a, int kind, const double *v, bool tpred, int ckind, int cslot, int form)
+template <int J, int R, typename C, typename V>
+__device__ __forceinline__ void k2_pairs(C *a, int kind, V v, bool tpred, int ckind, int cslot, int form)
 {
     const C u00 = mk<C>(v[0], v[1]), u01 = mk<C>(v[2], v[3]);
     const C u10 = mk<C>(v[4], v[5]), u11 = mk<C>(v[6], v[7]);
@@ -230,7 +230,7 @@ struct K2Ctx {
     uint64_t base;
     uint32_t tloc;               // local index of the thread's slot-0 amplitude
     unsigned char *lds;          // block buffer for re-layouts
-    const double2 *ufac;         // block-uniform factors
+    const unsigned char *ufac;   // block-uniform factors in LDS (type C)
     const unsigned char *table;  // plan table
     const unsigned char *tabs;   // the pass's lane/wave factors in LDS (type C)
 };
@@ -249,9 +249,8 @@ __device__ __forceinline__ uint32_t drop_bit(uint32_t x, int b)
 //  - split = x < 32: slot s holds x in both layouts; round h writes and
 //    reads the registers whose slot-s bit is h (the first round's reads do
 //    not overwrite the registers the second round writes);
-//  - split = 32 + x: x is the thread-id bit p in both layouts; round h is
-//    done by the threads whose bit p is h (whole waves when p >= 6), all of
-//    their registers.
+//  - split = 32 + x: x is the thread-id bit p >= 6 in both layouts; round h is
+//    done by the waves whose bit p is h, all of their registers.
 template <int LOGR, typename C>
 __device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, const int *rb_new, int split)
 {
@@ -271,61 +270,56 @@ __device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, co
         tnew = insert0_32(tnew, __builtin_ctz(rmask));
         rmask &= rmask - 1u;
     }
-    if (split < 0) {
-        const uint32_t tsw = swz<C>(cx.tloc) * (uint32_t)sizeof(C);
+    // LDS offset of each slot bit, old and new layout (a block that moves in
+    // halves is stored without bit x). The swizzle is linear, so slot k's offset
+    // is the XOR over its bits: one instruction from a slot with one bit less,
+    // which is what the interpreter pays where a compiled pass has constants.
+    const int x = split < 0 ? -1 : (split & 31);
+    auto at = [&](uint32_t loc) -> uint32_t { return swz<C>(x >= 0 ? drop_bit(loc, x) : loc) * (uint32_t)sizeof(C); };
+    uint32_t oo[R], on[R];
+    oo[0] = on[0] = 0u;
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            uint32_t kp = 0;
-#pragma unroll
-            for (int j = 0; j < LOGR; ++j)
-                if ((k >> j) & 1) kp |= 1u << rb_old[j];
-            *reinterpret_cast<C *>(cx.lds + (tsw ^ (swz<C>(kp) * (uint32_t)sizeof(C)))) = a[k];
+    for (int k = 1; k < R; ++k) {
+        if ((k & (k - 1)) == 0) {
+            const int j = __builtin_ctz(k);
+            // (the slot that holds x adds nothing: its half is stored alone)
+            oo[k] = rb_old[j] == x ? 0u : at(1u << rb_old[j]);
+            on[k] = rb_new[j] == x ? 0u : at(1u << rb_new[j]);
+        } else {
+            oo[k] = oo[k & (k - 1)] ^ oo[k & -k];
+            on[k] = on[k & (k - 1)] ^ on[k & -k];
         }
+    }
+    const uint32_t tso = at(cx.tloc), tsn = at(tnew);
+    auto put = [&](int k) { *reinterpret_cast<C *>(cx.lds + (tso ^ oo[k])) = a[k]; };
+    auto get = [&](int k) { a[k] = *reinterpret_cast<const C *>(cx.lds + (tsn ^ on[k])); };
+    if (split < 0) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) put(k);
         lds_barrier();
         cx.tloc = tnew;
-        const uint32_t tsn = swz<C>(cx.tloc) * (uint32_t)sizeof(C);
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            uint32_t kp = 0;
-#pragma unroll
-            for (int j = 0; j < LOGR; ++j)
-                if ((k >> j) & 1) kp |= 1u << rb_new[j];
-            a[k] = *reinterpret_cast<const C *>(cx.lds + (tsn ^ (swz<C>(kp) * (uint32_t)sizeof(C))));
-        }
+        for (int k = 0; k < R; ++k) get(k);
         lds_barrier();
         return;
     }
     if (split >= 32) {
-        const int x = split - 32;
         uint32_t om = 0;
 #pragma unroll
         for (int j = 0; j < LOGR; ++j) om |= 1u << rb_old[j];
         const int p = x - __builtin_popcount(om & ((1u << x) - 1u));
-        const uint32_t mine = (cx.tid >> p) & 1u;
-        const uint32_t tso = swz<C>(drop_bit(cx.tloc, x)) * (uint32_t)sizeof(C);
-        const uint32_t tsn = swz<C>(drop_bit(tnew, x)) * (uint32_t)sizeof(C);
+        // (p >= 6: the same for the whole wave)
+        const uint32_t mine = (__builtin_amdgcn_readfirstlane(cx.tid) >> p) & 1u;
 #pragma unroll
         for (uint32_t h = 0; h < 2; ++h) {
             if (mine == h) {
 #pragma unroll
-                for (int k = 0; k < R; ++k) {
-                    uint32_t kp = 0;
-#pragma unroll
-                    for (int j = 0; j < LOGR; ++j)
-                        if ((k >> j) & 1) kp |= 1u << rb_old[j];
-                    *reinterpret_cast<C *>(cx.lds + (tso ^ (swz<C>(drop_bit(kp, x)) * (uint32_t)sizeof(C)))) = a[k];
-                }
+                for (int k = 0; k < R; ++k) put(k);
             }
             lds_barrier();
             if (mine == h) {
 #pragma unroll
-                for (int k = 0; k < R; ++k) {
-                    uint32_t kp = 0;
-#pragma unroll
-                    for (int j = 0; j < LOGR; ++j)
-                        if ((k >> j) & 1) kp |= 1u << rb_new[j];
-                    a[k] = *reinterpret_cast<const C *>(cx.lds + (tsn ^ (swz<C>(drop_bit(kp, x)) * (uint32_t)sizeof(C))));
-                }
+                for (int k = 0; k < R; ++k) get(k);
             }
             lds_barrier();
         }
@@ -336,29 +330,15 @@ __device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, co
 #pragma unroll
     for (int j = 0; j < LOGR; ++j)
         if (rb_old[j] == split) s = j;
-    const uint32_t tso = swz<C>(drop_bit(cx.tloc, split)) * (uint32_t)sizeof(C);
-    const uint32_t tsn = swz<C>(drop_bit(tnew, split)) * (uint32_t)sizeof(C);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if (((k >> s) & 1) != h) continue;
-            uint32_t kp = 0;
-#pragma unroll
-            for (int j = 0; j < LOGR; ++j)
-                if (j != s && ((k >> j) & 1)) kp |= 1u << rb_old[j];
-            *reinterpret_cast<C *>(cx.lds + (tso ^ (swz<C>(drop_bit(kp, split)) * (uint32_t)sizeof(C)))) = a[k];
-        }
+        for (int k = 0; k < R; ++k)
+            if (((k >> s) & 1) == h) put(k);
         lds_barrier();
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if (((k >> s) & 1) != h) continue;
-            uint32_t kp = 0;
-#pragma unroll
-            for (int j = 0; j < LOGR; ++j)
-                if (j != s && ((k >> j) & 1)) kp |= 1u << rb_new[j];
-            a[k] = *reinterpret_cast<const C *>(cx.lds + (tsn ^ (swz<C>(drop_bit(kp, split)) * (uint32_t)sizeof(C))));
-        }
+        for (int k = 0; k < R; ++k)
+            if (((k >> s) & 1) == h) get(k);
         lds_barrier();
     }
     cx.tloc = tnew;
@@ -509,11 +489,11 @@ __device__ __forceinline__ void k2_mfma(C *a, K2Ctx &cx, const int *rb, const in
     lds_barrier();
 }
 
-// Thread factor of a diagonal-run group: block-uniform factor (FP64, cast
-// once) times the wave and lane entries of the pass's factor table in LDS,
-// in the state's precision.
-template <typename C>
-__device__ __forceinline__ C k2_group_factor(const svp::DiagGroup &G, const K2Ctx &cx)
+// Thread factor of a diagonal-run group: block-uniform factor times the wave and
+// lane entries of the pass's factor table, all in LDS in the state's
+// precision.
+template <typename C, typename Group>
+__device__ __forceinline__ C k2_group_factor(const Group &G, const K2Ctx &cx)
 {
     // keeps the scheduler from starting many runs' factors at once, which
     // would raise register use past the two-work-groups-per-CU budget
@@ -521,10 +501,10 @@ __device__ __forceinline__ C k2_group_factor(const svp::DiagGroup &G, const K2Ct
     C f = mk<C>(1.0, 0.0);
     bool on = true;
     if (G.cond_kind == 1) on = (cx.base >> G.cond_bit) & 1ull;
-    else if (G.cond_kind == 2) on = (cx.tid >> G.cond_bit) & 1u;
+    else if (G.cond_kind == 2) on = (__builtin_amdgcn_readfirstlane(cx.tid) >> G.cond_bit) & 1u;  // (a wave bit)
     if (on) {
         const C *tab = reinterpret_cast<const C *>(cx.tabs);
-        if (G.uidx >= 0) f = mk<C>(cx.ufac[G.uidx].x, cx.ufac[G.uidx].y);
+        if (G.uidx >= 0) f = reinterpret_cast<const C *>(cx.ufac)[G.uidx];
         if (G.wave_off >= 0) f = cmul(f, tab[G.wave_off + (cx.tid >> 6)]);
         if (G.lane_off >= 0) f = cmul(f, tab[G.lane_off + (cx.tid & 63u)]);
     }
@@ -539,24 +519,52 @@ template <typename C> __device__ __forceinline__ C k2_fold(bool first, C T, C g)
 
 // Slot k's multiply of a diagonal run: F = Q[k] * T (or Q[k] when no group
 // covers k, or T without a constant), a[k] = F * a[k].
-template <typename C> __device__ __forceinline__ void k2_diag_apply(C &ak, bool with_q, double2 q, bool have_t, C T)
+template <typename C> __device__ __forceinline__ void k2_diag_apply(C &ak, bool with_q, C q, bool have_t, C T)
 {
-    const C qc = mk<C>(q.x, q.y);
-    const C F = with_q ? (have_t ? cmul(qc, T) : qc) : T;
+    const C F = with_q ? (have_t ? cmul(q, T) : q) : T;
     ak = cmul(F, ak);
 }
 
-// A diagonal run evaluated slot by slot (the interpreter): each slot folds
-// its groups in the record's canonical order (see DiagRun), recomputing the
-// group factors it needs.
+// A diagonal run read from its record (the interpreter), folding each slot's
+// groups in the record's canonical order (see DiagRun).
 template <int LOGR, typename C>
-__device__ __forceinline__ void k2_diagrun(C *a, const K2Ctx &cx, const svp::DiagRun *rec)
+__device__ __forceinline__ void k2_diagrun(C *a, const K2Ctx &cx, const unsigned char *recp)
 {
+    using T_ = decltype(C::x);
     constexpr int R = 1 << LOGR;
-    const svp::DiagGroup *gs = reinterpret_cast<const svp::DiagGroup *>(rec + 1);
+    const k2_const<svp::DiagRun> rec = as_const<svp::DiagRun>(recp);
     const int ng = rec->ngroups;
-    const double2 *qt = reinterpret_cast<const double2 *>(gs + ng);
     const uint32_t kmask = rec->kmask, qmask = rec->qmask;
+    const k2_const<svp::DiagGroup> gs = as_const<svp::DiagGroup>(recp + sizeof(svp::DiagRun));
+    // Q in the state's precision: converting it costs as much as the multiply
+    const unsigned char *qp = recp + sizeof(svp::DiagRun) + (size_t)ng * sizeof(svp::DiagGroup);
+    const k2_const<T_> qt = as_const<T_>(qp + (sizeof(T_) == 4 ? 16 * (size_t)R : 0));
+    auto q = [&](int k) {
+        C r;
+        r.x = qt[2 * k];
+        r.y = qt[2 * k + 1];
+        return r;
+    };
+    if (rec->same) {
+        // one register mask for all groups (a Hadamard's controlled phases in
+        // a phase estimation): one product serves every slot that covers it
+        const int rm = gs[0].rmask;
+        C T = k2_group_factor<C>(gs[0], cx);
+        for (int i = 1; i < ng; ++i) T = cmul(T, k2_group_factor<C>(gs[i], cx));
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            if (!((kmask >> k) & 1u)) continue;
+            const bool in = (rm & ~k) == 0;
+            if ((qmask >> k) & 1u) {
+                C F = q(k);
+                if (in) F = cmul(F, T);
+                a[k] = cmul(F, a[k]);
+            } else if (in) {
+                a[k] = cmul(T, a[k]);
+            }
+        }
+        return;
+    }
     // The groups are stored by ascending top register bit (rmask = 0 first),
     // so one walk over them in record order hands every slot its factors in
     // the order the record defines: a group whose top bit is not in k has
@@ -567,35 +575,41 @@ __device__ __forceinline__ void k2_diagrun(C *a, const K2Ctx &cx, const svp::Dia
         // levels that lie within k are exactly those within k - 2^b) and
         // folds only the groups of level b that lie within k.
         C T[R];
-        bool have[R];
+        uint32_t have = 0;
         T[0] = mk<C>(1.0, 0.0);
-        have[0] = false;
         int i = 0;
         for (; i < ng && gs[i].rmask == 0; ++i) {
-            T[0] = k2_fold(!have[0], T[0], k2_group_factor<C>(gs[i], cx));
-            have[0] = true;
+            T[0] = k2_fold(!have, T[0], k2_group_factor<C>(gs[i], cx));
+            have = 1u;
         }
 #pragma unroll
         for (int b = 0; b < LOGR; ++b) {
 #pragma unroll
-            for (int k = 1 << b; k < (2 << b); ++k) {
-                T[k] = T[k - (1 << b)];
-                have[k] = have[k - (1 << b)];
-            }
+            for (int k = 1 << b; k < (2 << b); ++k) T[k] = T[k - (1 << b)];
+            have |= have << (1 << b);
             for (; i < ng && (31 - __builtin_clz((uint32_t)gs[i].rmask)) == b; ++i) {
                 const int rm = gs[i].rmask;
                 const C f = k2_group_factor<C>(gs[i], cx);
 #pragma unroll
                 for (int k = 1 << b; k < (2 << b); ++k) {
                     if (rm & ~k) continue;
-                    T[k] = k2_fold(!have[k], T[k], f);
-                    have[k] = true;
+                    if ((have >> k) & 1u) T[k] = cmul(T[k], f);
+                    else T[k] = f;
+                    have |= 1u << k;
                 }
             }
         }
 #pragma unroll
-        for (int k = 0; k < R; ++k)
-            if ((kmask >> k) & 1u) k2_diag_apply(a[k], ((qmask >> k) & 1u) != 0, qt[k], have[k], T[k]);
+        for (int k = 0; k < R; ++k) {
+            if (!((kmask >> k) & 1u)) continue;
+            if ((qmask >> k) & 1u) {
+                C F = q(k);
+                if ((have >> k) & 1u) F = cmul(F, T[k]);
+                a[k] = cmul(F, a[k]);
+            } else {
+                a[k] = cmul(T[k], a[k]);
+            }
+        }
     } else {
         // larger tiles: slot by slot (the accumulators would not fit)
 #pragma unroll
@@ -608,7 +622,12 @@ __device__ __forceinline__ void k2_diagrun(C *a, const K2Ctx &cx, const svp::Dia
                 T = k2_fold(!have, T, k2_group_factor<C>(gs[i], cx));
                 have = true;
             }
-            k2_diag_apply(a[k], ((qmask >> k) & 1u) != 0, qt[k], have, T);
+            if ((qmask >> k) & 1u) {
+                const C F = have ? cmul(q(k), T) : q(k);
+                a[k] = cmul(F, a[k]);
+            } else {
+                a[k] = cmul(T, a[k]);
+            }
         }
     }
 }
@@ -759,8 +778,8 @@ __device__ __forceinline__ void k2_store(const C *a, C *__restrict__ S, uint64_t
 // block; PF = 0 does not prefetch: the next block is loaded after the store,
 // for passes that keep two work-groups on a CU (half the registers each) and
 // let one compute while the other waits.
-template <typename T, int LOGR, bool V2, int PF, class Prog>
-__device__ __forceinline__ void k2_body(typename CT<T>::type *__restrict__ S, const svp::K2Args &args,
+template <typename T, int LOGR, bool V2, int PF, class Prog, class Args>
+__device__ __forceinline__ void k2_body(typename CT<T>::type *__restrict__ S, const Args &args,
                                         unsigned char *lds, const Prog &prog, uint64_t first, uint64_t stride)
 {
     using C = typename CT<T>::type;
@@ -777,7 +796,7 @@ __device__ __forceinline__ void k2_body(typename CT<T>::type *__restrict__ S, co
     constexpr bool vec2 = V2;
     // (offsets read as wave-uniform values: they stay in scalar registers)
     const svp::K2Lds L = svp::k2_lds_layout(l, (int)sizeof(C), args.nug, args.tab_count, args.nut, args.half_lds);
-    double2 *ufac = reinterpret_cast<double2 *>(lds + __builtin_amdgcn_readfirstlane(L.ufac));
+    C *ufac = reinterpret_cast<C *>(lds + __builtin_amdgcn_readfirstlane(L.ufac));
     C *tabs = reinterpret_cast<C *>(lds + __builtin_amdgcn_readfirstlane(L.tabs));
     svp::UTerm *uterm = reinterpret_cast<svp::UTerm *>(lds + __builtin_amdgcn_readfirstlane(L.uterm));
     svp::UGroup *ugrp = reinterpret_cast<svp::UGroup *>(lds + __builtin_amdgcn_readfirstlane(L.ugrp));
@@ -848,14 +867,17 @@ __device__ __forceinline__ void k2_body(typename CT<T>::type *__restrict__ S, co
                         if ((base & tm[j].tmask) == tm[j].tmask) acc += tm[j].angle;
                     float sn, cs;
                     sincospif(ldexpf((float)(int32_t)(acc >> 32), -31), &sn, &cs);
-                    ufac[g] = make_double2(cs, sn);
+                    C f;
+                    f.x = cs;
+                    f.y = sn;
+                    ufac[g] = f;
                 } else {
                     // complex128: product of the covered terms' FP64
                     // factors (no transcendental in the block loop)
                     double2 f = make_double2(1.0, 0.0);
                     for (int j = 0; j < ugrp[g].nterms; ++j)
                         if ((base & tm[j].tmask) == tm[j].tmask) f = cmul(f, make_double2(tm[j].re, tm[j].im));
-                    ufac[g] = f;
+                    ufac[g] = mk<C>(f.x, f.y);
                 }
             }
             lds_barrier();
@@ -872,7 +894,7 @@ __device__ __forceinline__ void k2_body(typename CT<T>::type *__restrict__ S, co
         const uint32_t tloc0 = tb == 0 ? 0u
                                        : ((tid_b & ((1u << (tb - 1)) - 1u)) << 1) |
                                              (((tid_b >> (tb - 1)) & 1u) << (l - 1));
-        K2Ctx cx{tid_b, base, tloc0, lds, ufac, args.table, reinterpret_cast<const unsigned char *>(tabs)};
+        K2Ctx cx{tid_b, base, tloc0, lds, reinterpret_cast<const unsigned char *>(ufac), args.table, reinterpret_cast<const unsigned char *>(tabs)};
         prog.template run<T, LOGR>(a, cx);
 
         // the program ends in the canonical layout. The thread's address bits
@@ -897,8 +919,8 @@ __device__ __forceinline__ void k2_body(typename CT<T>::type *__restrict__ S, co
 }
 
 // k2_body with the access width chosen once, outside the block loop.
-template <typename T, int LOGR, class Prog, int PF = 1>
-__device__ __forceinline__ void k2_body_any(typename CT<T>::type *__restrict__ S, const svp::K2Args &args,
+template <typename T, int LOGR, class Prog, int PF = 1, class Args>
+__device__ __forceinline__ void k2_body_any(typename CT<T>::type *__restrict__ S, const Args &args,
                                             unsigned char *lds, const Prog &prog, uint64_t first, uint64_t stride)
 {
     if (args.vec2) k2_body<T, LOGR, true, PF>(S, args, lds, prog, first, stride);
@@ -907,12 +929,19 @@ __device__ __forceinline__ void k2_body_any(typename CT<T>::type *__restrict__ S
 
 // ------------------------------------------------------------ interpreter
 
+template <int V> struct K2Int {
+    static constexpr int value = V;
+};
+
 // Runs the op list of a pass (ops[0..nops)) on one block. MFMA selects the
 // build that also runs matrix-core windows: their registers would otherwise
-// weigh on every program the interpreter runs.
+// weigh on every program the interpreter runs. Ops and records are read
+// through the constant address space: by plain pointers the compiler cannot
+// rule out that a block's stores changed them, and fetches every field with a
+// vector load that also waits for the memory traffic of the block.
 template <bool MFMA>
 struct K2Interp {
-    const svp::K2Op *__restrict__ ops;
+    k2_const<svp::K2Op> ops;
     int nops;
     int l;
 
@@ -926,7 +955,7 @@ struct K2Interp {
 #pragma unroll
         for (int j = 1; j < LOGR; ++j) rb[j] = svp::k2_canon_bit(j, l, LOGR);
         for (int oi = 0; oi < nops; ++oi) {
-            const svp::K2Op &op = ops[oi];
+            const auto &op = ops[oi];
             const int kind = op.kind;
             if (kind == svp::K2_HU) {
                 switch (op.a) {
@@ -938,7 +967,7 @@ struct K2Interp {
                 default: break;
                 }
             } else if (kind == svp::K2_DIAGRUN) {
-                k2_diagrun<LOGR>(a, cx, reinterpret_cast<const svp::DiagRun *>(cx.table + op.a));
+                k2_diagrun<LOGR>(a, cx, cx.table + op.a);
             } else if (kind == svp::K2_LAYOUT) {
                 int nrb[LOGR];
 #pragma unroll
@@ -962,18 +991,32 @@ struct K2Interp {
                 k2_diag<R>(a, cx, op.a, op.b, op.c, (uint32_t)op.m0, op.m1, mk<C>(op.v[0], op.v[1]),
                            mk<C>(op.v[2], op.v[3]));
             } else {
-                const int ckind = op.b;
-                const bool tpred = (ckind == svp::CK_MEM) ? code_bit(cx.tloc, cx.base, op.c) : true;
-                const int cslot = op.c;
-                const int form = (int)op.m0;
-                switch (op.a) {
-                case 0: k2_pairs<0, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
-                case 1: if constexpr (LOGR > 1) k2_pairs<1, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
-                case 2: if constexpr (LOGR > 2) k2_pairs<2, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
-                case 3: if constexpr (LOGR > 3) k2_pairs<3, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
-                case 4: if constexpr (LOGR > 4) k2_pairs<4, R>(a, kind, op.v, tpred, ckind, cslot, form); break;
-                default: break;
-                }
+                // the kind, the form and the control's kind picked once per op, not
+                // per pair of slots
+                const bool mem = op.b == svp::CK_MEM;
+                const bool tpred = mem ? code_bit(cx.tloc, cx.base, op.c) : true;
+                const int ckind = op.b, cslot = op.c, slot = op.a;
+                const k2_const<double> v = &op.v[0];
+                auto on_slot = [&](auto kind_c, auto form_c, bool pred) {
+                    constexpr int K = decltype(kind_c)::value, F = decltype(form_c)::value;
+                    switch (slot) {
+                    case 0: k2_pairs<0, R>(a, K, v, pred, ckind, cslot, F); break;
+                    case 1: if constexpr (LOGR > 1) k2_pairs<1, R>(a, K, v, pred, ckind, cslot, F); break;
+                    case 2: if constexpr (LOGR > 2) k2_pairs<2, R>(a, K, v, pred, ckind, cslot, F); break;
+                    case 3: if constexpr (LOGR > 3) k2_pairs<3, R>(a, K, v, pred, ckind, cslot, F); break;
+                    case 4: if constexpr (LOGR > 4) k2_pairs<4, R>(a, K, v, pred, ckind, cslot, F); break;
+                    default: break;
+                    }
+                };
+                auto on_pred = [&](auto kind_c, auto form_c) {
+                    if (mem) on_slot(kind_c, form_c, tpred);
+                    else on_slot(kind_c, form_c, true);
+                };
+                if (kind == svp::K2_H) on_pred(K2Int<svp::K2_H>{}, K2Int<0>{});
+                else if (kind == svp::K2_X) on_pred(K2Int<svp::K2_X>{}, K2Int<0>{});
+                else if (op.m0 == svp::DF_REAL) on_pred(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_REAL>{});
+                else if (op.m0 == svp::DF_CROSS) on_pred(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_CROSS>{});
+                else on_pred(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_FULL>{});
             }
         }
     }

@@ -1,4 +1,4 @@
-// Host-side launchers of the gfx950 kernels (kernels.hip, block.hip, readout.hip).
+// Host-side launchers of the gfx950 kernels (kernels.hip, block.hip, batch.hip, readout.hip).
 // Every launcher enqueues on `stream` and returns the hipError_t of the
 // launch (hipSuccess on success).
 #pragma once
@@ -27,17 +27,14 @@ hipError_t init_zero_state(void *S, int n, int dtype, hipStream_t st);
 bool plain_storage(int n, int dtype);
 hipError_t to_storage_order(void *S, int n, int dtype, hipStream_t st);
 
-// Batched passes: see k6_batch_kernel. grid must not exceed the resident
-// capacity (k6_occupancy work-groups per CU times the CU count) so that the
-// work-groups of one instance can wait for each other.
-// lmax: the largest register tile of any instance (3..5; selects the
-// build); mfma: some pass runs matrix-core windows. jobs: int2 (instance,
-// rank) records, work-group w running wg_off[w] .. wg_off[w+1]-1.
+// Batched passes: see k6_batch_kernel. lmax: the largest register tile of any
+// chunk (3..5; selects the build); mfma: some pass runs matrix-core windows.
+// ctr must be zero when the launch starts.
 int k6_max_threads(int dtype, int lmax);
 int k6_occupancy(int dtype, int lmax, unsigned threads, size_t lds, bool mfma);
-hipError_t k6_batch(int dtype, int lmax, unsigned grid, unsigned threads, size_t lds, const svp::BatchInst *insts,
-                    const int32_t *wg_off, const void *jobs, const svp::BatchPass *passes, const svp::K2Op *ops,
-                    unsigned *ctrs, int *err, unsigned limit, bool mfma, hipStream_t st);
+hipError_t k6_batch(int dtype, int lmax, unsigned grid, unsigned threads, size_t lds, const svp::BatchPass *passes,
+                    const svp::BatchChunk *chunks, unsigned nchunks, const svp::K2Op *ops, unsigned *ctr, bool mfma,
+                    hipStream_t st);
 hipError_t zero_u32(unsigned *p, uint32_t n, hipStream_t st);
 hipError_t k1_gate(void *S, int n, int dtype, const svp::MGate &g, hipStream_t st);
 // A plain circuit on a state of at most k1_small_max qubits in one launch:

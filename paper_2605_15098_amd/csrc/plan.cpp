@@ -324,13 +324,21 @@ struct Builder {
         if (head.kmask == 0) return;
         std::vector<double> q(2 * qang.size());
         for (size_t k = 0; k < qang.size(); ++k) cexp(qang[k], &q[2 * k]);
-        std::vector<uint8_t> blob(sizeof(DiagRun) + recs.size() * sizeof(DiagGroup) + q.size() * sizeof(double));
+        head.same = recs.empty() ? 0 : 1;
+        for (const DiagGroup &d : recs)
+            if (d.rmask != recs[0].rmask) head.same = 0;
+        std::vector<float> qf(cfg.dtype == 0 ? q.size() : 0);
+        for (size_t k = 0; k < qf.size(); ++k) qf[k] = (float)q[k];
+        std::vector<uint8_t> blob(sizeof(DiagRun) + recs.size() * sizeof(DiagGroup) + q.size() * sizeof(double) +
+                                  qf.size() * sizeof(float));
         uint8_t *w = blob.data();
         std::memcpy(w, &head, sizeof(DiagRun));
         w += sizeof(DiagRun);
         if (!recs.empty()) std::memcpy(w, recs.data(), recs.size() * sizeof(DiagGroup));
         w += recs.size() * sizeof(DiagGroup);
         std::memcpy(w, q.data(), q.size() * sizeof(double));
+        w += q.size() * sizeof(double);
+        if (!qf.empty()) std::memcpy(w, qf.data(), qf.size() * sizeof(float));
         K2Op op{};
         op.kind = K2_DIAGRUN;
         op.a = table_put(blob.data(), blob.size());
@@ -433,8 +441,7 @@ struct Builder {
                 if (((om | nm) >> x) & 1u) continue;
                 const uint32_t below = (1u << x) - 1u;
                 const int po = x - __builtin_popcount(om & below), pn = x - __builtin_popcount(nm & below);
-                // a lane bit splits within waves: only blocks of one wave or less
-                if (po == pn && (po >= 6 || l - r <= 6)) return 32 + x;
+                if (po == pn && po >= 6) return 32 + x;  // (a lane bit would split within waves)
             }
             return -1;
         };
@@ -1079,10 +1086,14 @@ std::string make_plan(const PlanConfig &cfg, const RawGate *gates, size_t m,
     if (l > max_block_qubits(cfg.dtype)) return "block_qubits above the on-chip maximum";
     // the default schedule as a whole: block, tile and pins by size
     const bool by_size = cfg.policy == 2 && cfg.remap == 0 && cfg.l <= 0 && cfg.logr <= 0 && cfg.pin_low < 0;
+    const bool by_pins = by_size || (cfg.policy == 2 && cfg.remap == 0 && cfg.auto_pins && cfg.pin_low < 0);
     AutoBlock ab{};
     if (by_size) {
         ab = auto_block(cfg.dtype, n);
         l = ab.l;
+    } else if (by_pins) {
+        const int p = default_pin_qubits(cfg.dtype);
+        ab = {l, 0, 3, {p, p - 1, p - 2}, {1.0, 1.1, 1.35}};
     }
     b.l = l;
     b.logr = by_size ? ab.logr : std::min(cfg.logr > 0 ? cfg.logr : default_reg_qubits(cfg.dtype), l);
@@ -1121,7 +1132,7 @@ std::string make_plan(const PlanConfig &cfg, const RawGate *gates, size_t m,
         GraphSchedule graph(cfg, gates, m, l2p);
         int64_t swaps = 0;
         std::vector<GraphSchedule::Pass> passes;
-        if (by_size) {
+        if (by_pins) {
             double best = 0.0;
             for (int k = 0; k < ab.npins; ++k) {
                 const int p = std::max(0, std::min(ab.pins[k], l - 1));

@@ -81,6 +81,8 @@ struct PlanConfig {
     int remap = 0;            // 0 virtual, 1 explicit
     int diag_free = 0;        // diagonal gates never force a SWAP
     int pin_low = -1;         // low memory bits kept in every block (-1 = auto)
+    int auto_pins = 0;        // pin_low < 0 with explicit sizes: fewer pins than the
+                              // default where that saves more passes than it costs
     int fuse_k = 1;           // 0: one op per gate; 1: diagonal runs combined,
                               // Hadamard normalization deferred
     int half_lds = 1;         // re-layouts in two halves: 0 never, 1 for blocks
