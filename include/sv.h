@@ -127,8 +127,9 @@ typedef struct {
                              (14 for complex64, 13 for complex128; with
                              SV_SWAP_GRAPH and block_qubits, reg_qubits and
                              pin_qubits all 0 the three are chosen by the
-                             state's size: smaller blocks and tiles below 23
-                             (22) qubits, and the pins that cost least)      */
+                             state's size: in complex128 smaller blocks and
+                             tiles below 22 qubits, and the pins that cost
+                             least, in complex64 from 24 qubits on)          */
     int32_t outer_qubits; /* l2 (0 = off): outer tier. Consecutive block
                              passes whose local qubits together number at
                              most l2 run outer block by outer block (2^l2

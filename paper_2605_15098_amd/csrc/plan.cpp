@@ -1002,14 +1002,16 @@ private:
 };
 
 // Blocks of the default schedule, by size. A pass of a large state streams
-// HBM and wants the largest block (fewest passes); below about 2^21
-// amplitudes there are fewer of those than CUs and a pass takes as long as one
-// work-group needs for one block, so smaller blocks with fewer amplitudes per
-// thread are faster although a circuit may need a pass more. Device us, the
-// largest block -> this: complex64 phase estimation 17 qubits 33.9 -> 21.5, 20
-// qubits 44.7 -> 31.6, 200 random gates on 17 qubits 91.9 -> 49.7, 22 qubits 128
-// -> 116; complex128 phase estimation 16 qubits 37.6 -> 21.1, 20 qubits 59.5 ->
-// 42.6, 200 random gates on 18 qubits 115 -> 59.
+// HBM and wants the largest block (fewest passes). Below about 2^21 amplitudes
+// there are fewer of those than CUs and a pass takes as long as one
+// work-group needs for one block, so in complex128 small states take smaller
+// blocks with fewer amplitudes per thread, although a circuit may need a pass
+// more. Device us, the largest block -> this: phase estimation 16 qubits 37.6 ->
+// 21.1, 20 qubits 59.5 -> 42.6, 200 random gates on 18 qubits 115 -> 59.
+// complex64 keeps the largest block and its longest runs up to 23 qubits: the
+// same grouping of the diagonal gates rounds the same, and readouts are in
+// double precision, where another grouping shows (smaller blocks measured 33.9 ->
+// 21.5 at 17 qubits, 44.7 -> 31.6 at 20).
 // Fewer pinned low qubits leave more free ones, so maybe a pass less, at
 // shorter runs: cost[] is what a pass with pins[] costs relative to the longest
 // runs (measured at 22-30 qubits: complex64 128-byte runs 1.03-1.08, 64-byte
@@ -1027,8 +1029,7 @@ AutoBlock auto_block(int dtype, int n)
 {
     AutoBlock b;
     if (dtype == 0) {
-        if (n <= 20) b = {12, 3, 2, {4, 3}, {1.0, 1.15}};
-        else if (n <= 22) b = {13, 4, 2, {4, 3}, {1.0, 1.2}};
+        if (n <= 23) b = {14, 5, 1, {5}, {1.0}};
         else b = {14, 5, 3, {5, 4, 3}, {1.0, 1.06, 1.3}};
     } else {
         if (n <= 18) b = {10, 2, 2, {3, 2}, {1.0, 1.05}};
