@@ -43,7 +43,20 @@ enum K2Kind {
 // Form of a dense 2x2 matrix: general; real (RY); real diagonal and imaginary
 // off-diagonal (RX). The last two take half the arithmetic: the terms left out
 // are products with zero, so finite amplitudes get the same bits.
-enum DenseForm { DF_FULL = 0, DF_REAL = 1, DF_CROSS = 2 };
+// The other four are rotations taken out of their larger entry m (the pass's
+// K2_SCALE puts the product of all m back), so that one fused multiply-add per
+// component is left of each product: v is U / m, with ones on the diagonal (_D, m
+// = cos) or off it (_O, m = sin). RY-like: [1 q; -q 1], [k -1; 1 k]; RX-like:
+// [1 iq; iq 1], [k i; i k]; uncontrolled only.
+enum DenseForm {
+    DF_FULL = 0,
+    DF_REAL = 1,
+    DF_CROSS = 2,
+    DF_RY_D = 3,
+    DF_RY_O = 4,
+    DF_RX_D = 5,
+    DF_RX_O = 6
+};
 // Control of a dense op: none, a register slot, or a bit code (0..l-1 =
 // local bit tested on the thread's local index, 64 + p = memory bit p of the
 // block base).

@@ -175,7 +175,10 @@ __device__ __forceinline__ void lds_barrier()
 // by another slot (ckind CK_SLOT) or a per-thread predicate (tpred).
 // The forms of cmad2 with zero halves keep its order of operations, so they
 // give its bits (24 qubits complex128, layers of RX and RY and CNOT: half of the pass
-// arithmetic is products with zero otherwise).
+// arithmetic is products with zero otherwise). The rotations out of their
+// larger entry halve it again: such passes are bound by vector instructions
+// (25 qubits complex64, 180 rotations a pass: 762 per amplitude, 488 us of
+// which the memory traffic needs 107).
 template <int J, int R, typename C, typename V>
 __device__ __forceinline__ void k2_pairs(C *a, int kind, V v, bool tpred, int ckind, int cslot, int form)
 {
@@ -197,6 +200,26 @@ __device__ __forceinline__ void k2_pairs(C *a, int kind, V v, bool tpred, int ck
         } else if (form == svp::DF_REAL) {
             nx = cmad2_rr(u00.x, x, u01.x, y);
             ny = cmad2_rr(u10.x, x, u11.x, y);
+        } else if (form == svp::DF_RY_D) {
+            nx.x = xfma(u01.x, y.x, x.x);
+            nx.y = xfma(u01.x, y.y, x.y);
+            ny.x = xfma(-u01.x, x.x, y.x);
+            ny.y = xfma(-u01.x, x.y, y.y);
+        } else if (form == svp::DF_RY_O) {
+            nx.x = xfma(u00.x, x.x, -y.x);
+            nx.y = xfma(u00.x, x.y, -y.y);
+            ny.x = xfma(u00.x, y.x, x.x);
+            ny.y = xfma(u00.x, y.y, x.y);
+        } else if (form == svp::DF_RX_D) {
+            nx.x = xfma(-u01.y, y.y, x.x);
+            nx.y = xfma(u01.y, y.x, x.y);
+            ny.x = xfma(-u01.y, x.y, y.x);
+            ny.y = xfma(u01.y, x.x, y.y);
+        } else if (form == svp::DF_RX_O) {
+            nx.x = xfma(u00.x, x.x, -y.y);
+            nx.y = xfma(u00.x, x.y, y.x);
+            ny.x = xfma(u00.x, y.x, -x.y);
+            ny.y = xfma(u00.x, y.y, x.x);
         } else if (form == svp::DF_CROSS) {
             nx = cmad2_ri(u00.x, x, u01.y, y);
             ny = cmad2_ir(u10.y, x, u11.x, y);
@@ -1016,6 +1039,10 @@ struct K2Interp {
                 else if (kind == svp::K2_X) on_pred(K2Int<svp::K2_X>{}, K2Int<0>{});
                 else if (op.m0 == svp::DF_REAL) on_pred(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_REAL>{});
                 else if (op.m0 == svp::DF_CROSS) on_pred(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_CROSS>{});
+                else if (op.m0 == svp::DF_RY_D) on_slot(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_RY_D>{}, true);
+                else if (op.m0 == svp::DF_RY_O) on_slot(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_RY_O>{}, true);
+                else if (op.m0 == svp::DF_RX_D) on_slot(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_RX_D>{}, true);
+                else if (op.m0 == svp::DF_RX_O) on_slot(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_RX_O>{}, true);
                 else on_pred(K2Int<svp::K2_DENSE>{}, K2Int<svp::DF_FULL>{});
             }
         }

@@ -353,6 +353,30 @@ struct Builder {
         return DF_FULL;
     }
 
+    // An RX- or RY-like rotation taken out of its larger entry: v = U / m, the
+    // form (DF_RY_D ..) and m; false if u is not one. The ones are exact, and the
+    // other entry is at most 1, so each product rounds once instead of twice.
+    static bool rotation_form(const double *u, double *v, uint64_t *form, double *m)
+    {
+        const uint64_t f = dense_form(u);
+        double c, s;  // the entry on the diagonal, the one off it
+        if (f == DF_REAL && u[0] == u[6] && u[2] == -u[4]) {
+            c = u[0];
+            s = u[4];
+        } else if (f == DF_CROSS && u[0] == u[6] && u[3] == u[5]) {
+            c = u[0];
+            s = u[3];
+        } else {
+            return false;
+        }
+        if (!(std::fabs(c * c + s * s - 1.0) < 1e-6)) return false;
+        const bool diag = std::fabs(c) >= std::fabs(s);
+        *m = diag ? c : s;
+        for (int k = 0; k < 8; ++k) v[k] = u[k] / *m;
+        *form = f == DF_REAL ? (diag ? DF_RY_D : DF_RY_O) : (diag ? DF_RX_D : DF_RX_O);
+        return true;
+    }
+
     // LDS of one work-group on gfx950.
     static constexpr uint32_t kLdsLimit = 160 * 1024;
     // blocks above this many bytes stage half at a time (one 2^14 complex64
@@ -727,7 +751,20 @@ struct Builder {
             plan.ops.push_back(op);
             plan.stats.fused += (int64_t)wg.size();
         };
-        int hscale = 0;  // unnormalized Hadamards applied in this pass
+        // unnormalized gates of this pass: Hadamards, and the product of the
+        // rotations' entries taken out; growth: log2 of the norm they leave
+        int hscale = 0;
+        double rscale = 1.0, growth = 0.0;
+        auto put_scale = [&]() {
+            if (hscale == 0 && rscale == 1.0) return;
+            K2Op op{};
+            op.kind = K2_SCALE;
+            op.v[0] = rscale * std::ldexp(1.0, -(hscale / 2)) * ((hscale & 1) ? 0.70710678118654752440 : 1.0);
+            plan.ops.push_back(op);
+            hscale = 0;
+            rscale = 1.0;
+            growth = 0.0;
+        };
         const int begin = (int)plan.ops.size();
         for (size_t i = 0; i < items.size(); ++i) {
             if (items[i].window) {
@@ -770,6 +807,7 @@ struct Builder {
                 if (combine && op.kind == K2_H) {
                     op.kind = K2_HU;
                     ++hscale;
+                    growth += 0.5;
                 }
             } else {
                 const int lc = rank[g.c];
@@ -778,16 +816,21 @@ struct Builder {
                 else { op.b = CK_MEM; op.c = code_of(g.c); }
             }
             for (int k = 0; k < 8; ++k) op.v[k] = g.u[k];
-            if (op.kind == K2_DENSE) op.m0 = dense_form(g.u);
+            if (op.kind == K2_DENSE) {
+                double m;
+                if (combine && op.b == CK_NONE && rotation_form(g.u, op.v, &op.m0, &m)) {
+                    rscale *= m;
+                    growth -= std::log2(std::fabs(m));
+                } else {
+                    op.m0 = dense_form(g.u);
+                }
+            }
             plan.ops.push_back(op);
+            // far from FP32's largest exponent, whatever the pass's length
+            if (growth > 60.0) put_scale();
         }
         flush_diag();
-        if (hscale > 0) {
-            K2Op op{};
-            op.kind = K2_SCALE;
-            op.v[0] = std::ldexp(1.0, -(hscale / 2)) * ((hscale & 1) ? 0.70710678118654752440 : 1.0);
-            plan.ops.push_back(op);
-        }
+        put_scale();
         emit_fixed(canon);
         Step s;
         s.kind = ST_K2;
