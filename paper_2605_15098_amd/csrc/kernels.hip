@@ -197,22 +197,71 @@ hipError_t k1_gate(void *S, int n, int dtype, const svp::MGate &g, hipStream_t s
 // after each, with k1_pair_kernel's and k1_diag_kernel's arithmetic (the same
 // bits). A launch per gate is bound by the launches: 3.2 us each against less
 // than a microsecond of work on up to 2^14 amplitudes (10 qubits complex128,
-// 64 gates of a phase estimation: 205 us in launches). ops: K2_PHASE /
-// K2_DIAG / K2_H / K2_X / K2_DENSE records with a: target, b: control or -1, v:
-// the matrix (uniform, read through the scalar unit).
-template <typename C>
+// 64 gates of a phase estimation: 205 us in launches). What is left is each wave's
+// own instructions, a thousand cycles a gate. So a thread has as few amplitudes
+// as there are threads for (PER, 0: any number), consecutive diagonal gates
+// keep them in registers, without LDS and barriers between the gates (for PER
+// = 0 their tests of every amplitude cost more: a controlled phase touches a
+// quarter), and the scalar cache has the records before the first gate needs
+// them. us with reset, export and readout of a phase estimation, before these -> now: 10
+// qubits complex64 72 -> 62, 12 qubits 106 -> 81, 14 qubits 238 -> 205.
+// ops: K2_PHASE / K2_DIAG / K2_H / K2_X / K2_DENSE records with a: target, b:
+// control or -1, v: the matrix.
+template <typename C, int PER>
 __global__ void __launch_bounds__(1024) k1_small_kernel(C *__restrict__ S, int n, const svp::K2Op *ops, int nops)
 {
-    extern __shared__ unsigned char small_lds[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char small_lds[];
     C *st = reinterpret_cast<C *>(small_lds);
-    const uint32_t N = 1u << n, nt = blockDim.x;
-    for (uint32_t i = threadIdx.x; i < N; i += nt) st[i] = S[i];
+    const uint32_t N = 1u << n, nt = blockDim.x, tid = threadIdx.x;
+    const k2_const<svp::K2Op> op = as_const<svp::K2Op>(ops);
+    auto diagonal = [&](int g) { return op[g].kind == svp::K2_PHASE || op[g].kind == svp::K2_DIAG; };
+    {
+        // one word of each 64-byte line of the first records (the scalar cache
+        // is 16 KiB), eight lines in flight
+        const int lines = min(nops, 128) * (int)sizeof(svp::K2Op) / 64;
+        const k2_const<int32_t> w = as_const<int32_t>(ops);
+        for (int i = 0; i + 8 <= lines; i += 8) {
+            int32_t x = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x ^= w[(i + k) * 16];
+            asm volatile("" ::"s"(x));
+        }
+    }
+    for (uint32_t i = tid; i < N; i += nt) st[i] = S[i];
     __syncthreads();
-    k2_const<int32_t> op = as_const<int32_t>(ops);
-    for (int g = 0; g < nops; ++g, op += (int)(sizeof(svp::K2Op) / 4)) {
-        const int kind = op[0], t = op[1], c = op[2];
-        const k2_const<double> v = (k2_const<double>)(op + 8);
+    for (int g = 0; g < nops;) {
+        const int t = op[g].a, c = op[g].b, kind = op[g].kind;
+        const k2_const<double> v = &op[g].v[0];
         if (kind == svp::K2_PHASE || kind == svp::K2_DIAG) {
+            if constexpr (PER > 0) {
+                C a[PER];
+#pragma unroll
+                for (int k = 0; k < PER; ++k) a[k] = st[tid + k * nt];
+                do {
+                    const int gt = op[g].a, gc = op[g].b;
+                    const uint32_t cb = gc >= 0 ? 1u << gc : 0u, tb = 1u << gt;
+                    const k2_const<double> d = &op[g].v[0];
+                    if (op[g].kind == svp::K2_PHASE) {
+                        const C d1 = mk<C>(d[6], d[7]);
+                        const uint32_t ones = cb | tb;
+#pragma unroll
+                        for (int k = 0; k < PER; ++k)
+                            if (((tid + k * nt) & ones) == ones) a[k] = cmul(d1, a[k]);
+                    } else {
+                        const C d0 = mk<C>(d[0], d[1]), d1 = mk<C>(d[6], d[7]);
+#pragma unroll
+                        for (int k = 0; k < PER; ++k) {
+                            const uint32_t j = tid + k * nt;
+                            if ((j & cb) == cb) a[k] = cmul(csel((j & tb) != 0u, d1, d0), a[k]);
+                        }
+                    }
+                    ++g;
+                } while (g < nops && diagonal(g));
+#pragma unroll
+                for (int k = 0; k < PER; ++k) st[tid + k * nt] = a[k];
+                __syncthreads();
+                continue;
+            }
             // amplitudes with every condition bit set: the control, and for a phase the target
             const C d0 = mk<C>(v[0], v[1]), d1 = mk<C>(v[6], v[7]);
             const bool phase = kind == svp::K2_PHASE;
@@ -225,7 +274,7 @@ __global__ void __launch_bounds__(1024) k1_small_kernel(C *__restrict__ S, int n
             }
             const uint32_t ones = (lo >= 0 ? 1u << lo : 0u) | (hi >= 0 ? 1u << hi : 0u);
             const uint32_t cnt = N >> ((lo >= 0) + (hi >= 0));
-            for (uint32_t p = threadIdx.x; p < cnt; p += nt) {
+            for (uint32_t p = tid; p < cnt; p += nt) {
                 uint32_t j = p;
                 if (lo >= 0) j = insert0_32(j, lo);
                 if (hi >= 0) j = insert0_32(j, hi);
@@ -234,31 +283,42 @@ __global__ void __launch_bounds__(1024) k1_small_kernel(C *__restrict__ S, int n
                 st[j] = cmul(d, st[j]);
             }
         } else {
-            const C u00 = mk<C>(v[0], v[1]), u01 = mk<C>(v[2], v[3]), u10 = mk<C>(v[4], v[5]), u11 = mk<C>(v[6], v[7]);
             const int lo = (c >= 0 && c < t) ? c : t, hi = (c >= 0 && c > t) ? c : t;
             const uint32_t cbit = c >= 0 ? 1u << c : 0u, pairs = N >> (c >= 0 ? 2 : 1);
-            for (uint32_t p = threadIdx.x; p < pairs; p += nt) {
-                uint32_t j = insert0_32(p, lo);
-                if (c >= 0) j = insert0_32(j, hi);
-                j |= cbit;
-                const uint32_t k = j | (1u << t);
-                C a = st[j], b = st[k];
-                if (kind == svp::K2_H) {
-                    hbfly(a, b);
-                    st[j] = a;
-                    st[k] = b;
-                } else if (kind == svp::K2_X) {
-                    st[j] = b;
-                    st[k] = a;
-                } else {
-                    st[j] = cmad2(u00, a, u01, b);
-                    st[k] = cmad2(u10, a, u11, b);
+            auto each = [&](auto &&f) {
+                for (uint32_t p = tid; p < pairs; p += nt) {
+                    uint32_t j = insert0_32(p, lo);
+                    if (c >= 0) j = insert0_32(j, hi);
+                    j |= cbit;
+                    f(st[j], st[j | (1u << t)]);
                 }
+            };
+            if (kind == svp::K2_H) {
+                each([](C &x, C &y) {
+                    C a = x, b = y;
+                    hbfly(a, b);
+                    x = a;
+                    y = b;
+                });
+            } else if (kind == svp::K2_X) {
+                each([](C &x, C &y) {
+                    const C a = x, b = y;
+                    x = b;
+                    y = a;
+                });
+            } else {
+                const C u00 = mk<C>(v[0], v[1]), u01 = mk<C>(v[2], v[3]), u10 = mk<C>(v[4], v[5]), u11 = mk<C>(v[6], v[7]);
+                each([&](C &x, C &y) {
+                    const C a = x, b = y;
+                    x = cmad2(u00, a, u01, b);
+                    y = cmad2(u10, a, u11, b);
+                });
             }
         }
+        ++g;
         __syncthreads();
     }
-    for (uint32_t i = threadIdx.x; i < N; i += nt) S[i] = st[i];
+    for (uint32_t i = tid; i < N; i += nt) S[i] = st[i];
 }
 
 int k1_small_max(int dtype) { return dtype == 0 ? 14 : 13; }
@@ -274,23 +334,30 @@ svp::K2Op k1_small_op(const svp::MGate &g)
     return op;
 }
 
-template <typename C> static hipError_t k1_small_launch(void *S, int n, const svp::K2Op *ops, int nops, hipStream_t st)
+template <typename C, int PER>
+static hipError_t k1_small_launch(void *S, int n, const svp::K2Op *ops, int nops, hipStream_t st)
 {
     const size_t lds = sizeof(C) << n;
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)k1_small_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k1_small_kernel<C, PER>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    // a thread per pair, whole waves
-    const unsigned threads = n >= 11 ? 1024u : (n <= 7 ? 64u : 1u << (n - 1));
-    k1_small_kernel<C><<<1, threads, lds, st>>>((C *)S, n, ops, nops);
+    k1_small_kernel<C, PER><<<1, n >= 10 ? 1024u : 1u << n, lds, st>>>((C *)S, n, ops, nops);
     return hipGetLastError();
+}
+
+template <typename C> static hipError_t k1_small_any(void *S, int n, const svp::K2Op *ops, int nops, hipStream_t st)
+{
+    if (n <= 10) return k1_small_launch<C, 1>(S, n, ops, nops, st);
+    if (n == 11) return k1_small_launch<C, 2>(S, n, ops, nops, st);
+    if (n == 12) return k1_small_launch<C, 4>(S, n, ops, nops, st);
+    return k1_small_launch<C, 0>(S, n, ops, nops, st);
 }
 
 hipError_t k1_small(void *S, int n, int dtype, const svp::K2Op *dev_ops, int nops, hipStream_t st)
 {
     if (n > k1_small_max(dtype)) return hipErrorInvalidValue;
-    return dtype == 0 ? k1_small_launch<float2>(S, n, dev_ops, nops, st) : k1_small_launch<double2>(S, n, dev_ops, nops, st);
+    return dtype == 0 ? k1_small_any<float2>(S, n, dev_ops, nops, st) : k1_small_any<double2>(S, n, dev_ops, nops, st);
 }
 
 // ---------------------------------------------------------------- extended gates
