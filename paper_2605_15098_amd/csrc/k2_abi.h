@@ -23,7 +23,8 @@ enum K2Kind {
                      // moves through LDS: -1 whole; 0..31 in two halves by
                      // that local bit, held by the same slot before and
                      // after; 32 + x in two halves by local bit x, a
-                     // thread-id bit at the same position before and after
+                     // thread-id bit at the same position before and after;
+                     // v: a K2Offsets, for the interpreter
     K2_DENSE = 1,    // a: slot; b: control kind; c: control slot or bit code;
                      // v[0..7]: row-major 2x2 (re, im); m0: DenseForm
     K2_H = 2,        // as K2_DENSE, Hadamard
@@ -62,6 +63,12 @@ enum DenseForm {
 // block base).
 enum CtlKind { CK_NONE = 0, CK_SLOT = 1, CK_MEM = 2 };
 
+// LDS byte offset of each register slot's local bit before and after a
+// re-layout (0 for the bit a split takes out).
+struct K2Offsets {
+    uint32_t before[5], after[5];
+};
+
 struct K2Op {
     int32_t kind, a, b, c;
     uint64_t m0, m1;
@@ -97,7 +104,8 @@ struct DiagRun {
     uint32_t kmask;
     uint32_t qmask;
     int32_t ngroups;
-    int32_t same;       // 1: ngroups >= 1 and all groups have the same rmask
+    int32_t same;       // 1: ngroups >= 1 and all groups have the same rmask;
+                        // 2 + b: that mask is register bit b, and kmask its slots
 };
 
 // Block-uniform factor: e^{2 pi i sum angle_j [base covers tmask_j]} with
@@ -159,6 +167,43 @@ inline K2Lds k2_lds_layout(int l, int amp, int nug, int tab_count, int nut, int 
     o.ugrp = up(o.uterm + 32u * (uint32_t)nut);
     o.total = up(o.ugrp + 8u * (uint32_t)nug);
     return o;
+}
+
+// LDS index swizzle: the low bits that span one 128-byte bank row (amp bytes an
+// amplitude) are XORed with a fold of the higher bits, so lanes whose local
+// indices differ only in high bits still spread over the banks. The map is
+// linear over GF(2) (shifts, XORs and a constant mask), so for disjoint bit
+// sets swz(a | b) = swz(a) ^ swz(b): a thread swizzles its own bits once and
+// each register slot adds a block-uniform term.
+#if defined(__HIPCC_RTC__) || defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
+__host__ __device__ __attribute__((always_inline))
+#endif
+constexpr uint32_t k2_swz(uint32_t x, int amp)
+{
+    const int e = amp == 8 ? 4 : 3;  // log2(amplitudes per 128 bytes)
+    const uint32_t h = x >> e;
+    return x ^ ((h ^ (h >> e) ^ (h >> (2 * e))) & ((1u << e) - 1u));
+}
+
+// Local index x with bit b taken out (the bits above it move down one).
+#if defined(__HIPCC_RTC__) || defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
+__host__ __device__ __attribute__((always_inline))
+#endif
+constexpr uint32_t k2_drop_bit(uint32_t x, int b)
+{
+    return (x & ((1u << b) - 1u)) | ((x >> (b + 1)) << b);
+}
+
+// LDS byte offset of local bit b in a re-layout with this split code (K2_LAYOUT's
+// b): 0 for the bit that is taken out, whose halves are stored one at a time.
+#if defined(__HIPCC_RTC__) || defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
+__host__ __device__ __attribute__((always_inline))
+#endif
+constexpr uint32_t k2_slot_offset(int b, int split, int amp)
+{
+    const int x = split < 0 ? -1 : (split & 31);
+    if (b == x) return 0u;
+    return k2_swz(x >= 0 ? k2_drop_bit(1u << b, x) : 1u << b, amp) * (uint32_t)amp;
 }
 
 // Canonical layout of a block pass (its load and store): register slot 0

@@ -125,19 +125,7 @@ template <typename C> __host__ __device__ __forceinline__ uint64_t sto(uint64_t 
     return i ^ (((h ^ (h >> 9) ^ (h >> 18) ^ (h >> 27) ^ (h >> 36)) & 511ull) << S0);
 }
 
-// LDS index swizzle: the low bits that span one 128-byte bank row are XORed
-// with a fold of the higher bits, so lanes whose local indices differ only in
-// high bits still spread over the banks. The map is linear over GF(2) (shifts,
-// XORs and a constant mask), so for disjoint bit sets
-// swz(a | b) = swz(a) ^ swz(b): a thread swizzles its own bits once and each
-// register slot adds a block-uniform term.
-template <typename C> __host__ __device__ __forceinline__ uint32_t swz(uint32_t x)
-{
-    constexpr int E = (sizeof(C) == 8) ? 4 : 3;  // log2(elements per 128 B)
-    constexpr uint32_t M = (1u << E) - 1u;
-    const uint32_t h = x >> E;
-    return x ^ ((h ^ (h >> E) ^ (h >> (2 * E))) & M);
-}
+template <typename C> __device__ __forceinline__ uint32_t swz(uint32_t x) { return svp::k2_swz(x, (int)sizeof(C)); }
 
 // A non-register condition bit: 0..l-1 = local bit (tested on the thread's
 // local index), 64 + p = memory bit p outside the block (the block base).
@@ -258,12 +246,6 @@ struct K2Ctx {
     const unsigned char *tabs;   // the pass's lane/wave factors in LDS (type C)
 };
 
-// Local index x with bit b taken out (the bits above it move down one).
-__device__ __forceinline__ uint32_t drop_bit(uint32_t x, int b)
-{
-    return (x & ((1u << b) - 1u)) | ((x >> (b + 1)) << b);
-}
-
 // Re-layout through LDS: the amplitudes leave registers in layout rb_old and
 // come back in layout rb_new (local bit of each register slot, any order).
 // With split < 0 the whole block passes through LDS at once. Otherwise the
@@ -274,8 +256,10 @@ __device__ __forceinline__ uint32_t drop_bit(uint32_t x, int b)
 //    not overwrite the registers the second round writes);
 //  - split = 32 + x: x is the thread-id bit p >= 6 in both layouts; round h is
 //    done by the waves whose bit p is h, all of their registers.
+// before, after: the slot bits' LDS offsets (K2Offsets).
 template <int LOGR, typename C>
-__device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, const int *rb_new, int split)
+__device__ __forceinline__ void k2_layout_at(C *a, K2Ctx &cx, const int *rb_old, const int *rb_new, int split,
+                                             const uint32_t *before, const uint32_t *after)
 {
     constexpr int R = 1 << LOGR;
     // The thread's indices are laundered here so that each re-layout derives
@@ -293,25 +277,18 @@ __device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, co
         tnew = insert0_32(tnew, __builtin_ctz(rmask));
         rmask &= rmask - 1u;
     }
-    // LDS offset of each slot bit, old and new layout (a block that moves in
-    // halves is stored without bit x). The swizzle is linear, so slot k's offset
-    // is the XOR over its bits: one instruction from a slot with one bit less,
-    // which is what the interpreter pays where a compiled pass has constants.
+    // The swizzle is linear, so slot k's LDS offset is the XOR over its bits: one
+    // instruction from a slot with one bit less, which is what the interpreter
+    // pays where a compiled pass has constants. (A block that moves in halves is
+    // stored without bit x.)
     const int x = split < 0 ? -1 : (split & 31);
-    auto at = [&](uint32_t loc) -> uint32_t { return swz<C>(x >= 0 ? drop_bit(loc, x) : loc) * (uint32_t)sizeof(C); };
+    auto at = [&](uint32_t loc) -> uint32_t { return swz<C>(x >= 0 ? svp::k2_drop_bit(loc, x) : loc) * (uint32_t)sizeof(C); };
     uint32_t oo[R], on[R];
     oo[0] = on[0] = 0u;
 #pragma unroll
     for (int k = 1; k < R; ++k) {
-        if ((k & (k - 1)) == 0) {
-            const int j = __builtin_ctz(k);
-            // (the slot that holds x adds nothing: its half is stored alone)
-            oo[k] = rb_old[j] == x ? 0u : at(1u << rb_old[j]);
-            on[k] = rb_new[j] == x ? 0u : at(1u << rb_new[j]);
-        } else {
-            oo[k] = oo[k & (k - 1)] ^ oo[k & -k];
-            on[k] = on[k & (k - 1)] ^ on[k & -k];
-        }
+        oo[k] = oo[k & (k - 1)] ^ before[__builtin_ctz(k)];
+        on[k] = on[k & (k - 1)] ^ after[__builtin_ctz(k)];
     }
     const uint32_t tso = at(cx.tloc), tsn = at(tnew);
     auto put = [&](int k) { *reinterpret_cast<C *>(cx.lds + (tso ^ oo[k])) = a[k]; };
@@ -365,6 +342,18 @@ __device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, co
         lds_barrier();
     }
     cx.tloc = tnew;
+}
+
+template <int LOGR, typename C>
+__device__ __forceinline__ void k2_layout(C *a, K2Ctx &cx, const int *rb_old, const int *rb_new, int split)
+{
+    uint32_t before[LOGR], after[LOGR];
+#pragma unroll
+    for (int j = 0; j < LOGR; ++j) {
+        before[j] = svp::k2_slot_offset(rb_old[j], split, (int)sizeof(C));
+        after[j] = svp::k2_slot_offset(rb_new[j], split, (int)sizeof(C));
+    }
+    k2_layout_at<LOGR>(a, cx, rb_old, rb_new, split, before, after);
 }
 
 // ---- dense window through the matrix cores (16x16x4 MFMA)
@@ -548,6 +537,32 @@ template <typename C> __device__ __forceinline__ void k2_diag_apply(C &ak, bool 
     ak = cmul(F, ak);
 }
 
+// A run whose groups all need register bit B and whose slots are those with it
+// (DiagRun::same = 2 + B): T the groups' product.
+template <int LOGR, int B, typename C, typename Q>
+__device__ __forceinline__ void k2_diag_bit(C *a, C T, uint32_t qmask, Q q)
+{
+    constexpr int R = 1 << LOGR;
+    if (qmask == 0) {
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            if ((k >> B) & 1) a[k] = cmul(T, a[k]);
+        return;
+    }
+    C f[R / 2];  // all constants at once, not one wait a slot
+#pragma unroll
+    for (int k = 0, i = 0; k < R; ++k)
+        if ((k >> B) & 1) f[i++] = q(k);
+#pragma unroll
+    for (int k = 0, i = 0; k < R; ++k) {
+        if (!((k >> B) & 1)) continue;
+        C F = T;
+        if ((qmask >> k) & 1u) F = cmul(f[i], T);
+        a[k] = cmul(F, a[k]);
+        ++i;
+    }
+}
+
 // A diagonal run read from its record (the interpreter), folding each slot's
 // groups in the record's canonical order (see DiagRun).
 template <int LOGR, typename C>
@@ -574,6 +589,18 @@ __device__ __forceinline__ void k2_diagrun(C *a, const K2Ctx &cx, const unsigned
         const int rm = gs[0].rmask;
         C T = k2_group_factor<C>(gs[0], cx);
         for (int i = 1; i < ng; ++i) T = cmul(T, k2_group_factor<C>(gs[i], cx));
+        if (rec->same >= 2) {
+            // (most runs of a phase estimation: no test per slot)
+            switch (rec->same - 2) {
+            case 0: k2_diag_bit<LOGR, 0>(a, T, qmask, q); break;
+            case 1: if constexpr (LOGR > 1) k2_diag_bit<LOGR, 1>(a, T, qmask, q); break;
+            case 2: if constexpr (LOGR > 2) k2_diag_bit<LOGR, 2>(a, T, qmask, q); break;
+            case 3: if constexpr (LOGR > 3) k2_diag_bit<LOGR, 3>(a, T, qmask, q); break;
+            case 4: if constexpr (LOGR > 4) k2_diag_bit<LOGR, 4>(a, T, qmask, q); break;
+            default: break;
+            }
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < R; ++k) {
             if (!((kmask >> k) & 1u)) continue;
@@ -995,7 +1022,14 @@ struct K2Interp {
                 int nrb[LOGR];
 #pragma unroll
                 for (int j = 0; j < LOGR; ++j) nrb[j] = (op.a >> (5 * j)) & 31;
-                k2_layout<LOGR>(a, cx, rb, nrb, op.b);
+                const k2_const<uint32_t> off = as_const<uint32_t>((const void *)(uint64_t)&op.v[0]);
+                uint32_t before[LOGR], after[LOGR];
+#pragma unroll
+                for (int j = 0; j < LOGR; ++j) {
+                    before[j] = off[j];
+                    after[j] = off[5 + j];
+                }
+                k2_layout_at<LOGR>(a, cx, rb, nrb, op.b, before, after);
 #pragma unroll
                 for (int j = 0; j < LOGR; ++j) rb[j] = nrb[j];
             } else if (kind == svp::K2_MFMA) {

@@ -387,6 +387,8 @@ struct Builder {
         head.same = recs.empty() ? 0 : 1;
         for (const DiagGroup &d : recs)
             if (d.rmask != recs[0].rmask) head.same = 0;
+        if (head.same && __builtin_popcount((uint32_t)recs[0].rmask) == 1 && head.kmask == (cover(recs[0].rmask) & all))
+            head.same = 2 + top_bit(recs[0].rmask);
         std::vector<float> qf(cfg.dtype == 0 ? q.size() : 0);
         for (size_t k = 0; k < qf.size(); ++k) qf[k] = (float)q[k];
         std::vector<uint8_t> blob(sizeof(DiagRun) + recs.size() * sizeof(DiagGroup) + q.size() * sizeof(double) +
@@ -516,6 +518,13 @@ struct Builder {
             for (int j = 0; j < r; ++j) packed |= nrb[j] << (5 * j);
             op.a = packed;
             op.b = split;
+            K2Offsets off{};
+            for (int j = 0; j < r; ++j) {
+                off.before[j] = k2_slot_offset(rb[j], split, ab);
+                off.after[j] = k2_slot_offset(nrb[j], split, ab);
+            }
+            static_assert(sizeof off <= sizeof op.v, "K2Offsets lies in v");
+            std::memcpy(op.v, &off, sizeof off);
             plan.ops.push_back(op);
             rb = nrb;
         };
