@@ -358,7 +358,7 @@ def sweep(reps=2):
 
 
 def bench_batch(steps):
-    """256 QPE instances (12..22 qubits, complex64) in one persistent launch
+    """256 QPE instances (12..22 qubits, complex64) in one launch per block pass
     under a captured graph, schedule picked by the batch autotuner."""
     import torch
     from oracle import compare as C
