@@ -256,8 +256,11 @@ struct K2Ctx {
 //    not overwrite the registers the second round writes);
 //  - split = 32 + x: x is the thread-id bit p >= 6 in both layouts; round h is
 //    done by the waves whose bit p is h, all of their registers.
-// before, after: the slot bits' LDS offsets (K2Offsets).
-template <int LOGR, typename C>
+// before, after: the slot bits' LDS offsets (K2Offsets). UNIFORM: which waves do
+// a round is a scalar branch, which keeps the interpreter's op loop free of
+// divergent ones; in a compiled pass the lanes' mask schedules better (32-qubit
+// phase estimation complex64 45.3 ms, 46.0 with the scalar branch).
+template <int LOGR, bool UNIFORM = false, typename C>
 __device__ __forceinline__ void k2_layout_at(C *a, K2Ctx &cx, const int *rb_old, const int *rb_new, int split,
                                              const uint32_t *before, const uint32_t *after)
 {
@@ -308,8 +311,7 @@ __device__ __forceinline__ void k2_layout_at(C *a, K2Ctx &cx, const int *rb_old,
 #pragma unroll
         for (int j = 0; j < LOGR; ++j) om |= 1u << rb_old[j];
         const int p = x - __builtin_popcount(om & ((1u << x) - 1u));
-        // (p >= 6: the same for the whole wave)
-        const uint32_t mine = (__builtin_amdgcn_readfirstlane(cx.tid) >> p) & 1u;
+        const uint32_t mine = ((UNIFORM ? __builtin_amdgcn_readfirstlane(cx.tid) : cx.tid) >> p) & 1u;
 #pragma unroll
         for (uint32_t h = 0; h < 2; ++h) {
             if (mine == h) {
@@ -1029,7 +1031,7 @@ struct K2Interp {
                     before[j] = off[j];
                     after[j] = off[5 + j];
                 }
-                k2_layout_at<LOGR>(a, cx, rb, nrb, op.b, before, after);
+                k2_layout_at<LOGR, true>(a, cx, rb, nrb, op.b, before, after);
 #pragma unroll
                 for (int j = 0; j < LOGR; ++j) rb[j] = nrb[j];
             } else if (kind == svp::K2_MFMA) {
