@@ -22,6 +22,7 @@
 #include <cstring>
 #include <mutex>
 
+#include "grid.h"
 #include "k2_device.h"
 #include "launch.h"
 #include "plan.h"
@@ -31,12 +32,14 @@ namespace svk {
 // ---------------------------------------------------------------- init
 
 // |0...0>: one 16-byte store per thread, 4 KiB per work-group. More per
-// work-group is slower: 64 MiB alone 12.6 us here, 21-25 with 16, 32 or 64
-// KiB, 14 in a grid-stride loop (the runtime's fill 13.2); after a readout of the same state
-// 18.1 against 20.9, and 4 GiB 612 against 685 us (7.0 TB/s).
-template <typename V> __global__ void __launch_bounds__(256) init_kernel(V *S, uint64_t count, V first)
+// work-group is slower up to 4 GiB of complex64: 64 MiB alone 12.6 us here,
+// 21-25 with 16, 32 or 64 KiB, 14 in a grid-stride loop (the runtime's fill 13.2);
+// after a readout of the same state 18.1 against 20.9, and 4 GiB 612 against 685
+// us (7.0 TB/s). From 64 GiB on that is more threads than one launch may have.
+template <typename V>
+__global__ void __launch_bounds__(256) init_kernel(V *S, uint64_t count, uint64_t group0, V first)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint64_t i = (group0 + blockIdx.x) * 256 + threadIdx.x;
     if (i < count) S[i] = i == 0 ? first : V{};
 }
 
@@ -48,8 +51,10 @@ template <typename V> static hipError_t init_launch(void *S, uint64_t bytes, int
     if (dtype == 0) std::memcpy(&first, &one32, sizeof one32);
     else std::memcpy(&first, &one64, sizeof one64);
     const uint64_t count = bytes / sizeof(V);
-    init_kernel<V><<<(unsigned)((count + 255) / 256), 256, 0, st>>>((V *)S, count, first);
-    return hipGetLastError();
+    return split_launch((count + 255) / 256, 256, [&](uint64_t group0, unsigned groups) {
+        init_kernel<V><<<groups, 256, 0, st>>>((V *)S, count, group0, first);
+        return hipGetLastError();
+    });
 }
 
 hipError_t init_zero_state(void *S, int n, int dtype, hipStream_t st)

@@ -1,0 +1,228 @@
+// Test-only stand-in for the HIP runtime: the program defines the runtime's
+// entry points itself, so the simulator library it is linked with allocates
+// addresses that nobody reads, and launches kernels that are only written down.
+// Host code (launch shapes, error paths, caches, tuners) then runs on a
+// machine without a GPU, at sizes that no test machine's memory holds.
+//
+// A launch is refused as the runtime refuses it, from 2^32 threads in one
+// dimension on. Device times are invented: the LDS bytes of the launches.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "../../include/sv.h"
+
+namespace {
+
+constexpr uintptr_t kDeviceFrom = uintptr_t(1) << 44;
+uintptr_t g_next = kDeviceFrom;
+hipError_t g_last = hipSuccess;
+bool g_fail_launches = false, g_capturing = false;
+int g_launches = 0, g_graphs = 0;
+uint64_t g_most_threads = 0;
+double g_clock = 0.0;
+struct FakeGraph {
+    double cost = 0.0;
+};
+FakeGraph *g_graph = nullptr;
+struct FakeEvent {
+    double at = 0.0;
+};
+struct Call {
+    dim3 grid, block;
+    size_t lds;
+    hipStream_t st;
+};
+std::vector<Call> g_calls;
+
+}  // namespace
+
+extern "C" {
+
+hipError_t hipMalloc(void **p, size_t bytes)
+{
+    *p = (void *)g_next;
+    g_next += (bytes + 511) / 512 * 512;
+    return hipSuccess;
+}
+hipError_t hipFree(void *) { return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned)
+{
+    *p = std::calloc(1, bytes);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *dst, const void *, size_t bytes, hipMemcpyKind kind, hipStream_t)
+{
+    if (kind == hipMemcpyDeviceToHost) std::memset(dst, 0, bytes);
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
+{
+    std::memset(a, 0, sizeof *a);
+    a->type = (uintptr_t)p >= kDeviceFrom && (uintptr_t)p < g_next ? hipMemoryTypeDevice : hipMemoryTypeHost;
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void)
+{
+    const hipError_t e = g_last;
+    g_last = hipSuccess;
+    return e;
+}
+hipError_t hipLaunchKernel(const void *, dim3 grid, dim3 block, void **, size_t lds, hipStream_t)
+{
+    const uint64_t threads = (uint64_t)grid.x * block.x;
+    if (threads > g_most_threads) g_most_threads = threads;
+    if (g_fail_launches || threads >= (1ull << 32) || grid.x == 0) return g_last = hipErrorInvalidConfiguration;
+    ++g_launches;
+    (g_capturing ? g_graph->cost : g_clock) += (double)lds;
+    return hipSuccess;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t st)
+{
+    g_calls.push_back({grid, block, lds, st});
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *st)
+{
+    const Call c = g_calls.back();
+    g_calls.pop_back();
+    *grid = c.grid;
+    *block = c.block;
+    *lds = c.lds;
+    *st = c.st;
+    return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t)
+{
+    *n = 2;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d)
+{
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int)
+{
+    *v = 256;
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
+{
+    *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode)
+{
+    g_graph = new FakeGraph();
+    g_capturing = true;
+    return hipSuccess;
+}
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g)
+{
+    g_capturing = false;
+    *g = reinterpret_cast<hipGraph_t>(g_graph);
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t g, hipGraphNode_t *, char *, size_t)
+{
+    ++g_graphs;
+    *x = reinterpret_cast<hipGraphExec_t>(g);
+    return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t)
+{
+    g_clock += reinterpret_cast<FakeGraph *>(x)->cost;
+    return hipSuccess;
+}
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t g)
+{
+    delete reinterpret_cast<FakeGraph *>(g);
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t *e)
+{
+    *e = reinterpret_cast<hipEvent_t>(new FakeEvent());
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e)
+{
+    delete reinterpret_cast<FakeEvent *>(e);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+{
+    reinterpret_cast<FakeEvent *>(e)->at = g_clock;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b)
+{
+    *ms = (float)(reinterpret_cast<FakeEvent *>(b)->at - reinterpret_cast<FakeEvent *>(a)->at);
+    return hipSuccess;
+}
+
+}  // extern "C"
+
+namespace {
+
+// One call: its name, status, launches and the most threads of any of them.
+template <typename F> void call(const char *name, F &&f)
+{
+    g_launches = 0;
+    g_most_threads = 0;
+    const sv_status st = f();
+    std::printf("%s %d %d %llu\n", name, (int)st, g_launches, (unsigned long long)g_most_threads);
+}
+
+void *device(size_t bytes)
+{
+    void *p = nullptr;
+    hipMalloc(&p, bytes);
+    return p;
+}
+
+sv_gate gate(int op, int t, int c = -1, double theta = 0.0, int t2 = -1)
+{
+    sv_gate g{};
+    g.op = op;
+    g.target = t;
+    g.control = c;
+    g.target2 = t2;
+    g.theta = theta;
+    return g;
+}
+
+int reset(int n, sv_dtype dt)
+{
+    const size_t bytes = (dt == SV_COMPLEX64 ? 8ull : 16ull) << n;
+    sv_handle h = nullptr;
+    call("create", [&] { return sv_create(n, dt, &h); });
+    call("reset", [&] { return sv_reset(h); });
+    sv_destroy(h);
+    char *p = (char *)device(bytes + 8);
+    call("wrap", [&] { return sv_wrap(n, dt, p + 8, bytes, nullptr, &h); });
+    call("reset_between_units", [&] { return sv_reset(h); });
+    sv_destroy(h);
+    return 0;
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    auto num = [&](int i) { return argc > i ? std::atoi(argv[i]) : 0; };
+    if (what == "reset") return reset(num(2), (sv_dtype)num(3));
+    return 2;
+}

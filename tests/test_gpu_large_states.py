@@ -1,0 +1,50 @@
+"""GPU: states of 64 GiB and more, where a thread per unit of work is more
+threads than one launch may have (2^32)."""
+import numpy as np
+import pytest
+
+from oracle import qpe as cf
+from paper_2605_15098_amd import sv
+from paper_2605_15098_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+class Wrapped:
+    """A handle on a buffer of ones that starts `skip` real numbers into its allocation."""
+
+    def __init__(self, n, dtype, skip=0):
+        import torch
+        torch.cuda.empty_cache()
+        self.n, self.dtype = n, dtype
+        self.buf = torch.full(((2 << n) + 2 * skip,), 1.0, dtype=torch.float32 if dtype == "c64" else torch.float64, device="cuda")
+        size = self.buf.element_size()
+        self.h = sv.sv_wrap(n, dtype, self.buf.data_ptr() + skip * size, (2 << n) * size)
+
+    def close(self):
+        import torch
+        sv.sv_destroy(self.h)
+        self.buf = None
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype,n,skip", [("c64", 32, 2), ("c64", 33, 0), ("c128", 32, 0)])
+def test_reset_and_phase_estimation(dtype, n, skip):
+    print(f"case reset n={n} {dtype} skip={skip}", flush=True)
+    w = Wrapped(n, dtype, skip)
+    try:
+        sv.sv_reset(w.h)
+        # every other amplitude would add 2 to the sum of squares
+        assert sv.sv_norm(w.h) == 1.0
+        for off in (0, 1 << (n - 1), (1 << n) - 4):
+            assert np.array_equal(sv.sv_state_range(w.h, off, 4, dtype), np.eye(4)[0] if off == 0 else np.zeros(4))
+        if skip:
+            assert w.buf[:skip].tolist() == [1.0] * skip and w.buf[-skip:].tolist() == [1.0] * skip
+        phi = W.phi_for_seed(n)
+        sv.sv_apply_circuit(w.h, W.qpe_gates(n, phi))
+        m, _, p = sv.sv_qpe_readout(w.h, n - 1)
+        want = cf.qpe_argmax(n - 1, phi)
+        # the project's bounds on an amplitude, twice for its square
+        assert m == want and abs(p - cf.qpe_probabilities(n - 1, phi, [want])[0]) <= (2e-12 if dtype == "c128" else 4e-5)
+    finally:
+        w.close()

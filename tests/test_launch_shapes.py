@@ -1,0 +1,55 @@
+"""Host code of the library over a stand-in for the HIP runtime (CPU).
+
+tests/emu/fake_hip.cpp defines the runtime's entry points in the program that
+the library is linked into, so calls on states of up to 2^36 amplitudes run here
+without a GPU or their memory: what is checked is what the host side launches,
+returns and keeps. The stand-in refuses a launch of 2^32 threads in one
+dimension, as the runtime does.
+"""
+import os
+import subprocess
+
+import pytest
+
+from paper_2605_15098_amd import sv
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+SRC = os.path.join(HERE, "emu", "fake_hip.cpp")
+LIBDIR = os.path.join(ROOT, "paper_2605_15098_amd")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    """Runs the stand-in program: host(*args, **environment) -> its lines, split."""
+    sv.load()  # built
+    exe = str(tmp_path_factory.mktemp("host") / "fake_hip")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", "-o", exe, SRC, "-rdynamic",
+                    os.path.join(LIBDIR, "libsvmi.so"), f"-Wl,-rpath,{LIBDIR}", f"-Wl,-rpath-link,{ROCM}/lib"], check=True)
+
+    def run(*args, **env):
+        out = subprocess.run([exe, *map(str, args)], env=dict(os.environ, SV_JIT="0", **env), check=True,
+                             capture_output=True, text=True, timeout=100).stdout
+        return [line.split() for line in out.splitlines()]
+
+    return run
+
+
+def calls(lines):
+    """{name: (status, launches, most threads of a launch)}"""
+    return {name: tuple(int(x) for x in rest) for name, *rest in lines}
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n", [1, 14, 30, 31, 32, 33, 34, 35, 36])
+def test_reset_of_every_size(host, n, dtype):
+    """A launch per 32 GiB (2^31 threads of 16 bytes), 16 GiB where a buffer starts between two 16-byte units."""
+    got = calls(host("reset", n, dtype))
+    nbytes = (16 if dtype else 8) << n
+    for name, unit in (("create", 16), ("reset", 16), ("reset_between_units", 8)):
+        status, launches, threads = got[name]
+        units = nbytes // unit
+        assert status == 0 and launches == max(1, units >> 31), (name, got[name])
+        assert threads == max(256, min(units, 1 << 31)), (name, got[name])
+    assert got["wrap"][0] == 0
