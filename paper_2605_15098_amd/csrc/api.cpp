@@ -654,8 +654,9 @@ sv_status sv_destroy(sv_handle h)
 sv_status sv_reset(sv_handle h)
 {
     if (sv_status s = check_handle(h)) return s;
-    for (int q = 0; q < h->n; ++q) h->l2p[q] = q;
     SV_HIP(svk::init_zero_state(h->buf, h->n, h->dtype, h->stream), "init");
+    // (a launch that failed leaves the amplitudes in the layout they were in)
+    for (int q = 0; q < h->n; ++q) h->l2p[q] = q;
     return SV_OK;
 }
 

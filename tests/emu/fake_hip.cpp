@@ -188,7 +188,7 @@ template <typename F> void call(const char *name, F &&f)
 void *device(size_t bytes)
 {
     void *p = nullptr;
-    hipMalloc(&p, bytes);
+    (void)hipMalloc(&p, bytes);
     return p;
 }
 
@@ -217,6 +217,26 @@ int reset(int n, sv_dtype dt)
     return 0;
 }
 
+// A reset whose launch fails, from a layout that SWAPs permuted: status, then the layout.
+int failed_reset()
+{
+    sv_handle h = nullptr;
+    sv_create(5, SV_COMPLEX64, &h);
+    const sv_gate g[] = {gate(SV_SWAP, 0, -1, 0.0, 3), gate(SV_SWAP, 1, -1, 0.0, 4)};
+    call("swap", [&] { return sv_apply_circuit(h, g, 2, nullptr); });
+    g_fail_launches = true;
+    call("reset", [&] { return sv_reset(h); });
+    g_fail_launches = false;
+    int lay[5];
+    sv_layout(h, lay);
+    std::printf("layout %d %d %d %d %d\n", lay[0], lay[1], lay[2], lay[3], lay[4]);
+    call("reset", [&] { return sv_reset(h); });
+    sv_layout(h, lay);
+    std::printf("layout %d %d %d %d %d\n", lay[0], lay[1], lay[2], lay[3], lay[4]);
+    sv_destroy(h);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -224,5 +244,6 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     auto num = [&](int i) { return argc > i ? std::atoi(argv[i]) : 0; };
     if (what == "reset") return reset(num(2), (sv_dtype)num(3));
+    if (what == "failed_reset") return failed_reset();
     return 2;
 }

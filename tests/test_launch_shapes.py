@@ -53,3 +53,11 @@ def test_reset_of_every_size(host, n, dtype):
         assert status == 0 and launches == max(1, units >> 31), (name, got[name])
         assert threads == max(256, min(units, 1 << 31)), (name, got[name])
     assert got["wrap"][0] == 0
+
+
+def test_reset_that_fails_leaves_the_layout(host):
+    """The amplitudes stay in the permuted layout when the launch fails; the next reset succeeds."""
+    got = host("failed_reset")
+    assert got[0][:2] == ["swap", "0"]
+    assert got[1][:2] == ["reset", str(sv.SV_ERR_DEVICE)] and got[2] == ["layout", "3", "4", "2", "0", "1"]
+    assert got[3][:2] == ["reset", "0"] and got[4] == ["layout", "0", "1", "2", "3", "4"]
