@@ -102,9 +102,9 @@ enum { K1_DENSE = 0, K1_H = 1, K1_X = 2 };
 // Pairs (j, j + 2^t) with bit t of j clear and, if c >= 0, bit c set.
 template <typename C>
 __global__ void __launch_bounds__(K1_BLOCK)
-k1_pair_kernel(C *__restrict__ S, uint64_t npairs, int t, int c, int kind, C u00, C u01, C u10, C u11)
+k1_pair_kernel(C *__restrict__ S, uint64_t npairs, uint64_t group0, int t, int c, int kind, C u00, C u01, C u10, C u11)
 {
-    const uint64_t base = (uint64_t)blockIdx.x * (K1_BLOCK * K1_PER) + threadIdx.x;
+    const uint64_t base = (group0 + blockIdx.x) * (K1_BLOCK * K1_PER) + threadIdx.x;
     const int lo = (c >= 0 && c < t) ? c : t;
     const int hi = (c >= 0 && c > t) ? c : t;
     const uint64_t cbit = c >= 0 ? (1ull << c) : 0ull;
@@ -138,9 +138,9 @@ k1_pair_kernel(C *__restrict__ S, uint64_t npairs, int t, int c, int kind, C u00
 // to bit tsel.
 template <typename C>
 __global__ void __launch_bounds__(K1_BLOCK)
-k1_diag_kernel(C *__restrict__ S, uint64_t namps, int nones, int lo, int hi, int tsel, C d0, C d1)
+k1_diag_kernel(C *__restrict__ S, uint64_t namps, uint64_t group0, int nones, int lo, int hi, int tsel, C d0, C d1)
 {
-    const uint64_t base = (uint64_t)blockIdx.x * (K1_BLOCK * K1_PER) + threadIdx.x;
+    const uint64_t base = (group0 + blockIdx.x) * (K1_BLOCK * K1_PER) + threadIdx.x;
     uint64_t ones = 0;
     if (nones >= 1) ones |= 1ull << lo;
     if (nones >= 2) ones |= 1ull << hi;
@@ -159,6 +159,9 @@ k1_diag_kernel(C *__restrict__ S, uint64_t namps, int nones, int lo, int hi, int
     }
 }
 
+// Work-groups of a sweep over `work` pairs or amplitudes.
+static uint64_t k1_groups(uint64_t work) { return (work + K1_BLOCK * K1_PER - 1) / (K1_BLOCK * K1_PER); }
+
 template <typename T> static hipError_t k1_launch(void *Sv, int n, const svp::MGate &g, hipStream_t st)
 {
     using C = typename CT<T>::type;
@@ -171,19 +174,21 @@ template <typename T> static hipError_t k1_launch(void *Sv, int n, const svp::MG
         if (ptype) bits[nb++] = g.t;
         if (nb == 2 && bits[0] > bits[1]) { int x = bits[0]; bits[0] = bits[1]; bits[1] = x; }
         const uint64_t namps = 1ull << (n - nb);
-        const unsigned grid = (unsigned)((namps + K1_BLOCK * K1_PER - 1) / (K1_BLOCK * K1_PER));
-        k1_diag_kernel<C><<<grid, K1_BLOCK, 0, st>>>(S, namps, nb, nb > 0 ? bits[0] : 0,
-                                                     nb > 1 ? bits[1] : 0, ptype ? -1 : g.t,
-                                                     mk<C>(u[0], u[1]), mk<C>(u[6], u[7]));
-        return hipGetLastError();
+        return split_launch(k1_groups(namps), K1_BLOCK, [&](uint64_t group0, unsigned groups) {
+            k1_diag_kernel<C><<<groups, K1_BLOCK, 0, st>>>(S, namps, group0, nb, nb > 0 ? bits[0] : 0,
+                                                           nb > 1 ? bits[1] : 0, ptype ? -1 : g.t,
+                                                           mk<C>(u[0], u[1]), mk<C>(u[6], u[7]));
+            return hipGetLastError();
+        });
     }
     const uint64_t npairs = 1ull << (n - 1 - (g.c >= 0 ? 1 : 0));
-    const unsigned grid = (unsigned)((npairs + K1_BLOCK * K1_PER - 1) / (K1_BLOCK * K1_PER));
     const int kind = g.op == 0 ? K1_H : (g.cls == svp::GC_PERM ? K1_X : K1_DENSE);
-    k1_pair_kernel<C><<<grid, K1_BLOCK, 0, st>>>(S, npairs, g.t, g.c, kind, mk<C>(u[0], u[1]),
-                                                 mk<C>(u[2], u[3]), mk<C>(u[4], u[5]),
-                                                 mk<C>(u[6], u[7]));
-    return hipGetLastError();
+    return split_launch(k1_groups(npairs), K1_BLOCK, [&](uint64_t group0, unsigned groups) {
+        k1_pair_kernel<C><<<groups, K1_BLOCK, 0, st>>>(S, npairs, group0, g.t, g.c, kind, mk<C>(u[0], u[1]),
+                                                       mk<C>(u[2], u[3]), mk<C>(u[4], u[5]),
+                                                       mk<C>(u[6], u[7]));
+        return hipGetLastError();
+    });
 }
 
 hipError_t k1_gate(void *S, int n, int dtype, const svp::MGate &g, hipStream_t st)
@@ -371,10 +376,10 @@ hipError_t k1_small(void *S, int n, int dtype, const svp::K2Op *dev_ops, int nop
 // addresses (scalar loads), the 2^k outputs are stored after all inputs are
 // in registers.
 template <typename C, int K>
-__global__ void __launch_bounds__(128) kq_kernel(C *__restrict__ S, uint64_t ngroups, KqArg a, const C *__restrict__ U)
+__global__ void __launch_bounds__(128) kq_kernel(C *__restrict__ S, uint64_t ngroups, uint64_t group0, KqArg a, const C *__restrict__ U)
 {
     constexpr int D = 1 << K;
-    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t g = (group0 + blockIdx.x) * 128 + threadIdx.x;
     if (g >= ngroups) return;
     uint64_t j = g;
     for (int i = 0; i < a.nfixed; ++i) j = insert0(j, a.fixed[i]);
@@ -524,21 +529,22 @@ template <typename C, int K> static hipError_t kq_mfma_launch(C *S, uint64_t ngr
 template <typename C> static hipError_t kq_launch(void *S, int n, const KqArg &a, const void *U, hipStream_t st)
 {
     const uint64_t ngroups = 1ull << (n - a.nfixed);
-    const unsigned grid = (unsigned)((ngroups + 127) / 128);
     const bool mfma = ngroups >= 32;
     if (mfma && a.k == 4) return kq_mfma_launch<C, 4>((C *)S, ngroups, a, (const C *)U, st);
     if (mfma && a.k == 5) return kq_mfma_launch<C, 5>((C *)S, ngroups, a, (const C *)U, st);
     if (mfma && a.k == 6) return kq_mfma_launch<C, 6>((C *)S, ngroups, a, (const C *)U, st);
-    switch (a.k) {
-    case 1: kq_kernel<C, 1><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
-    case 2: kq_kernel<C, 2><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
-    case 3: kq_kernel<C, 3><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
-    case 4: kq_kernel<C, 4><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
-    case 5: kq_kernel<C, 5><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
-    case 6: kq_kernel<C, 6><<<grid, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return split_launch((ngroups + 127) / 128, 128, [&](uint64_t group0, unsigned groups) {
+        switch (a.k) {
+        case 1: kq_kernel<C, 1><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        case 2: kq_kernel<C, 2><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        case 3: kq_kernel<C, 3><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        case 4: kq_kernel<C, 4><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        case 5: kq_kernel<C, 5><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        case 6: kq_kernel<C, 6><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    });
 }
 
 hipError_t kq_gate(void *S, int n, int dtype, const int *tbits, int k, const int *cbits, int nc, const void *U,
@@ -566,9 +572,9 @@ hipError_t kq_gate(void *S, int n, int dtype, const int *tbits, int k, const int
 // Exchange memory bits p and v: amplitude i with bit p = 1, bit v = 0 trades
 // places with i ^ 2^p ^ 2^v. Pure data movement, exact.
 template <typename C>
-__global__ void __launch_bounds__(K1_BLOCK) k3_kernel(C *__restrict__ S, uint64_t npairs, int p, int v)
+__global__ void __launch_bounds__(K1_BLOCK) k3_kernel(C *__restrict__ S, uint64_t npairs, uint64_t group0, int p, int v)
 {
-    const uint64_t base = (uint64_t)blockIdx.x * (K1_BLOCK * K1_PER) + threadIdx.x;
+    const uint64_t base = (group0 + blockIdx.x) * (K1_BLOCK * K1_PER) + threadIdx.x;
     const int lo = p < v ? p : v, hi = p < v ? v : p;
     const uint64_t flip = (1ull << p) | (1ull << v);
 #pragma unroll
@@ -586,10 +592,11 @@ __global__ void __launch_bounds__(K1_BLOCK) k3_kernel(C *__restrict__ S, uint64_
 hipError_t k3_swap(void *S, int n, int dtype, int p, int v, hipStream_t st)
 {
     const uint64_t npairs = 1ull << (n - 2);
-    const unsigned grid = (unsigned)((npairs + K1_BLOCK * K1_PER - 1) / (K1_BLOCK * K1_PER));
-    if (dtype == 0) k3_kernel<float2><<<grid, K1_BLOCK, 0, st>>>((float2 *)S, npairs, p, v);
-    else k3_kernel<double2><<<grid, K1_BLOCK, 0, st>>>((double2 *)S, npairs, p, v);
-    return hipGetLastError();
+    return split_launch(k1_groups(npairs), K1_BLOCK, [&](uint64_t group0, unsigned groups) {
+        if (dtype == 0) k3_kernel<float2><<<groups, K1_BLOCK, 0, st>>>((float2 *)S, npairs, group0, p, v);
+        else k3_kernel<double2><<<groups, K1_BLOCK, 0, st>>>((double2 *)S, npairs, group0, p, v);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace svk

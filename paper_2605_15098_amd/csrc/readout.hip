@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <mutex>
 
+#include "grid.h"
 #include "k2_device.h"
 #include "launch.h"
 #include "plan.h"
@@ -381,11 +382,11 @@ __global__ void __launch_bounds__(256) marg_finish_kernel(const double *__restri
 // one in bit-reversed layout: 4958 us with a thread per output, which
 // fetched every 128-byte line for one amplitude at a time.
 template <typename C, int NS>
-__global__ void __launch_bounds__(256) marg_tile_kernel(const C *__restrict__ S, MargArg q, double *__restrict__ out)
+__global__ void __launch_bounds__(256) marg_tile_kernel(const C *__restrict__ S, MargArg q, uint64_t tile0, double *__restrict__ out)
 {
     __shared__ double tile[MARG_TILE];
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t base = xor_masks(blockIdx.x, q.oa) ^ lane, mbase = xor_masks(blockIdx.x, q.om);
+    const uint64_t base = xor_masks(tile0 + blockIdx.x, q.oa) ^ lane, mbase = xor_masks(tile0 + blockIdx.x, q.om);
     uint32_t lpos = 0;
 #pragma unroll
     for (int b = 0; b < 6; ++b)
@@ -555,11 +556,12 @@ static hipError_t marginal_t(const C *S, int n, const int *qbits, int nq, const 
         }
     }
     if (p.kind == 2) {
-        const unsigned grid = 1u << a.no;
-        if (a.ns == 0) marg_tile_kernel<C, 0><<<grid, 256, 0, st>>>(S, a, out);
-        else if (a.ns == 1) marg_tile_kernel<C, 1><<<grid, 256, 0, st>>>(S, a, out);
-        else marg_tile_kernel<C, 2><<<grid, 256, 0, st>>>(S, a, out);
-        return hipGetLastError();
+        return split_launch(1ull << a.no, 256, [&](uint64_t tile0, unsigned groups) {
+            if (a.ns == 0) marg_tile_kernel<C, 0><<<groups, 256, 0, st>>>(S, a, tile0, out);
+            else if (a.ns == 1) marg_tile_kernel<C, 1><<<groups, 256, 0, st>>>(S, a, tile0, out);
+            else marg_tile_kernel<C, 2><<<groups, 256, 0, st>>>(S, a, tile0, out);
+            return hipGetLastError();
+        });
     }
     double *part = p.shares > 1 ? (double *)scratch : out;
     marg_reduce_kernel<C><<<dim3(1u << a.no, (unsigned)p.shares), 64 * p.waves, 0, st>>>(S, a, part, M);
@@ -1022,13 +1024,13 @@ struct PermTile {
 };
 
 template <typename C, bool IMPORT>
-__global__ void __launch_bounds__(256) perm_tile_kernel(C *__restrict__ S, PermTile q, C *__restrict__ user)
+__global__ void __launch_bounds__(256) perm_tile_kernel(C *__restrict__ S, PermTile q, uint64_t tile0, C *__restrict__ user)
 {
     constexpr int TB = perm_tile_bits<C>(), E = 1 << (TB - 8);
     __shared__ C tile[1 << TB];
     const uint32_t tid = threadIdx.x;
     uint64_t sa = q.base, ua = 0;
-    for (uint64_t v = blockIdx.x; v != 0; v &= v - 1) {
+    for (uint64_t v = tile0 + blockIdx.x; v != 0; v &= v - 1) {
         const int k = __builtin_ctzll(v);
         sa ^= q.oa[k];
         ua |= q.ol[k];
@@ -1131,8 +1133,10 @@ static hipError_t perm_copy(void *S, int n, const int *perm, void *user, uint64_
     // the identity layout is coalesced in logical order; a range that is not a
     // whole number of tiles is walked too
     if (!pa.ident && perm_tiles<C>(perm, n, offset, count, q)) {
-        perm_tile_kernel<C, IMPORT><<<(unsigned)(count >> perm_tile_bits<C>()), 256, 0, st>>>((C *)S, q, (C *)user);
-        return hipGetLastError();
+        return split_launch(count >> perm_tile_bits<C>(), 256, [&](uint64_t tile0, unsigned groups) {
+            perm_tile_kernel<C, IMPORT><<<groups, 256, 0, st>>>((C *)S, q, tile0, (C *)user);
+            return hipGetLastError();
+        });
     }
     const unsigned g = grid_for(count, 256, 16384);
     if (IMPORT) scatter_kernel<C><<<g, 256, 0, st>>>((C *)S, pa, (const C *)user, offset, count);

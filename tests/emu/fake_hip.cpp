@@ -217,6 +217,56 @@ int reset(int n, sv_dtype dt)
     return 0;
 }
 
+// One call of everything that sweeps the state or its outcomes.
+int sweeps(int n, sv_dtype dt)
+{
+    const size_t bytes = (dt == SV_COMPLEX64 ? 8ull : 16ull) << n;
+    void *user = device(bytes);
+    double *out = (double *)device(8ull << n);
+    sv_handle h = nullptr;
+    call("create", [&] { return sv_create(n, dt, &h); });
+    std::vector<int> low(n - 1);
+    for (int q = 0; q < n - 1; ++q) low[q] = q;
+    const int few[] = {n - 1, 0, 7};
+    double u[4] = {0.1, 0.2, 0.3, 0.4}, x = 0.0, y = 0.0;
+    uint64_t shots[4], m = 0;
+    sv_schedule plain{};
+    plain.mode = SV_PLAIN;
+    sv_schedule paper{};
+    paper.mode = SV_PARTITIONED;
+    paper.block_qubits = 10;
+    paper.remap = SV_REMAP_EXPLICIT;
+    std::vector<double> mat(2 * 64 * 64, 0.0);
+    for (int layout = 0; layout < 2; ++layout) {
+        call("state", [&] { return sv_state(h, user); });
+        call("set_state", [&] { return sv_set_state_range(h, 0, 1ull << n, user); });
+        call("probabilities", [&] { return sv_probabilities(h, nullptr, 0, out); });
+        call("marginal", [&] { return sv_probabilities(h, low.data(), n - 1, out); });
+        call("marginal_of_few", [&] { return sv_probabilities(h, few, 3, out); });
+        call("norm", [&] { return sv_norm(h, &x); });
+        call("qpe_readout", [&] { return sv_qpe_readout(h, n - 1, &m, &x, &y); });
+        call("sample", [&] { return sv_sample(h, nullptr, 0, u, 4, shots); });
+        call("sample_of_few", [&] { return sv_sample(h, few, 3, u, 4, shots); });
+        const sv_gate sweep[] = {gate(SV_H, n - 1), gate(SV_X, 1), gate(SV_RX, 2, -1, 0.3), gate(SV_RZ, 3, -1, 0.4),
+                                 gate(SV_P, 4, -1, 0.5), gate(SV_X, 5, 0)};
+        call("plain", [&] { return sv_apply_circuit(h, sweep, 6, &plain); });
+        call("explicit_remap", [&] { return sv_apply_circuit(h, sweep, 6, &paper); });
+        call("partitioned", [&] { return sv_apply_circuit(h, sweep, 6, nullptr); });
+        for (int k = 1; k <= 6; ++k) {
+            sv_gate_ex g{};
+            g.op = SV_UK;
+            g.ntargets = k;
+            for (int b = 0; b < k; ++b) g.targets[b] = n - 1 - 2 * b;
+            g.uk = mat.data();
+            call("unitary", [&] { return sv_apply_circuit_ex(h, &g, 1, nullptr); });
+        }
+        const sv_gate rename[] = {gate(SV_SWAP, 0, -1, 0.0, n - 1), gate(SV_SWAP, 2, -1, 0.0, 9)};
+        call("swap", [&] { return sv_apply_circuit(h, rename, 2, nullptr); });
+    }
+    sv_destroy(h);
+    return 0;
+}
+
 // A reset whose launch fails, from a layout that SWAPs permuted: status, then the layout.
 int failed_reset()
 {
@@ -244,6 +294,7 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     auto num = [&](int i) { return argc > i ? std::atoi(argv[i]) : 0; };
     if (what == "reset") return reset(num(2), (sv_dtype)num(3));
+    if (what == "sweeps") return sweeps(num(2), (sv_dtype)num(3));
     if (what == "failed_reset") return failed_reset();
     return 2;
 }

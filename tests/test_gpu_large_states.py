@@ -48,3 +48,30 @@ def test_reset_and_phase_estimation(dtype, n, skip):
         assert m == want and abs(p - cf.qpe_probabilities(n - 1, phi, [want])[0]) <= (2e-12 if dtype == "c128" else 4e-5)
     finally:
         w.close()
+
+
+@pytest.mark.parametrize("what,n", [("unitary", 33), ("plain", 34)])
+def test_gates_in_more_than_one_launch(what, n):
+    """Amplitudes on both sides of where a sweep over complex64 amplitudes splits: a dense 2x2 unitary
+    from 2^33 amplitudes on, an RZ without control in a plain circuit from 2^34 on."""
+    print(f"case split {what} n={n}", flush=True)
+    w = Wrapped(n, "c64")
+    try:
+        sv.sv_reset(w.h)
+        half = 1 << (n - 1)
+        for at, a in ((0, [0, 0, 0.6, 0]), (half, [0, 0, 0, 0.8j])):
+            sv.sv_set_state_range(w.h, at, np.array(a, dtype=np.complex64))
+        th = 0.7
+        c, s, e = np.cos(th / 2), np.sin(th / 2), np.exp(0.5j * th)
+        if what == "unitary":
+            sv.sv_apply_circuit_ex(w.h, [("U", [0], [], np.array([[c, -s], [s, c]], dtype=complex))])
+            want = ((0, [0, 0, 0.6 * c, 0.6 * s]), (half, [0, 0, -0.8j * s, 0.8j * c]))
+        else:
+            sv.sv_apply_circuit(w.h, W.gates_from_tuples([("RZ", 0, -1, th)]), sv.schedule("plain"))
+            want = ((0, [0, 0, 0.6 / e, 0]), (half, [0, 0, 0, 0.8j * e]))
+        for at, a in want:
+            # two FP32 roundings of each product of entries rounded once
+            assert np.max(np.abs(sv.sv_state_range(w.h, at, 4, "c64") - np.array(a))) <= 4 * 2.0 ** -24
+        assert abs(sv.sv_norm(w.h) - 1.0) <= 16 * 2.0 ** -24
+    finally:
+        w.close()

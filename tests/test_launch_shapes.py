@@ -55,6 +55,17 @@ def test_reset_of_every_size(host, n, dtype):
     assert got["wrap"][0] == 0
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n", [20, 30, 32, 33, 34, 35, 36])
+def test_no_launch_is_too_large(host, n, dtype):
+    """Every call that sweeps the state, in the identity and in a permuted layout (shots are drawn of at most 32 qubits)."""
+    seen = host("sweeps", n, dtype)
+    assert len(seen) == 1 + 2 * 19
+    for name, status, _, threads in seen:
+        want = sv.SV_ERR_UNSUPPORTED if name == "sample" and n > 32 else 0
+        assert int(status) == want and int(threads) <= 1 << 31, (name, status, threads)
+
+
 def test_reset_that_fails_leaves_the_layout(host):
     """The amplitudes stay in the permuted layout when the launch fails; the next reset succeeds."""
     got = host("failed_reset")
