@@ -305,6 +305,7 @@ template <typename T> sv_status upload(sv_handle h, T **buf, size_t *cap, const 
 // and uploaded unless the handle still holds it.
 sv_status prepared(sv_handle h, const svp::PlanConfig &c, const svp::RawGate *gates, size_t m, PreparedPlan **out)
 {
+    if (m > 0 && !gates) return fail(SV_ERR_INVALID_ARG, "gate array is null");  // (compared below, before the planner looks)
     // Block passes run as kernels compiled for their op lists (cached), unless
     // SV_JIT=0 selects the op interpreter.
     const bool jit = !env_is("SV_JIT", '0'), fuse_all = env_is("SV_FUSE_ALL", '1');

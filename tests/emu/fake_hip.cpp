@@ -287,6 +287,19 @@ int failed_reset()
     return 0;
 }
 
+// A circuit without its gate array, after one of as many gates was applied.
+int null_gates()
+{
+    sv_handle h = nullptr;
+    sv_create(5, SV_COMPLEX64, &h);
+    const sv_gate g[] = {gate(SV_H, 0), gate(SV_X, 1, 0), gate(SV_RZ, 2, -1, 0.3)};
+    call("apply", [&] { return sv_apply_circuit(h, g, 3, nullptr); });
+    call("null", [&] { return sv_apply_circuit(h, nullptr, 3, nullptr); });
+    call("apply", [&] { return sv_apply_circuit(h, g, 3, nullptr); });
+    sv_destroy(h);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -296,5 +309,6 @@ int main(int argc, char **argv)
     if (what == "reset") return reset(num(2), (sv_dtype)num(3));
     if (what == "sweeps") return sweeps(num(2), (sv_dtype)num(3));
     if (what == "failed_reset") return failed_reset();
+    if (what == "null_gates") return null_gates();
     return 2;
 }

@@ -72,3 +72,9 @@ def test_reset_that_fails_leaves_the_layout(host):
     assert got[0][:2] == ["swap", "0"]
     assert got[1][:2] == ["reset", str(sv.SV_ERR_DEVICE)] and got[2] == ["layout", "3", "4", "2", "0", "1"]
     assert got[3][:2] == ["reset", "0"] and got[4] == ["layout", "0", "1", "2", "3", "4"]
+
+
+def test_null_gate_array(host):
+    """Refused also where a plan of that many gates is kept."""
+    assert [(name, int(status)) for name, status, *_ in host("null_gates")] == \
+        [("apply", 0), ("null", sv.SV_ERR_INVALID_ARG), ("apply", 0)]
