@@ -9,6 +9,9 @@
 // Inputs are standardised inside the kernels: x' = (x - mean) * inv_std with
 // norm = {mean[in], inv_std[in]} (norm may be null: identity).
 //
+// Samples are counted in int, up to 2^31 - 1 of them: loops go over tiles, and a
+// sample's index is formed only where it lies in the batch.
+//
 // Every reduction runs in a fixed order (matrix products over their inner
 // index, per work-group in tile order, across work-groups in group order), so
 // results are deterministic for a given batch.
@@ -28,6 +31,8 @@ constexpr int TILE = 16;        // samples per work-group step: the columns of o
 constexpr int THREADS = 256;    // four waves, sixteen hidden units each
 constexpr int ROW = TILE + 1;   // LDS row stride [unit][sample]: reads along either index hit 64 different banks
 constexpr int MAX_ROWS = 128;   // partial gradients (work-groups of the gradient kernel)
+
+__host__ __device__ constexpr int tiles_of(int batch) { return (batch - 1) / TILE + 1; }
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -75,13 +80,14 @@ struct Net {
     }
     __device__ __forceinline__ int unit(int r) const { return 16 * w + 4 * q + r; }
 
-    // Standardised inputs of samples s0 .. s0 + 15 as xs[input][sample], zeros beyond the batch and the inputs.
-    __device__ __forceinline__ void stage(float (*xs)[ROW], const float *X, const float *norm, int s0, int batch) const
+    // Standardised inputs of samples s0 .. s0 + 15 as xs[input][sample], zeros beyond the `left` samples from s0 on
+    // and the inputs.
+    __device__ __forceinline__ void stage(float (*xs)[ROW], const float *X, const float *norm, int s0, int left) const
     {
         for (int e = threadIdx.x; e < TILE * kMlpMaxIn; e += THREADS) {
             const int i = e % kMlpMaxIn, s = e / kMlpMaxIn;
             float x = 0.f;
-            if (i < in && s0 + s < batch) {
+            if (i < in && s < left) {
                 x = X[(size_t)(s0 + s) * in + i];
                 if (norm) x = (x - norm[i]) * norm[in + i];
             }
@@ -128,11 +134,12 @@ __global__ void __launch_bounds__(THREADS) k7_forward_kernel(const float *P, int
     __shared__ float xs[kMlpMaxIn][ROW], h1s[H][ROW], ys[4][TILE], all[kMlpArgminMax];
     Net net;
     net.load(P, in);
-    for (int s0 = blockIdx.x * TILE; s0 < batch; s0 += gridDim.x * TILE) {
-        net.stage(xs, X, norm, s0, batch);
+    for (int t = blockIdx.x; t < tiles_of(batch); t += gridDim.x) {
+        const int s0 = t * TILE, left = batch - s0;
+        net.stage(xs, X, norm, s0, left);
         __syncthreads();
         f4 h1, h2;
-        const bool valid = s0 + net.n < batch;
+        const bool valid = net.n < left;
         const float out = net.forward(xs, h1s, ys, valid, h1, h2);
         if (threadIdx.x < TILE && valid) {
             y[s0 + net.n] = out;
@@ -167,9 +174,10 @@ __global__ void __launch_bounds__(THREADS) k7_grad_kernel(const float *P, int in
     f4 g1[kMlpMaxIn / 16] = {zero, zero}, g2[4] = {zero, zero, zero, zero};
     f4 gb1 = zero, gb2 = zero, gw3 = zero;
     float gb3 = 0.f, loss = 0.f;
-    for (int s0 = blockIdx.x * TILE; s0 < batch; s0 += gridDim.x * TILE) {
-        net.stage(xs, X, norm, s0, batch);
-        const bool valid = s0 + n < batch;
+    for (int t = blockIdx.x; t < tiles_of(batch); t += gridDim.x) {
+        const int s0 = t * TILE, left = batch - s0;
+        net.stage(xs, X, norm, s0, left);
+        const bool valid = n < left;
         const float target = valid ? T[s0 + n] : 0.f;
         __syncthreads();
         f4 h1, h2, d2;
@@ -278,7 +286,7 @@ bool in_ok(int in) { return in >= 1 && in <= kMlpMaxIn; }
 
 int mlp_grad_groups(int batch)
 {
-    const int tiles = (batch + TILE - 1) / TILE;
+    const int tiles = tiles_of(batch);
     return tiles < MAX_ROWS ? tiles : MAX_ROWS;
 }
 
@@ -288,7 +296,7 @@ hipError_t mlp_forward(const float *P, int in, const float *norm, const float *X
     if (!in_ok(in) || batch < 1) return hipErrorInvalidValue;
     if (argmin && batch > kMlpArgminMax) return hipErrorInvalidValue;
     // a work-group per tile up to four per CU, which then take several tiles each
-    const int tiles = (batch + TILE - 1) / TILE;
+    const int tiles = tiles_of(batch);
     const unsigned grid = argmin ? 1u : (unsigned)(tiles < 1024 ? tiles : 1024);
     k7_forward_kernel<<<grid, THREADS, 0, st>>>(P, in, norm, X, batch, y, argmin);
     return hipGetLastError();

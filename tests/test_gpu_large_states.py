@@ -1,8 +1,10 @@
-"""GPU: states of 64 GiB and more, where a thread per unit of work is more
-threads than one launch may have (2^32)."""
+"""GPU: sizes near the limits of launches and counters. States of 64 GiB and
+more, where a thread per unit of work is more threads than one launch may have
+(2^32), and batches of the cost-model network up to the largest int."""
 import numpy as np
 import pytest
 
+from oracle import mlp
 from oracle import qpe as cf
 from paper_2605_15098_amd import sv
 from paper_2605_15098_amd import workloads as W
@@ -75,3 +77,31 @@ def test_gates_in_more_than_one_launch(what, n):
         assert abs(sv.sv_norm(w.h) - 1.0) <= 16 * 2.0 ** -24
     finally:
         w.close()
+
+
+def test_network_on_the_largest_batch():
+    """2^31 - 1 samples of one input: predictions at both ends and around the last 2^14 samples, where an int
+    that counts samples in steps of the grid wraps; the gradient of a network that predicts 1/2 everywhere."""
+    import torch
+    batch = (1 << 31) - 1
+    rng = np.random.default_rng(9)
+    p = rng.normal(size=sv.sv_mlp_param_count(1)).astype(np.float32) * 0.3
+    x, y = torch.empty(batch, device="cuda"), torch.full((batch,), np.nan, device="cuda")
+    x.uniform_(-2.0, 2.0)
+    print("case network forward", flush=True)
+    sv.sv_mlp_forward(torch.tensor(p, device="cuda"), 1, None, x, batch, y)
+    norm = np.array([0.0, 1.0])
+    for at in (0, batch - (1 << 14) - 512, batch - 1024):
+        want = mlp.forward(p.astype(np.float64), norm, x[at:at + 1024].cpu().numpy().astype(np.float64).reshape(-1, 1))
+        assert np.all(np.abs(y[at:at + 1024].cpu().numpy() - want) <= 1e-5 * np.maximum(1.0, np.abs(want)))
+    assert not bool(torch.isnan(y).any())
+    p[:] = 0.0
+    p[-1] = 0.5
+    y.zero_()
+    grad, loss = torch.zeros(len(p), device="cuda"), torch.zeros(1, device="cuda")
+    ws = torch.full((sv.sv_mlp_workspace_bytes(1, batch) // 4,), 7.0, device="cuda")
+    print("case network gradient", flush=True)
+    sv.sv_mlp_grad(torch.tensor(p, device="cuda"), 1, None, x, y, batch, grad, loss, ws)
+    # sums of equal powers of two: exact but for the last, incomplete tile
+    assert abs(float(loss.item()) - 0.25) <= 1e-6 and abs(float(grad[-1].item()) - 1.0) <= 1e-6
+    assert not bool(grad[:-1].any())

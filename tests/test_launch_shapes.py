@@ -78,3 +78,10 @@ def test_null_gate_array(host):
     """Refused also where a plan of that many gates is kept."""
     assert [(name, int(status)) for name, status, *_ in host("null_gates")] == \
         [("apply", 0), ("null", sv.SV_ERR_INVALID_ARG), ("apply", 0)]
+
+
+def test_network_workspace_of_the_largest_batch():
+    """128 rows of partial gradients from 2048 samples on, up to the largest int."""
+    row = 4 * (sv.sv_mlp_param_count(1) + 1)
+    for batch, rows in ((1, 1), (16, 1), (17, 2), (2048, 128), (2049, 128), ((1 << 31) - 17, 128), ((1 << 31) - 1, 128)):
+        assert sv.sv_mlp_workspace_bytes(1, batch) == rows * row, batch
