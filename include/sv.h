@@ -296,10 +296,10 @@ sv_status sv_prepare(sv_handle h, const sv_gate *gates, size_t m, const sv_sched
  * the schedule leaves block, tile and pins to the library, an instance pins fewer low
  * qubits than the dtype's default where that saves passes. The work-groups of a
  * launch take chunks of an instance's blocks from a counter, the most expensive
- * chunks first. The graph is cached by a hash of the gate lists, layouts,
- * buffers and schedule, so the same batch applied again replays it. Runs on the
- * first handle's stream and synchronizes it. Schedules that are not
- * partitioned with virtual remap, or a register tile outside 3..5 (3..4 for
+ * chunks first. The graphs of the last eight batches are kept with their
+ * gate lists, layouts, buffers and schedule, so the same batch applied again
+ * replays its graph. Runs on the first handle's stream and synchronizes it.
+ * Schedules that are not partitioned with virtual remap, or a register tile outside 3..5 (3..4 for
  * complex128), are applied one circuit after another. Each handle's stats
  * receive its own counts, its block size and the batch's device time. */
 sv_status sv_apply_batch(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m,

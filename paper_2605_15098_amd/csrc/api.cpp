@@ -1652,11 +1652,38 @@ sv_status sv_mlp_adam(float *params, float *m, float *v, const float *grad, size
 
 namespace {
 
-// One prepared batch: its device arrays and captured graph, keyed by a hash
-// of everything its plans depend on.
+// What a batch's graph depends on, compared whole: a look at the counts and
+// buffers first, then at every gate.
+struct BatchKey {
+    int tbits = 0;
+    long max_grid = 0;
+    bool fuse_all = false;
+    svp::PlanConfig cfg;
+    struct Inst {
+        void *buf;
+        int n;
+        std::vector<int> l2p;
+        std::vector<svp::RawGate> gates;
+    };
+    std::vector<Inst> insts;
+
+    bool matches(int t, long grid, bool all, const svp::PlanConfig &c, sv_handle *hs, int count, const sv_gate *const *gates,
+                 const size_t *m) const
+    {
+        if (t != tbits || grid != max_grid || all != fuse_all || !same_config(c, cfg) || (size_t)count != insts.size()) return false;
+        for (int i = 0; i < count; ++i) {
+            const Inst &x = insts[i];
+            if (hs[i]->buf != x.buf || hs[i]->n != x.n || m[i] != x.gates.size() || hs[i]->l2p != x.l2p) return false;
+        }
+        for (int i = 0; i < count; ++i)
+            if (m[i] > 0 && std::memcmp(insts[i].gates.data(), gates[i], m[i] * sizeof(svp::RawGate)) != 0) return false;
+        return true;
+    }
+};
+
+// One prepared batch: its device arrays and captured graph.
 struct BatchEntry {
-    uint64_t key = 0;
-    int count = 0;
+    BatchKey key;
     void *dbuf = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1673,27 +1700,6 @@ struct BatchEntry {
 
 std::mutex g_batch_mu;
 std::vector<std::shared_ptr<BatchEntry>> g_batches;  // most recent last, at most 8
-
-uint64_t mix64(uint64_t h, uint64_t x)
-{
-    h ^= x + 0x9e3779b97f4a7c15ull + (h << 6) + (h >> 2);
-    h *= 0xff51afd7ed558ccdull;
-    return h ^ (h >> 33);
-}
-
-uint64_t hash_bytes(uint64_t h, const void *p, size_t n)
-{
-    const unsigned char *b = static_cast<const unsigned char *>(p);
-    size_t i = 0;
-    for (; i + 8 <= n; i += 8) {
-        uint64_t w;
-        std::memcpy(&w, b + i, 8);
-        h = mix64(h, w);
-    }
-    uint64_t tail = 0;
-    std::memcpy(&tail, b + i, n - i);
-    return mix64(h, tail ^ n);
-}
 
 size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
@@ -1731,20 +1737,13 @@ std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *c
         ri[i] = li[i] - tbits;
         lmax_tile = std::max(lmax_tile, ri[i]);
     }
-    uint64_t key = mix64(0x5eed, (uint64_t)count);
-    key = mix64(key, (uint64_t)tbits);
-    if (const char *env = std::getenv("SV_BATCH_MAX_GRID")) key = mix64(key, (uint64_t)std::atol(env));
-    key = hash_bytes(key, &base, sizeof(base));
-    for (int i = 0; i < count; ++i) {
-        key = mix64(key, (uint64_t)(uintptr_t)hs[i]->buf);
-        key = mix64(key, (uint64_t)hs[i]->n);
-        key = hash_bytes(key, hs[i]->l2p.data(), hs[i]->l2p.size() * sizeof(int));
-        key = hash_bytes(key, gates[i], m[i] * sizeof(sv_gate));
-    }
+    const char *grid_env = std::getenv("SV_BATCH_MAX_GRID");
+    const long max_grid = grid_env ? std::atol(grid_env) : 0;
+    const bool fuse_all = env_is("SV_FUSE_ALL", '1');
     {
         std::lock_guard<std::mutex> lk(g_batch_mu);
         for (size_t k = 0; k < g_batches.size(); ++k)
-            if (g_batches[k]->key == key && g_batches[k]->count == count) {
+            if (g_batches[k]->key.matches(tbits, max_grid, fuse_all, base, hs, count, gates, m)) {
                 std::shared_ptr<BatchEntry> e = g_batches[k];
                 g_batches.erase(g_batches.begin() + k);
                 g_batches.push_back(e);
@@ -1854,10 +1853,7 @@ std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *c
         return nullptr;
     }
     long cap = (long)per_cu * cus;
-    if (const char *env = std::getenv("SV_BATCH_MAX_GRID")) {
-        const long v = std::atol(env);
-        if (v > 0) cap = std::min(cap, v);
-    }
+    if (max_grid > 0) cap = std::min(cap, max_grid);
     // Chunks: an eighth of a work-group's share of its launch or a block,
     // whichever is more (a chunk's own cost, the staging of its tables, is about
     // a tenth of a block's; a work-group ends within one chunk of the others),
@@ -1904,10 +1900,14 @@ std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *c
     up(o_ops, ops.data(), ops.size() * sizeof(svp::K2Op));
     up(o_tab, table.data(), table.size());
     if (he == hipSuccess) he = hipStreamSynchronize(st);
-    e->key = key;
-    e->count = count;
+    e->key.tbits = tbits;
+    e->key.max_grid = max_grid;
+    e->key.fuse_all = fuse_all;
+    e->key.cfg = base;
     e->l = li;
     for (int i = 0; i < count; ++i) {
+        const svp::RawGate *g = reinterpret_cast<const svp::RawGate *>(gates[i]);
+        e->key.insts.push_back({hs[i]->buf, hs[i]->n, hs[i]->l2p, std::vector<svp::RawGate>(g, g + m[i])});
         e->l2p_after.push_back(plans[i].l2p_after);
         e->stats.push_back(plans[i].stats);
     }

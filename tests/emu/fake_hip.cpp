@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/sv.h"
+#include "../../paper_2605_15098_amd/csrc/plan.h"
 
 namespace {
 
@@ -300,6 +301,71 @@ int null_gates()
     return 0;
 }
 
+// Batches of one instance, with the number of graphs built so far after each:
+// a circuit, the same again, under another fusion rule, and a circuit with
+// another angle whose 64-bit mixed hash, words in the order of the inputs, is
+// that of the first.
+int batch()
+{
+    const int n = 10;
+    const void *buf = (void *)g_next;
+    sv_handle h = nullptr;
+    sv_create(n, SV_COMPLEX64, &h);
+    sv_gate a[] = {gate(SV_H, 0), gate(SV_X, 1, 0), gate(SV_RZ, 9, -1, 0.3)}, b[3];
+    std::memcpy(b, a, sizeof a);
+    b[2].theta = 1.7;
+    auto salt = [](uint64_t k) { return 0x9e3779b97f4a7c15ull + (k << 6) + (k >> 2); };
+    auto mix = [&](uint64_t k, uint64_t x) {
+        k = (k ^ (x + salt(k))) * 0xff51afd7ed558ccdull;
+        return k ^ (k >> 33);
+    };
+    auto words = [&](uint64_t k, const void *p, size_t count) {
+        for (size_t i = 0; i < count; ++i) {
+            uint64_t w;
+            std::memcpy(&w, (const char *)p + 8 * i, 8);
+            k = mix(k, w);
+        }
+        return k;
+    };
+    svp::PlanConfig c;
+    c.n = n;
+    c.dtype = SV_COMPLEX64;
+    c.mode = 1;
+    c.policy = SV_SWAP_GRAPH;
+    c.diag_free = 1;
+    c.fuse_k = 1;
+    c.auto_pins = 1;
+    int l2p[n];
+    for (int q = 0; q < n; ++q) l2p[q] = q;
+    static_assert(sizeof c % 8 == 0 && sizeof l2p % 8 == 0, "whole words");
+    uint64_t k = mix(mix(0x5eed, 1), 7);
+    k = mix(words(k, &c, sizeof c / 8), sizeof c);
+    k = mix(mix(k, (uint64_t)(uintptr_t)buf), n);
+    k = mix(words(k, l2p, sizeof l2p / 8), sizeof l2p);
+    k = words(k, a, 24);  // all but the last gate's angle and matrix, which an RZ does not read
+    uint64_t ta, tb, ua = 0, ub;
+    std::memcpy(&ta, &a[2].theta, 8);
+    std::memcpy(&tb, &b[2].theta, 8);
+    const uint64_t ka = mix(k, ta), kb = mix(k, tb);
+    ub = (kb ^ ka ^ (ua + salt(ka))) - salt(kb);
+    std::memcpy(&b[2].u[0], &ub, 8);
+    const sv_gate *la = a, *lb = b;
+    const size_t m = 3;
+    auto apply = [&](const char *name, const sv_gate *const *list) {
+        call(name, [&] { return sv_apply_batch(&h, 1, list, &m, nullptr); });
+        std::printf("graphs %d\n", g_graphs);
+    };
+    apply("first", &la);
+    apply("same", &la);
+    apply("other_angle", &lb);
+    setenv("SV_FUSE_ALL", "1", 1);
+    apply("other_rule", &la);
+    unsetenv("SV_FUSE_ALL");
+    apply("same", &la);
+    sv_destroy(h);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -310,5 +376,6 @@ int main(int argc, char **argv)
     if (what == "sweeps") return sweeps(num(2), (sv_dtype)num(3));
     if (what == "failed_reset") return failed_reset();
     if (what == "null_gates") return null_gates();
+    if (what == "batch") return batch();
     return 2;
 }

@@ -85,3 +85,11 @@ def test_network_workspace_of_the_largest_batch():
     row = 4 * (sv.sv_mlp_param_count(1) + 1)
     for batch, rows in ((1, 1), (16, 1), (17, 2), (2048, 128), (2049, 128), ((1 << 31) - 17, 128), ((1 << 31) - 1, 128)):
         assert sv.sv_mlp_workspace_bytes(1, batch) == rows * row, batch
+
+
+def test_kept_batches_are_compared_whole(host):
+    """A batch replays the graph of equal inputs only: not that of gate lists with an equal hash, nor one planned
+    under another fusion rule."""
+    got = host("batch")
+    assert all(line[1] == "0" for line in got if line[0] != "graphs")
+    assert [int(line[1]) for line in got if line[0] == "graphs"] == [1, 1, 2, 3, 3]
