@@ -397,9 +397,10 @@ sv_status sv_plan(int n, sv_dtype dtype, const sv_gate *gates, size_t m, const s
 sv_status sv_tune_candidates(int n, sv_dtype dtype, sv_schedule *out, int cap, int *count);
 
 /* Pick a schedule for this circuit on this handle among the candidates.
- * mode = SV_TUNER_EXHAUSTIVE times every candidate on a scratch copy of the
- * state (median of three timed runs after one warm-up, device time) and
- * returns the fastest; SV_TUNER_LEARNED ranks them with the cost model set by
+ * mode = SV_TUNER_EXHAUSTIVE times every candidate, and the default schedule
+ * where its block, tile and pins are none of theirs (it is returned with the
+ * three written out), on a scratch copy of the state (median of three timed
+ * runs after one warm-up, device time) and returns the fastest; SV_TUNER_LEARNED ranks them with the cost model set by
  * sv_set_cost_model, one forward pass of the network on the device over all
  * candidates, and returns the smallest prediction (exhaustive when no model
  * is set). The state and its layout are not changed. OUT_OF_MEMORY if the

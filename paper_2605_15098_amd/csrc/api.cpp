@@ -1354,6 +1354,30 @@ std::vector<sv_schedule> candidates(int n, int dtype)
     return out;
 }
 
+// The default schedule's block, tile and pins for this circuit written out as
+// candidates (with and without windows), where the list has none like them:
+// small complex128 states take smaller blocks and tiles, large ones fewer pins
+// than any candidate, and a tuner that does not time them may return a schedule
+// slower than the untuned one.
+sv_status add_default(sv_handle h, const sv_gate *gates, size_t m, std::vector<sv_schedule> &cs)
+{
+    svp::Plan plan;
+    std::string err = svp::make_plan(config_from(h, nullptr), reinterpret_cast<const svp::RawGate *>(gates), m, h->l2p, plan);
+    if (!err.empty()) return fail(SV_ERR_INVALID_ARG, err);
+    if (plan.steps.empty() || plan.pin < 1) return SV_OK;  // (a schedule's 0 pins are the default ones)
+    sv_schedule d = cs[0];
+    d.block_qubits = plan.l;
+    d.reg_qubits = plan.steps[0].logr;
+    d.pin_qubits = plan.pin;
+    for (const sv_schedule &c : cs)
+        if (c.block_qubits == d.block_qubits && c.reg_qubits == d.reg_qubits && c.pin_qubits == d.pin_qubits) return SV_OK;
+    for (int fk : {1, 5}) {
+        d.fuse_k = fk;
+        cs.push_back(d);
+    }
+    return SV_OK;
+}
+
 svp::PlanConfig config_for(int n, int dtype, const sv_schedule *s)
 {
     sv_handle_s tmp;
@@ -1530,7 +1554,7 @@ sv_status sv_tune(sv_handle h, const sv_gate *gates, size_t m, int mode, sv_sche
     if (sv_status st = check_handle(h)) return st;
     if (!out) return fail(SV_ERR_INVALID_ARG, "out is null");
     if (mode != SV_TUNER_EXHAUSTIVE && mode != SV_TUNER_LEARNED) return fail(SV_ERR_INVALID_ARG, "unknown tuner mode");
-    const std::vector<sv_schedule> cs = candidates(h->n, h->dtype);
+    std::vector<sv_schedule> cs = candidates(h->n, h->dtype);
     CostModel model;
     if (mode == SV_TUNER_LEARNED) {
         std::lock_guard<std::mutex> lk(g_model_mu);
@@ -1570,6 +1594,7 @@ sv_status sv_tune(sv_handle h, const sv_gate *gates, size_t m, int mode, sv_sche
         *out = cs[best];
         return SV_OK;
     }
+    if (sv_status st = add_default(h, gates, m, cs)) return st;
     std::vector<double> ms(cs.size(), 0.0);
     if (sv_status st = sv_tune_time(h, gates, m, cs.data(), (int)cs.size(), 3, ms.data(), nullptr)) return st;
     size_t best = 0;

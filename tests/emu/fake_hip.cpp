@@ -366,6 +366,26 @@ int batch()
     return 0;
 }
 
+// The exhaustive tuner's pick for a Fourier transform, and the untuned schedule's block.
+int tune(int n, sv_dtype dt)
+{
+    sv_handle h = nullptr;
+    sv_create(n, dt, &h);
+    std::vector<sv_gate> g;
+    for (int q = n - 1; q >= 0; --q) {
+        g.push_back(gate(SV_H, q));
+        for (int c = 0; c < q; ++c) g.push_back(gate(SV_P, q, c, 0.1 + c));
+    }
+    sv_schedule s{};
+    call("tune", [&] { return sv_tune(h, g.data(), g.size(), SV_TUNER_EXHAUSTIVE, &s); });
+    float f[SV_FEATURES];
+    sv_features(n, dt, g.data(), g.size(), nullptr, f);
+    std::printf("pick %d %d %d\n", s.block_qubits, s.reg_qubits, s.pin_qubits);
+    std::printf("default %d %d %d\n", (int)f[2], (int)f[3], (int)f[4]);
+    sv_destroy(h);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -377,5 +397,6 @@ int main(int argc, char **argv)
     if (what == "failed_reset") return failed_reset();
     if (what == "null_gates") return null_gates();
     if (what == "batch") return batch();
+    if (what == "tune") return tune(num(2), (sv_dtype)num(3));
     return 2;
 }

@@ -93,3 +93,16 @@ def test_kept_batches_are_compared_whole(host):
     got = host("batch")
     assert all(line[1] == "0" for line in got if line[0] != "graphs")
     assert [int(line[1]) for line in got if line[0] == "graphs"] == [1, 1, 2, 3, 3]
+
+
+@pytest.mark.parametrize("dtype,n", [("c128", 16), ("c128", 18), ("c128", 20), ("c128", 24), ("c64", 16), ("c64", 24)])
+def test_exhaustive_tuner_times_the_default(host, dtype, n):
+    """With device times that grow with the LDS of the launches, the default's smaller blocks of complex128 win;
+    elsewhere the pick is a candidate, and where the default is one nothing else is timed."""
+    got = host("tune", n, sv.DTYPES[dtype])
+    pick, default = (tuple(int(x) for x in line[1:]) for line in got[1:])
+    assert got[0][1] == "0"
+    listed = {(c.block_qubits, c.reg_qubits, c.pin_qubits) for c in sv.sv_tune_candidates(n, dtype)}
+    assert pick in listed | {default}
+    if dtype == "c128" and n <= 18:
+        assert default not in listed and pick == default
