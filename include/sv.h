@@ -309,8 +309,10 @@ sv_status sv_apply_batch(sv_handle *hs, int count, const sv_gate *const *gates, 
  * states for the six largest block sizes (the largest is the dtype's
  * maximum, capped by the largest instance; at least 7), register tiles of
  * the dtype's default and one below, and fusion widths fuse_k 1, 4 and 5
- * (matrix-core windows where the cost gate admits them), and returns the
- * fastest schedule (median of three runs after a warm-up).
+ * (matrix-core windows where the cost gate admits them), and for the default
+ * schedule (block_qubits, reg_qubits and pin_qubits 0) where it plans the
+ * batch like none of these, and returns the fastest schedule (median of three
+ * runs after a warm-up).
  * The states are not changed. */
 sv_status sv_tune_batch(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m, sv_schedule *out);
 

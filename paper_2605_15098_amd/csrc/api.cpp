@@ -1728,6 +1728,46 @@ std::vector<std::shared_ptr<BatchEntry>> g_batches;  // most recent last, at mos
 
 size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
+// Planner input of a batch under schedule s, but for the sizes that are an
+// instance's own.
+svp::PlanConfig batch_config(sv_handle h, const sv_schedule *s)
+{
+    svp::PlanConfig c = config_from(h, s);
+    // a schedule that leaves the sizes to the library leaves it the pins too: 22
+    // qubits in blocks of 13 take two passes with 128-byte runs, three with 256
+    c.auto_pins = c.l <= 0 && c.logr <= 0 && c.pin_low < 0;
+    return c;
+}
+
+// One work-group size for the launch, 2^tbits threads; instance i runs
+// blocks of l_i = min(n_i, tbits + rmax) qubits with a register tile of
+// l_i - tbits (3 .. rmax) amplitude bits.
+struct BatchShape {
+    int tbits = 0, lmax_tile = 3;
+    std::vector<int> l, r;
+
+    // false: the schedule does not run as one launch. reg: the schedule's own tile (0: none).
+    bool set(sv_handle *hs, int count, const svp::PlanConfig &c, int reg)
+    {
+        int min_n = 64;
+        for (int i = 0; i < count; ++i) min_n = std::min(min_n, hs[i]->n);
+        const int lreq = c.l > 0 ? c.l : svp::default_block_qubits(c.dtype);
+        // default tile: one below the single-state default (the batched kernel
+        // runs the interpreter, whose largest tile needs twice the registers and
+        // halves the resident work-groups)
+        const int rmax = std::min(reg > 0 ? reg : svp::default_reg_qubits(c.dtype) - 1, lreq);
+        if (c.mode != 1 || c.remap != 0 || rmax < 3 || rmax > (c.dtype == 0 ? 5 : 4) || min_n < 3) return false;
+        tbits = std::min(lreq - rmax, min_n - 3);
+        while ((1 << tbits) > svk::k6_max_threads(c.dtype, rmax)) --tbits;
+        for (int i = 0; i < count; ++i) {
+            l.push_back(std::min(hs[i]->n, tbits + rmax));
+            r.push_back(l[i] - tbits);
+            lmax_tile = std::max(lmax_tile, r[i]);
+        }
+        return true;
+    }
+};
+
 // Build (or fetch) the batch for these handles; nullptr + message on failure.
 // *sequential is set when the schedule does not run as one launch.
 std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m, const sv_schedule *s,
@@ -1735,33 +1775,14 @@ std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *c
 {
     *sequential = false;
     const int dtype = hs[0]->dtype;
-    svp::PlanConfig base = config_from(hs[0], s);
-    // a schedule that leaves the sizes to the library leaves it the pins too: 22
-    // qubits in blocks of 13 take two passes with 128-byte runs, three with 256
-    base.auto_pins = base.l <= 0 && base.logr <= 0 && base.pin_low < 0;
-    int min_n = 64;
-    for (int i = 0; i < count; ++i) min_n = std::min(min_n, hs[i]->n);
-    // One work-group size for the launch, 2^tbits threads; instance i runs
-    // blocks of l_i = min(n_i, tbits + rmax) qubits with a register tile of
-    // l_i - tbits (3 .. rmax) amplitude bits.
-    const int lreq = base.l > 0 ? base.l : svp::default_block_qubits(dtype);
-    // default tile: one below the single-state default (the batched kernel
-    // runs the interpreter, whose largest tile needs twice the registers and
-    // halves the resident work-groups)
-    const int rmax = std::min(s && s->reg_qubits > 0 ? s->reg_qubits : svp::default_reg_qubits(dtype) - 1, lreq);
-    if (base.mode != 1 || base.remap != 0 || rmax < 3 || rmax > (dtype == 0 ? 5 : 4) || min_n < 3) {
+    const svp::PlanConfig base = batch_config(hs[0], s);
+    BatchShape shape;
+    if (!shape.set(hs, count, base, s ? s->reg_qubits : 0)) {
         *sequential = true;
         return nullptr;
     }
-    int tbits = std::min(lreq - rmax, min_n - 3);
-    while ((1 << tbits) > svk::k6_max_threads(dtype, rmax)) --tbits;
-    std::vector<int> li(count), ri(count);
-    int lmax_tile = 3;
-    for (int i = 0; i < count; ++i) {
-        li[i] = std::min(hs[i]->n, tbits + rmax);
-        ri[i] = li[i] - tbits;
-        lmax_tile = std::max(lmax_tile, ri[i]);
-    }
+    const int tbits = shape.tbits, lmax_tile = shape.lmax_tile;
+    const std::vector<int> &li = shape.l, &ri = shape.r;
     const char *grid_env = std::getenv("SV_BATCH_MAX_GRID");
     const long max_grid = grid_env ? std::atol(grid_env) : 0;
     const bool fuse_all = env_is("SV_FUSE_ALL", '1');
@@ -1967,6 +1988,32 @@ std::shared_ptr<BatchEntry> get_batch(sv_handle *hs, int count, const sv_gate *c
     return e;
 }
 
+// True if the default schedule d plans this batch as one of cs does: the same
+// block and tile for every instance, and the dtype's default pins.
+bool batch_default_listed(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m, const sv_schedule &d,
+                          const std::vector<sv_schedule> &cs)
+{
+    const svp::PlanConfig base = batch_config(hs[0], &d);
+    BatchShape shape;
+    if (!shape.set(hs, count, base, 0)) return true;  // one circuit after another, whatever the schedule
+    bool same_sizes = false;
+    for (const sv_schedule &s : cs) {
+        BatchShape x;
+        same_sizes = same_sizes || (x.set(hs, count, batch_config(hs[0], &s), s.reg_qubits) && x.tbits == shape.tbits && x.l == shape.l);
+    }
+    if (!same_sizes) return false;
+    for (int i = 0; i < count; ++i) {
+        svp::PlanConfig c = config_from(hs[i], &d);
+        c.l = shape.l[i];
+        c.logr = shape.r[i];
+        c.auto_pins = base.auto_pins;
+        svp::Plan plan;
+        if (!svp::make_plan(c, reinterpret_cast<const svp::RawGate *>(gates[i]), m[i], hs[i]->l2p, plan).empty()) return true;
+        if (plan.pin >= 0 && plan.pin != std::min(svp::default_pin_qubits(c.dtype), plan.l - 1)) return false;
+    }
+    return true;
+}
+
 sv_status check_batch(sv_handle *hs, int count, const sv_gate *const *gates, const size_t *m)
 {
     if (count < 0 || (count > 0 && (!hs || !gates || !m))) return fail(SV_ERR_INVALID_ARG, "bad batch arrays");
@@ -2058,37 +2105,47 @@ sv_status sv_tune_batch(sv_handle *hs, int count, const sv_gate *const *gates, c
         else rc = sv_wrap(hs[i]->n, (sv_dtype)dtype, dst, nb, hs[0]->stream, &tmp[i]);
         if (rc == SV_OK) tmp[i]->l2p = hs[i]->l2p;
     }
+    std::vector<sv_schedule> cs;
     sv_schedule best{};
     double best_ms = 1e30;
     if (rc == SV_OK) {
         const int lmax = std::min(max_n, svp::max_block_qubits(dtype));
         static const int fuse_ks[] = {1, 4, 5};
         const int rdef = svp::default_reg_qubits(dtype);
-        for (int l = std::max(7, lmax - 5); l <= lmax && rc == SV_OK; ++l)
-            for (int r = rdef - 1; r <= rdef && rc == SV_OK; ++r)
+        sv_schedule c{};
+        c.mode = SV_PARTITIONED;
+        c.swap_policy = SV_SWAP_GRAPH;
+        c.remap = SV_REMAP_VIRTUAL;
+        c.diag_free = 1;
+        for (int l = std::max(7, lmax - 5); l <= lmax; ++l)
+            for (int r = rdef - 1; r <= rdef; ++r)
+                for (int fuse : fuse_ks) {
+                    c.block_qubits = l;
+                    c.reg_qubits = r;
+                    c.fuse_k = fuse;
+                    cs.push_back(c);
+                }
+        // the default, sizes and pins left to the library, unless one of these plans the same
+        c.block_qubits = c.reg_qubits = 0;
+        if (!batch_default_listed(tmp.data(), count, gates, m, c, cs))
             for (int fuse : fuse_ks) {
-                if (rc != SV_OK) break;
-                sv_schedule c{};
-                c.mode = SV_PARTITIONED;
-                c.block_qubits = l;
-                c.reg_qubits = r;
                 c.fuse_k = fuse;
-                c.swap_policy = SV_SWAP_GRAPH;
-                c.remap = SV_REMAP_VIRTUAL;
-                c.diag_free = 1;
-                std::vector<double> t;
-                for (int rep = 0; rep < 4 && rc == SV_OK; ++rep) {
-                    rc = sv_apply_batch(tmp.data(), count, gates, m, &c);
-                    if (rc == SV_OK && rep > 0) t.push_back(tmp[0]->st.device_ms);
-                }
-                if (rc != SV_OK) break;
-                std::sort(t.begin(), t.end());
-                const double med = t[t.size() / 2];
-                if (med < best_ms) {
-                    best_ms = med;
-                    best = c;
-                }
+                cs.push_back(c);
             }
+    }
+    for (const sv_schedule &c : cs) {
+        std::vector<double> t;
+        for (int rep = 0; rep < 4 && rc == SV_OK; ++rep) {
+            rc = sv_apply_batch(tmp.data(), count, gates, m, &c);
+            if (rc == SV_OK && rep > 0) t.push_back(tmp[0]->st.device_ms);
+        }
+        if (rc != SV_OK) break;
+        std::sort(t.begin(), t.end());
+        const double med = t[t.size() / 2];
+        if (med < best_ms) {
+            best_ms = med;
+            best = c;
+        }
     }
     for (sv_handle h : tmp)
         if (h) sv_destroy(h);

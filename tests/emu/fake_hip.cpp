@@ -5,7 +5,8 @@
 // machine without a GPU, at sizes that no test machine's memory holds.
 //
 // A launch is refused as the runtime refuses it, from 2^32 threads in one
-// dimension on. Device times are invented: the LDS bytes of the launches.
+// dimension on. Device times are invented: first the number of launches counts, then their
+// LDS bytes.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdint>
@@ -80,7 +81,7 @@ hipError_t hipLaunchKernel(const void *, dim3 grid, dim3 block, void **, size_t 
     if (threads > g_most_threads) g_most_threads = threads;
     if (g_fail_launches || threads >= (1ull << 32) || grid.x == 0) return g_last = hipErrorInvalidConfiguration;
     ++g_launches;
-    (g_capturing ? g_graph->cost : g_clock) += (double)lds;
+    (g_capturing ? g_graph->cost : g_clock) += 1e6 + (double)lds;
     return hipSuccess;
 }
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t st)
@@ -386,6 +387,32 @@ int tune(int n, sv_dtype dt)
     return 0;
 }
 
+// The batch tuner's pick for Fourier transforms of two sizes.
+int tune_batch(int n0, int n1, sv_dtype dt)
+{
+    sv_handle hs[2] = {};
+    std::vector<sv_gate> g[2];
+    const int ns[2] = {n0, n1};
+    for (int i = 0; i < 2; ++i) {
+        sv_create(ns[i], dt, &hs[i]);
+        for (int q = ns[i] - 1; q >= 0; --q) {
+            g[i].push_back(gate(SV_H, q));
+            for (int c = 0; c < q; ++c) g[i].push_back(gate(SV_P, q, c, 0.1 + c));
+        }
+    }
+    const sv_gate *lists[] = {g[0].data(), g[1].data()};
+    const size_t m[] = {g[0].size(), g[1].size()};
+    sv_schedule s{};
+    s.block_qubits = -1;
+    call("tune", [&] { return sv_tune_batch(hs, 2, lists, m, &s); });
+    std::printf("pick %d %d %d\n", s.block_qubits, s.reg_qubits, s.pin_qubits);
+    sv_stats st{};
+    call("default", [&] { return sv_apply_batch(hs, 2, lists, m, nullptr); });
+    sv_stats_get(hs[1], &st);
+    std::printf("passes %d\n", (int)st.passes);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -398,5 +425,6 @@ int main(int argc, char **argv)
     if (what == "null_gates") return null_gates();
     if (what == "batch") return batch();
     if (what == "tune") return tune(num(2), (sv_dtype)num(3));
+    if (what == "tune_batch") return tune_batch(num(2), num(3), (sv_dtype)num(4));
     return 2;
 }

@@ -106,3 +106,14 @@ def test_exhaustive_tuner_times_the_default(host, dtype, n):
     assert pick in listed | {default}
     if dtype == "c128" and n <= 18:
         assert default not in listed and pick == default
+
+
+@pytest.mark.parametrize("dtype,ns,default", [("c64", (12, 22), True), ("c64", (12, 14), False), ("c64", (10, 18), True),
+                                              ("c128", (12, 22), True)])
+def test_batch_tuner_times_the_default(host, dtype, ns, default):
+    """With device times that count launches and then their LDS, the default's pins win where they save a pass;
+    where the default is planned like a candidate, the pick is a candidate."""
+    got = host("tune_batch", *ns, sv.DTYPES[dtype])
+    assert got[0][1] == "0" and got[2][1] == "0"
+    block, reg, pin = (int(x) for x in got[1][1:])
+    assert (block, reg, pin) == (0, 0, 0) if default else block >= 7 and reg >= 3
