@@ -345,6 +345,14 @@ def learned_pick(n: int, dtype: str, gates, model_path: str, h) -> Tuple[int, fl
     return [_fields(c) for c in sv.sv_tune_candidates(n, dtype)].index(_fields(pick)), dt
 
 
+def default_schedule(n: int, dtype: str, gates):
+    """The untuned default schedule with the block, tile and pins that the
+    library chooses for this circuit written out, so that it matches its
+    candidate where it is one."""
+    f = sv.sv_features(n, dtype, gates, sv.schedule())
+    return sv.schedule(block_qubits=int(f[2]), reg_qubits=int(f[3]), pin_qubits=int(f[4]))
+
+
 def evaluate(idxs: Sequence[int], model_paths: Sequence[str], dtype: str = "c64", repeats: int = 1,
              workers: int = 12, paper_l: int = 13, budget_s: float = 0.0) -> dict:
     """Per held-out circuit: the time of every candidate (median of `repeats`
@@ -353,22 +361,19 @@ def evaluate(idxs: Sequence[int], model_paths: Sequence[str], dtype: str = "c64"
     (LRU victim, data-moving SWAP, l = paper_l; one run, no warm-up)."""
     t_start = time.perf_counter()
     jobs, plan = [], []
-    # the untuned default schedule, with the dtype's defaults written out
-    # (block, register and pinned qubits) so that it matches its candidate
-    default = sv.schedule(block_qubits=14 if dtype == "c64" else 13, reg_qubits=5 if dtype == "c64" else 4,
-                          pin_qubits=5 if dtype == "c64" else 3)
     for i in idxs:
         n, g = circuit("eval", i)
         cands = sv.sv_tune_candidates(n, dtype)
+        default = default_schedule(n, dtype, g)
         extra = [sv.paper_schedule(paper_l)]
         if _fields(default) not in [_fields(c) for c in cands]:
             extra.append(default)
-        plan.append((i, n, cands, extra))
+        plan.append((i, n, cands, extra, default))
         jobs += [(n, dtype, "eval", i, _fields(c)) for c in cands + extra]
     pipe = Pipeline(jobs, workers)
     per = []
     try:
-        for k, (i, n, cands, extra) in enumerate(plan):
+        for k, (i, n, cands, extra, default) in enumerate(plan):
             if budget_s and time.perf_counter() - t_start > budget_s:
                 log(f"time budget reached after {k} circuits")
                 break

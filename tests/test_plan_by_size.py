@@ -38,3 +38,12 @@ def test_pass_counts_by_size(n, dtype):
             longest = sv.sv_plan(n, dtype, g, sv.schedule(pin_qubits=5 if dtype == "c64" else 4, **largest))
             assert auto["passes"] <= longest["passes"]
             assert auto["block_qubits"] == largest["block_qubits"]
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n", [8, 16, 18, 20, 23, 24, 26, 28, 31])
+def test_written_out_default(n, dtype):
+    """The default that tuned schedules are compared with plans as the default does."""
+    from paper_2605_15098_amd import costmodel
+    for g in (W.qpe_gates(n, 0.3), W.random_circuit(n, 200, np.random.default_rng([n, 8]))):
+        assert sv.sv_plan(n, dtype, g, costmodel.default_schedule(n, dtype, g)) == sv.sv_plan(n, dtype, g, None)
