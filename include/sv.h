@@ -254,9 +254,8 @@ typedef struct {
 /* Apply m extended gates in order (calls accumulate, like sv_apply_circuit).
  * Runs of gates that sv_gate can express (one target, at most one control,
  * uncontrolled SWAP) go through the schedule s as sv_apply_circuit would
- * apply them; every other gate is one sweep over the state (a group of 2^k
- * amplitudes per thread) on the current layout. All gates are validated
- * before any is applied. Errors: INVALID_ARG (qubits out of range or
+ * apply them; every other gate is one sweep over the state on the current
+ * layout. All gates are validated before any is applied. Errors: INVALID_ARG (qubits out of range or
  * repeated, counts out of range, non-finite numbers, null uk), UNSUPPORTED
  * (k > 6, more than 16 controls, a tuner in s), DEVICE. */
 sv_status sv_apply_circuit_ex(sv_handle h, const sv_gate_ex *gates, size_t m, const sv_schedule *s);

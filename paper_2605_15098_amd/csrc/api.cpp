@@ -1014,9 +1014,8 @@ sv_status sv_probabilities(sv_handle h, const int *qubits, int nq, double *out)
     return SV_OK;
 }
 
-// The argmax kernels' result: the index, then its value.
-// The index at res and the value after it, through `slot` (a HostSlot that the
-// kernels wrote to) or with a copy from device memory.
+// The argmax kernels' result, the index at res and the value after it: through
+// `slot` (a HostSlot that the kernels wrote to) or with a copy from device memory.
 static sv_status fetch_argmax(sv_handle h, const uint64_t *res, const void *slot, uint64_t *m, double *p)
 {
     uint64_t r[2] = {0, 0};

@@ -700,7 +700,12 @@ struct Builder {
             // qubits, two rounds, windows growing across rounds): complex128
             // windows won only at D = 8 and complex64 windows lost at every
             // depth up to 8, so a 5-qubit window needs about 780 units of
-            // replaced work in complex128 and about 1540 in complex64.
+            // replaced work in complex128 and about 1540 in complex64. The costs
+            // count every 2x2 product as eight; an uncontrolled RX or RY outside
+            // a window takes two. Measured on those circuits again, the windows
+            // admitted still win or cost next to nothing (D = 16, 20, 24: complex64
+            // 23.9 -> 24.3, 28.1 -> 22.7, 32.7 -> 22.1 ms; complex128 71.4 -> 54.2,
+            // 83.0 -> 56.4, 97.7 -> 56.7), and up to D = 8 none is.
             auto valu = [&](const MGate &g) {
                 double c = g.cls == GC_DIAG ? 1.0 : (g.cls == GC_PERM ? 1.0 : (g.op == 0 ? 2.0 : 8.0));
                 return g.c >= 0 && g.cls != GC_DIAG ? 0.5 * c : c;
@@ -1133,10 +1138,13 @@ private:
 // blocks with fewer amplitudes per thread, although a circuit may need a pass
 // more. Device us, the largest block -> this: phase estimation 16 qubits 37.6 ->
 // 21.1, 20 qubits 59.5 -> 42.6, 200 random gates on 18 qubits 115 -> 59.
-// complex64 keeps the largest block and its longest runs up to 23 qubits: the
-// same grouping of the diagonal gates rounds the same, and readouts are in
-// double precision, where another grouping shows (smaller blocks measured 33.9 ->
-// 21.5 at 17 qubits, 44.7 -> 31.6 at 20).
+// complex64 keeps the largest block and its longest runs up to 23 qubits, so
+// that its results there keep the bits of those sizes written out: another block
+// groups the diagonal gates differently, and readouts in double precision show
+// the other rounding (1e-7, no further from the exact result). That is a choice,
+// not a crossover: smaller blocks measured faster (33.9 -> 21.5 at 17 qubits,
+// 44.7 -> 31.6 at 20). From 24 qubits on, where other pins save a whole sweep of
+// HBM, the rounding changes too.
 // Fewer pinned low qubits leave more free ones, so maybe a pass less, at
 // shorter runs: cost[] is what a pass with pins[] costs relative to the longest
 // runs (measured at 22-30 qubits: complex64 128-byte runs 1.03-1.08, 64-byte

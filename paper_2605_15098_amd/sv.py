@@ -69,7 +69,8 @@ def schedule(mode="partitioned", block_qubits=0, outer_qubits=0, fuse_k=1, swap_
     """An sv_schedule (see include/sv.h for every field). swap_policy: "graph"
     (default; gates in any order their dependences allow), "lookahead" (list
     order, look-ahead gathering) or "lru" (list order, the paper's victim).
-    Zero for block_qubits, reg_qubits or pin_qubits means the dtype's default."""
+    Zero for block_qubits, reg_qubits or pin_qubits means the dtype's default,
+    zero for all three with "graph" the library's choice by the state's size."""
     s = sv_schedule()
     s.mode = {"plain": SV_PLAIN, "partitioned": SV_PARTITIONED}.get(mode, mode)
     s.block_qubits = int(block_qubits)
