@@ -53,7 +53,9 @@ hipError_t dev_alloc(void **p, size_t bytes)
         *p = nullptr;
         return hipErrorOutOfMemory;
     }
-    return hipMalloc(p, bytes);
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();  // else the check after the next launch gets it
+    return e;
 }
 
 bool launch_fault()
@@ -599,7 +601,6 @@ sv_status sv_create(int n, sv_dtype dtype, sv_handle *out)
     h->owns = true;
     hipError_t e = dev_alloc(&h->buf, h->bytes);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
         h->buf = nullptr;
         free_handle(h);
         if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
@@ -1503,10 +1504,7 @@ sv_status sv_tune_time(sv_handle h, const sv_gate *gates, size_t m, const sv_sch
     if (svj::cache_size() > 256) svj::trim_cache(128);
     const size_t nb = amp_bytes(h->dtype) << h->n;
     void *scratch = nullptr;
-    if (dev_alloc(&scratch, nb) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(SV_ERR_OUT_OF_MEMORY, "tuner scratch state does not fit");
-    }
+    if (dev_alloc(&scratch, nb) != hipSuccess) return fail(SV_ERR_OUT_OF_MEMORY, "tuner scratch state does not fit");
     sv_handle tmp = nullptr;
     sv_status rc = status_of(hipMemcpyAsync(scratch, h->buf, nb, hipMemcpyDeviceToDevice, h->stream), "copy");
     if (rc == SV_OK) rc = sv_wrap(h->n, (sv_dtype)h->dtype, scratch, nb, h->stream, &tmp);

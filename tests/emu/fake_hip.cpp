@@ -24,7 +24,7 @@ namespace {
 constexpr uintptr_t kDeviceFrom = uintptr_t(1) << 44;
 uintptr_t g_next = kDeviceFrom;
 hipError_t g_last = hipSuccess;
-bool g_fail_launches = false, g_capturing = false;
+bool g_fail_launches = false, g_fail_allocations = false, g_capturing = false;
 int g_launches = 0, g_graphs = 0;
 uint64_t g_most_threads = 0;
 double g_clock = 0.0;
@@ -48,6 +48,7 @@ extern "C" {
 
 hipError_t hipMalloc(void **p, size_t bytes)
 {
+    if (g_fail_allocations) return g_last = hipErrorOutOfMemory;
     *p = (void *)g_next;
     g_next += (bytes + 511) / 512 * 512;
     return hipSuccess;
@@ -289,6 +290,22 @@ int failed_reset()
     return 0;
 }
 
+// An allocation that fails, then a call that needs none.
+int failed_allocation()
+{
+    sv_handle h = nullptr;
+    sv_create(12, SV_COMPLEX64, &h);
+    double p[4096], x = 0.0;
+    g_fail_allocations = true;
+    call("probabilities", [&] { return sv_probabilities(h, nullptr, 0, p); });
+    call("norm", [&] { return sv_norm(h, &x); });
+    call("reset", [&] { return sv_reset(h); });
+    g_fail_allocations = false;
+    call("norm", [&] { return sv_norm(h, &x); });
+    sv_destroy(h);
+    return 0;
+}
+
 // A circuit without its gate array, after one of as many gates was applied.
 int null_gates()
 {
@@ -426,5 +443,6 @@ int main(int argc, char **argv)
     if (what == "batch") return batch();
     if (what == "tune") return tune(num(2), (sv_dtype)num(3));
     if (what == "tune_batch") return tune_batch(num(2), num(3), (sv_dtype)num(4));
+    if (what == "failed_allocation") return failed_allocation();
     return 2;
 }

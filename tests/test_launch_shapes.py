@@ -117,3 +117,9 @@ def test_batch_tuner_times_the_default(host, dtype, ns, default):
     assert got[0][1] == "0" and got[2][1] == "0"
     block, reg, pin = (int(x) for x in got[1][1:])
     assert (block, reg, pin) == (0, 0, 0) if default else block >= 7 and reg >= 3
+
+
+def test_failed_allocation_is_not_the_next_calls_error(host):
+    """The runtime keeps a failed allocation's error until it is asked for one; the launch after it must not get it."""
+    assert [(name, int(status)) for name, status, *_ in host("failed_allocation")] == \
+        [("probabilities", sv.SV_ERR_OUT_OF_MEMORY), ("norm", sv.SV_ERR_OUT_OF_MEMORY), ("reset", 0), ("norm", 0)]
