@@ -340,7 +340,7 @@ sv_status sv_qpe_readout(sv_handle h, int t, uint64_t *m, double *phi, double *p
  * uniform u in [0, 1) maps to the smallest m with C(m) > u * C(2^nq - 1),
  * C(m) = P(0) + ... + P(m) (inverse CDF over ascending m, summed in FP64 in
  * a fixed order; dividing by the total keeps a drifted norm harmless). At
- * most 32 measured qubits; 2^nq doubles of device scratch. */
+ * most 32 measured qubits; up to 2^(nq+1) doubles of device scratch. */
 
 /* `shots` outcomes for the uniforms (host or device arrays, shots each);
  * the state is unchanged. */

@@ -1107,22 +1107,34 @@ static sv_status check_measured(sv_handle h, const int *qubits, int nq)
 
 // Scratch of a call that draws shots, and how it draws them: through the
 // cumulative table of every outcome, or without one (few shots of many
-// outcomes); then a full register in the identity layout needs no array of
-// probabilities either (direct).
+// outcomes); a full register in the identity layout needs no array of
+// probabilities either (direct), and is drawn that way also where the device
+// memory for the other two is not there (lean).
 struct ShotLayout {
     uint64_t M;
     bool table, direct;
     size_t o_p = 0, o_c, o_w, bytes;  // probabilities, table or tile sums, work
-    ShotLayout(sv_handle h, int nq, uint64_t shots) : M(1ull << (nq == 0 ? h->n : nq))
+    ShotLayout(sv_handle h, int nq, uint64_t shots, bool lean) : M(1ull << (nq == 0 ? h->n : nq))
     {
         auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-        table = !svk::shots_without_table(M, shots);
-        direct = !table && nq == 0 && identity(h->l2p);
+        direct = nq == 0 && identity(h->l2p) && (lean || svk::shots_from_state(h->dtype, M, shots));
+        table = !direct && !svk::shots_without_table(M, shots);
         o_c = direct ? 0 : up(M * 8);
         o_w = o_c + up(table ? M * 8 : svk::shot_scratch_bytes(M));
         bytes = o_w + up(std::max(outcome_work_bytes(h, nq), table ? svk::scan_scratch_bytes(M) : size_t(0)));
     }
 };
+
+// The layout of a call with `extra` bytes after its own, and its scratch.
+static sv_status shots_scratch(sv_handle h, int nq, uint64_t shots, size_t extra, ShotLayout *L)
+{
+    *L = ShotLayout(h, nq, shots, false);
+    sv_status st = ensure_scratch(h, L->bytes + extra);
+    const ShotLayout lean(h, nq, shots, true);
+    if (st != SV_ERR_OUT_OF_MEMORY || lean.direct == L->direct) return st;
+    *L = lean;
+    return ensure_scratch(h, L->bytes + extra);
+}
 
 static sv_status shots_begin(sv_handle h, const int *qubits, int nq, const ShotLayout &L, char *base)
 {
@@ -1150,9 +1162,9 @@ sv_status sv_sample(sv_handle h, const int *qubits, int nq, const double *unifor
     const bool du = is_device_ptr(uniforms), dout = is_device_ptr(out);
     const size_t chunk = std::min<size_t>(shots, size_t(1) << 22);
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    const ShotLayout L(h, nq, shots);
-    const size_t o_u = L.bytes, o_o = o_u + up(chunk * 8), need = o_o + up(chunk * 8);
-    if (sv_status st = ensure_scratch(h, need)) return st;
+    ShotLayout L(h, nq, shots, false);
+    if (sv_status st = shots_scratch(h, nq, shots, 2 * up(chunk * 8), &L)) return st;
+    const size_t o_u = L.bytes, o_o = o_u + up(chunk * 8);
     char *base = (char *)h->scratch;
     if (sv_status st = shots_begin(h, qubits, nq, L, base)) return st;
     for (size_t off = 0; off < shots; off += chunk) {
@@ -1178,9 +1190,9 @@ sv_status sv_measure(sv_handle h, const int *qubits, int nq, double u, uint64_t 
     if (sv_status s = check_measured(h, qubits, nq)) return s;
     if (!outcome || !prob) return fail(SV_ERR_INVALID_ARG, "null output");
     if (!(u >= 0.0 && u < 1.0)) return fail(SV_ERR_INVALID_ARG, "u must be in [0, 1)");
-    const ShotLayout L(h, nq, 1);
-    const size_t o_u = L.bytes, need = o_u + 256;
-    if (sv_status st = ensure_scratch(h, need)) return st;
+    ShotLayout L(h, nq, 1, false);
+    if (sv_status st = shots_scratch(h, nq, 1, 256, &L)) return st;
+    const size_t o_u = L.bytes;
     char *base = (char *)h->scratch;
     if (sv_status st = shots_begin(h, qubits, nq, L, base)) return st;
     SV_HIP(hipMemcpyAsync(base + o_u, &u, 8, hipMemcpyHostToDevice, h->stream), "copy");

@@ -70,6 +70,7 @@ hipError_t sample_outcomes(const double *cdf, uint64_t M, const double *u, uint6
 // tiles into scratch (shot_scratch_bytes(M)), shot_outcomes draws. p: the M
 // probabilities (device), or null for those of state S in the identity layout.
 bool shots_without_table(uint64_t M, uint64_t shots);
+bool shots_from_state(int dtype, uint64_t M, uint64_t shots);
 size_t shot_scratch_bytes(uint64_t M);
 hipError_t shot_prepare(const double *p, const void *S, int dtype, uint64_t M, void *scratch, hipStream_t st);
 hipError_t shot_outcomes(const double *p, const void *S, int dtype, uint64_t M, const void *scratch, const double *u,

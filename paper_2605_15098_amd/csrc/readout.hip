@@ -703,10 +703,31 @@ static uint64_t shot_tiles(uint64_t M) { return (M + SHOT_TILE - 1) / SHOT_TILE;
 
 size_t shot_scratch_bytes(uint64_t M) { return ((shot_tiles(M) * 8 + 255) & ~(size_t)255) + scan_scratch_bytes(shot_tiles(M)); }
 
-// A table pays once there are about M / 64 shots: it costs some 6 ps per
-// outcome more, and then a shot costs about 0.4 ns (a thread's search) instead
-// of 0.75 ns (a wave's).
-bool shots_without_table(uint64_t M, uint64_t shots) { return shots < M / 64; }
+// A table costs four more passes over M values, and then a shot costs a thread's
+// search (0.24 ns at 2^26 outcomes) instead of a wave's that reads 4 KiB (1.2 ns).
+// They cross at about M / 64 shots while the probabilities fit the Infinity
+// Cache and at M / 85 beyond (us without copies, table / none: 2^22 M / 64 99 / 92,
+// M / 32 104 / 135; 2^24 M / 64 321 / 300; 2^25 M / 84 671 / 560; 2^26 M / 128 1235 /
+// 968, M / 64 1356 / 1583). Up to 2048 outcomes one launch scans the table (20.5 / 21.5).
+bool shots_without_table(uint64_t M, uint64_t shots)
+{
+    return M > SCAN_TILE && shots < M / (M <= (1ull << 25) ? 64 : 96);
+}
+
+// Without a table, straight from the state or from an array of probabilities.
+// The array costs a write and a read of 8 M bytes, the state more per shot
+// (2^26 outcomes complex64, array / state: one shot 342 / 191, M / 512 503 / 404,
+// M / 256 657 / 613, M / 128 968 / 1032; 2^22 M / 512 52 / 50, M / 256 58 / 61; 2^20 M / 64
+// 44 / 44). In complex128 a lane's eight amplitudes fill a 128-byte line and a
+// wave's load touches 64 of them: beyond the caches that takes longer than the
+// array (2^22 50 / 90, 2^24 115 / 317, 2^26 454 / 977), within them less, for the
+// fewer shots the larger the state (2^17 M / 64 25 / 25; 2^20 one shot 27 / 25, M / 512
+// 31 / 29, M / 256 34 / 36; 2^21 one 40 / 34, M / 2048 40 / 38, M / 105 56 / 128).
+bool shots_from_state(int dtype, uint64_t M, uint64_t shots)
+{
+    if (dtype == 0) return shots < M / (M <= (1ull << 20) ? 64 : 256);
+    return M <= (1ull << 21) && shots < M / (M <= (1ull << 18) ? 64 : (M <= (1ull << 20) ? 512 : 2048));
+}
 
 template <typename Src> static hipError_t shot_sums(const Src &src, uint64_t M, void *scratch, hipStream_t st)
 {

@@ -25,6 +25,7 @@ constexpr uintptr_t kDeviceFrom = uintptr_t(1) << 44;
 uintptr_t g_next = kDeviceFrom;
 hipError_t g_last = hipSuccess;
 bool g_fail_launches = false, g_fail_allocations = false, g_capturing = false;
+size_t g_allocated = 0, g_most_bytes = ~size_t(0);  // since the last call(); allocations above this fail
 int g_launches = 0, g_graphs = 0;
 uint64_t g_most_threads = 0;
 double g_clock = 0.0;
@@ -48,7 +49,8 @@ extern "C" {
 
 hipError_t hipMalloc(void **p, size_t bytes)
 {
-    if (g_fail_allocations) return g_last = hipErrorOutOfMemory;
+    if (g_fail_allocations || bytes > g_most_bytes) return g_last = hipErrorOutOfMemory;
+    g_allocated += bytes;
     *p = (void *)g_next;
     g_next += (bytes + 511) / 512 * 512;
     return hipSuccess;
@@ -184,6 +186,7 @@ template <typename F> void call(const char *name, F &&f)
 {
     g_launches = 0;
     g_most_threads = 0;
+    g_allocated = 0;
     const sv_status st = f();
     std::printf("%s %d %d %llu\n", name, (int)st, g_launches, (unsigned long long)g_most_threads);
 }
@@ -286,6 +289,26 @@ int failed_reset()
     call("reset", [&] { return sv_reset(h); });
     sv_layout(h, lay);
     std::printf("layout %d %d %d %d %d\n", lay[0], lay[1], lay[2], lay[3], lay[4]);
+    sv_destroy(h);
+    return 0;
+}
+
+// Shots (their logarithm; -1: a projective measurement) of a full register in the
+// identity or a permuted layout, and the scratch that they took; little: with
+// no memory for an array of the probabilities.
+int shots(int n, sv_dtype dt, int log_shots, bool permuted, bool little)
+{
+    sv_handle h = nullptr;
+    sv_create(n, dt, &h);
+    const sv_gate g = gate(SV_SWAP, 0, -1, 0.0, n - 1);
+    if (permuted) sv_apply_circuit(h, &g, 1, nullptr);
+    const size_t count = size_t(1) << (log_shots > 0 ? log_shots : 0);
+    double *u = (double *)device(8 * count);
+    uint64_t *out = (uint64_t *)device(8 * count), m = 0;
+    double p = 0.0;
+    if (little) g_most_bytes = (size_t(1) << n) + 16 * count + 4096;
+    call("shots", [&] { return log_shots < 0 ? sv_measure(h, nullptr, 0, 0.5, &m, &p) : sv_sample(h, nullptr, 0, u, count, out); });
+    std::printf("scratch %zu\n", g_allocated);
     sv_destroy(h);
     return 0;
 }
@@ -444,5 +467,6 @@ int main(int argc, char **argv)
     if (what == "tune") return tune(num(2), (sv_dtype)num(3));
     if (what == "tune_batch") return tune_batch(num(2), num(3), (sv_dtype)num(4));
     if (what == "failed_allocation") return failed_allocation();
+    if (what == "shots") return shots(num(2), (sv_dtype)num(3), num(4), num(5) != 0, num(6) != 0);
     return 2;
 }

@@ -123,3 +123,26 @@ def test_failed_allocation_is_not_the_next_calls_error(host):
     """The runtime keeps a failed allocation's error until it is asked for one; the launch after it must not get it."""
     assert [(name, int(status)) for name, status, *_ in host("failed_allocation")] == \
         [("probabilities", sv.SV_ERR_OUT_OF_MEMORY), ("norm", sv.SV_ERR_OUT_OF_MEMORY), ("reset", 0), ("norm", 0)]
+
+
+@pytest.mark.parametrize("dtype,n,log_shots,permuted,how", [
+    # complex128 straight from the state only within the caches
+    (1, 18, 11, 0, "state"), (1, 18, 12, 0, "table"), (1, 20, 0, 0, "state"), (1, 20, 11, 0, "array"), (1, 21, 9, 0, "state"),
+    (1, 21, 10, 0, "array"), (1, 22, 0, 0, "array"), (1, 26, 0, 0, "array"), (1, 26, 19, 0, "array"),
+    (1, 26, 20, 0, "table"), (1, 26, -1, 0, "array"),
+    (0, 20, 13, 0, "state"), (0, 20, 14, 0, "table"), (0, 24, 15, 0, "state"), (0, 24, 16, 0, "array"), (0, 24, 17, 0, "array"),
+    (0, 24, 18, 0, "table"), (0, 25, 18, 1, "array"), (0, 25, 19, 1, "table"), (0, 26, 0, 0, "state"), (0, 26, -1, 0, "state"), (0, 26, 19, 0, "array"), (0, 26, 20, 0, "table"),
+    (0, 11, 0, 0, "state"), (0, 11, 0, 1, "table"), (0, 12, 0, 1, "array"), (1, 26, 0, 1, "array"), (0, 26, 20, 1, "table")])
+def test_how_shots_are_drawn(host, dtype, n, log_shots, permuted, how):
+    """By the scratch: tile sums (M / 64 bytes), with the probabilities (8 M more), or those and the table (16 M)."""
+    got = host("shots", n, dtype, log_shots, permuted, 0)
+    M, extra = 1 << n, 16 << max(log_shots, 5)
+    scratch = int(got[1][1])
+    # (a measurement of all zeros ends with an error, after the draw)
+    assert int(got[0][1]) == (sv.SV_ERR_INVALID_ARG if log_shots < 0 else 0)
+    least = {"state": 0, "array": 8 * M, "table": 16 * M}[how]
+    assert least <= scratch <= least + M // 32 + extra + 4096, scratch
+    if not permuted:
+        # where there is no memory for the array, straight from the state
+        few = host("shots", n, dtype, log_shots, permuted, 1)
+        assert few[0][1] == got[0][1]
