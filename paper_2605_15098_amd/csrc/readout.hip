@@ -466,11 +466,16 @@ static BitList make_bits(const int *b, int cnt)
     return bl;
 }
 
-// How a marginal runs. Below 2^10 amplitudes: a thread per output. From
+// How a marginal runs. Below 2^10 amplitudes, and below 2^20 of them where no
+// qubit is summed over (the state is in the caches): a thread per output (all
+// 18 qubits reversed: 16.6 us, a wave per 64 outputs 19.8). From
 // 2^20 outputs: tiles (512 work-groups or more of 2^11 outputs each). Else
-// work-groups that split the summed terms: 16 waves, and where more than 12
-// qubits are summed over also `shares` work-groups per output row, so that
-// about 8192 waves are in flight with 8 loads or more each.
+// a work-group per output row (2^no of them), which splits the summed terms
+// over up to 16 waves, and where more than 12 qubits are summed over also over
+// `shares` work-groups, so that about 8192 waves are in flight with 8 loads or
+// more each. With 2^13 rows the rows alone are that many: more waves only add
+// LDS sums (16 waves -> this, complex64: 19 of 24 qubits 70 -> 35 us, 18 of 26
+// scattered ones 488 -> 108).
 struct MargPlan {
     int kind;  // 0 thread per output, 1 reduce, 2 tiles
     int lanes; // marginal bits that are lane bits
@@ -480,17 +485,18 @@ struct MargPlan {
 static MargPlan marg_plan(int n, int nq, int lane_q)
 {
     MargPlan p{0, lane_q, 1, 1};
-    if (n < 10) return p;
+    if (n < 10 || (nq == n && n < 20)) return p;
     if (nq >= 20) {
         p.kind = 2;
         return p;
     }
     p.kind = 1;
-    const int ns = n - 6 - (nq - lane_q);  // summed bits outside the lanes
-    int lw = std::min(4, ns);
+    const int no = nq - lane_q;
+    const int ns = n - 6 - no;  // summed bits outside the lanes
+    const int lw = std::min({4, ns, std::max(0, 13 - no)});
     p.waves = 1 << lw;
     if (n - nq > 12) {
-        int lg = std::max(0, 13 - (nq - lane_q) - lw);
+        int lg = std::max(0, 13 - no - lw);
         lg = std::min(lg, std::max(0, ns - lw - 3));
         p.shares = 1 << lg;
     }

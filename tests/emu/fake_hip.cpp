@@ -293,6 +293,19 @@ int failed_reset()
     return 0;
 }
 
+// The marginal of the low nq qubits (of all: in reversed order).
+int marginal(int n, int nq)
+{
+    sv_handle h = nullptr;
+    sv_create(n, SV_COMPLEX64, &h);
+    std::vector<int> q(nq);
+    for (int k = 0; k < nq; ++k) q[k] = nq == n ? n - 1 - k : k;
+    double *out = (double *)device(8ull << nq);
+    call("marginal", [&] { return sv_probabilities(h, q.data(), nq, out); });
+    sv_destroy(h);
+    return 0;
+}
+
 // Shots (their logarithm; -1: a projective measurement) of a full register in the
 // identity or a permuted layout, and the scratch that they took; little: with
 // no memory for an array of the probabilities.
@@ -468,5 +481,6 @@ int main(int argc, char **argv)
     if (what == "tune_batch") return tune_batch(num(2), num(3), (sv_dtype)num(4));
     if (what == "failed_allocation") return failed_allocation();
     if (what == "shots") return shots(num(2), (sv_dtype)num(3), num(4), num(5) != 0, num(6) != 0);
+    if (what == "marginal") return marginal(num(2), num(3));
     return 2;
 }

@@ -146,3 +146,14 @@ def test_how_shots_are_drawn(host, dtype, n, log_shots, permuted, how):
         # where there is no memory for the array, straight from the state
         few = host("shots", n, dtype, log_shots, permuted, 1)
         assert few[0][1] == got[0][1]
+
+
+@pytest.mark.parametrize("n,nq", [(24, 19), (24, 18), (24, 15), (24, 13), (22, 19), (26, 19), (21, 19), (20, 14), (16, 16), (18, 18), (19, 19), (12, 11)])
+def test_waves_of_a_marginal(host, n, nq):
+    """A row of 64 outputs per work-group, and no more waves than 2^13 or one a row: a row's 16 waves are for few rows.
+    Nothing summed over: a thread per output."""
+    (name, status, launches, threads), = host("marginal", n, nq)
+    rows, summed = 1 << (nq - 6), 1 << (n - nq)
+    waves = max(1, min(16, summed, (1 << 13) // rows))
+    assert int(status) == 0 and int(launches) == 1
+    assert int(threads) == (1 << n if n == nq else 64 * rows * waves)
