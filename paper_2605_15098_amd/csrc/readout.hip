@@ -363,6 +363,24 @@ __global__ void __launch_bounds__(1024) marg_reduce_kernel(const C *__restrict__
     part[(uint64_t)blockIdx.y * M + m] = s;
 }
 
+// As many rows as waves: each wave sums a row by itself, four to a work-group. One
+// wave to a work-group costs the launch of each (16 of 22 qubits, all six lane bits
+// summed, 2^16 rows of 64 amplitudes: 39 us, four 26).
+template <typename C>
+__global__ void __launch_bounds__(256) marg_rows_kernel(const C *__restrict__ S, MargArg q, double *__restrict__ out)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t c = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (c >> q.no) return;
+    const double s = fold_lanes(marg_terms(S, xor_masks(c, q.oa) ^ lane, q, 0, 1ull << q.ns), q.lane_sum);
+    if (lane & q.lane_sum) return;
+    uint64_t m = xor_masks(c, q.om);
+#pragma unroll
+    for (int b = 0; b < 6; ++b)
+        if ((lane >> b) & 1u) m |= q.lm[b];
+    out[m] = s;
+}
+
 // Adds the shares: a wave per output, its lanes in steps of 64, then across the lanes.
 __global__ void __launch_bounds__(256) marg_finish_kernel(const double *__restrict__ part, uint64_t M, int shares,
                                                           double *__restrict__ out)
@@ -466,34 +484,30 @@ static BitList make_bits(const int *b, int cnt)
     return bl;
 }
 
-// How a marginal runs. Below 2^10 amplitudes, and below 2^20 of them where no
-// qubit is summed over (the state is in the caches): a thread per output (all
-// 18 qubits reversed: 16.6 us, a wave per 64 outputs 19.8). From
+// How a marginal runs, unless a thread per output sums it (marg_by_threads). From
 // 2^20 outputs: tiles (512 work-groups or more of 2^11 outputs each). Else
 // a work-group per output row (2^no of them), which splits the summed terms
 // over up to 16 waves, and where more than 12 qubits are summed over also over
 // `shares` work-groups, so that about 8192 waves are in flight with 8 loads or
-// more each. With 2^13 rows the rows alone are that many: more waves only add
-// LDS sums (16 waves -> this, complex64: 19 of 24 qubits 70 -> 35 us, 18 of 26
-// scattered ones 488 -> 108).
+// more each. More waves than 2^13 in all only add LDS sums while the state is in
+// the caches, and some more cover its misses beyond them (2^15 from 24 qubits on,
+// 2^16 from 26. 16 waves a row -> these, complex64: 17 of 22 qubits 28 -> 18 us, 19 of
+// 24 70 -> 35, 18 of 26 scattered ones 488 -> 108; 16 of 26 with 2^13 waves 111, with
+// 2^14 94 as before).
 struct MargPlan {
-    int kind;  // 0 thread per output, 1 reduce, 2 tiles
-    int lanes; // marginal bits that are lane bits
-    int waves, shares;
+    bool tiles;
+    int waves, shares;  // of a row
 };
 
+// lane_q: marginal bits that are lane bits.
 static MargPlan marg_plan(int n, int nq, int lane_q)
 {
-    MargPlan p{0, lane_q, 1, 1};
-    if (n < 10 || (nq == n && n < 20)) return p;
-    if (nq >= 20) {
-        p.kind = 2;
-        return p;
-    }
-    p.kind = 1;
+    MargPlan p{nq >= 20, 1, 1};
+    if (p.tiles) return p;
     const int no = nq - lane_q;
     const int ns = n - 6 - no;  // summed bits outside the lanes
-    const int lw = std::min({4, ns, std::max(0, 13 - no)});
+    const int most = n < 24 ? 13 : (n < 26 ? 15 : 16);  // log2 of the waves
+    const int lw = std::min({4, ns, std::max(0, most - no)});
     p.waves = 1 << lw;
     if (n - nq > 12) {
         int lg = std::max(0, 13 - no - lw);
@@ -503,13 +517,35 @@ static MargPlan marg_plan(int n, int nq, int lane_q)
     return p;
 }
 
+// A thread per output: below 2^10 amplitudes; where nothing is summed of a state
+// below 2^20 (all 18 qubits reversed 16.6 us, a wave per 64 outputs 19.8); and for few
+// terms of a state within the L2s (32 MiB together; two terms: 16 MiB, 21 of 22
+// qubits 25 and tiles 10) whose lines of 128 bytes a wave uses up by itself: each
+// bit of a line is summed over or a low bit of the outputs' index (from 2^20
+// outputs on also a run of neighbouring qubits, whose address is a shift: others
+// cost an instruction or two a bit, 20 of 22 qubits 21 us and tiles 11). There the other kernels read 64 amplitudes at a time and, where
+// lane bits are summed, fold them for few outputs (threads / rows / tiles, complex64:
+// 19 of 22 qubits without the low three 10 / 25 / 36 us, 18 of 21 7 / 14 / 36; with
+// the lines spread over the outputs, 19 scattered ones of 22, 40 / 19 / 21; 19 of 24
+// without 3..7 26 / 31, 18 of 24 without the low six, 64 terms, 81 / 100).
+static bool marg_by_threads(int n, size_t amp, const int *qbits, int nq)
+{
+    if (n < 10) return true;
+    if (nq == n) return n < 20;
+    if (n - nq > 4 || (amp << n) > (n - nq == 1 ? 16ull : 32ull) << 20) return false;
+    const int line = amp == 8 ? 4 : 3;
+    for (int k = 1; k < nq; ++k)
+        if ((k >= 6 && qbits[k] < line) || (nq >= 20 && qbits[k] != qbits[0] + k)) return false;
+    return true;
+}
+
 size_t marginal_scratch_bytes(int n, int nq)
 {
     // the most that any choice of nq qubits needs (all of its lane bits summed, or none)
     size_t b = 0;
     for (int lane_q = std::max(0, nq - (n - 6)); lane_q <= std::min(6, nq); ++lane_q) {
         const MargPlan p = marg_plan(n, nq, lane_q);
-        if (p.kind == 1 && p.shares > 1) b = std::max(b, (size_t)sizeof(double) * p.shares << nq);
+        if (p.shares > 1) b = std::max(b, (size_t)sizeof(double) * p.shares << nq);
     }
     return b;
 }
@@ -519,14 +555,14 @@ static hipError_t marginal_t(const C *S, int n, const int *qbits, int nq, const 
                              double *out, void *scratch, hipStream_t st)
 {
     const uint64_t M = 1ull << nq;
-    int lane_q = 0;
-    for (int k = 0; k < nq; ++k) lane_q += qbits[k] < 6;
-    const MargPlan p = marg_plan(n, nq, lane_q);
-    if (p.kind == 0) {
+    if (marg_by_threads(n, sizeof(C), qbits, nq)) {
         const BitList qb = make_bits(qbits, nq), ob = make_bits(obits, n - nq);
         marg_direct_kernel<C><<<grid_for(M, 256, 65535), 256, 0, st>>>(S, qb, ob, out);
         return hipGetLastError();
     }
+    int lane_q = 0;
+    for (int k = 0; k < nq; ++k) lane_q += qbits[k] < 6;
+    const MargPlan p = marg_plan(n, nq, lane_q);
     MargArg a{};
     uint64_t run = 0;
     for (int k = 0; k < n - nq; ++k) {
@@ -535,7 +571,7 @@ static hipError_t marginal_t(const C *S, int n, const int *qbits, int nq, const 
     }
     // bits of the tile: the low ones of the index (32 outputs, 256 bytes), the lane bits, then the next of the index
     bool tile[64] = {};
-    if (p.kind == 2) {
+    if (p.tiles) {
         int tb = 0;
         for (int k = 0; k < nq; ++k) {
             tile[k] = k < 5 || qbits[k] < 6;
@@ -561,13 +597,17 @@ static hipError_t marginal_t(const C *S, int n, const int *qbits, int nq, const 
             a.om[a.no++] = 1ull << k;
         }
     }
-    if (p.kind == 2) {
+    if (p.tiles) {
         return split_launch(1ull << a.no, 256, [&](uint64_t tile0, unsigned groups) {
             if (a.ns == 0) marg_tile_kernel<C, 0><<<groups, 256, 0, st>>>(S, a, tile0, out);
             else if (a.ns == 1) marg_tile_kernel<C, 1><<<groups, 256, 0, st>>>(S, a, tile0, out);
             else marg_tile_kernel<C, 2><<<groups, 256, 0, st>>>(S, a, tile0, out);
             return hipGetLastError();
         });
+    }
+    if (p.waves == 1 && p.shares == 1) {
+        marg_rows_kernel<C><<<((1u << a.no) + 3) / 4, 256, 0, st>>>(S, a, out);
+        return hipGetLastError();
     }
     double *part = p.shares > 1 ? (double *)scratch : out;
     marg_reduce_kernel<C><<<dim3(1u << a.no, (unsigned)p.shares), 64 * p.waves, 0, st>>>(S, a, part, M);

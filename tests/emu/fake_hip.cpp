@@ -293,13 +293,13 @@ int failed_reset()
     return 0;
 }
 
-// The marginal of the low nq qubits (of all: in reversed order).
-int marginal(int n, int nq)
+// The marginal of the nq qubits from `first` on (of all: in reversed order).
+int marginal(int n, int nq, int first)
 {
     sv_handle h = nullptr;
     sv_create(n, SV_COMPLEX64, &h);
     std::vector<int> q(nq);
-    for (int k = 0; k < nq; ++k) q[k] = nq == n ? n - 1 - k : k;
+    for (int k = 0; k < nq; ++k) q[k] = nq == n ? n - 1 - k : first + k;
     double *out = (double *)device(8ull << nq);
     call("marginal", [&] { return sv_probabilities(h, q.data(), nq, out); });
     sv_destroy(h);
@@ -481,6 +481,6 @@ int main(int argc, char **argv)
     if (what == "tune_batch") return tune_batch(num(2), num(3), (sv_dtype)num(4));
     if (what == "failed_allocation") return failed_allocation();
     if (what == "shots") return shots(num(2), (sv_dtype)num(3), num(4), num(5) != 0, num(6) != 0);
-    if (what == "marginal") return marginal(num(2), num(3));
+    if (what == "marginal") return marginal(num(2), num(3), num(4));
     return 2;
 }

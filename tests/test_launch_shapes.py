@@ -148,12 +148,19 @@ def test_how_shots_are_drawn(host, dtype, n, log_shots, permuted, how):
         assert few[0][1] == got[0][1]
 
 
-@pytest.mark.parametrize("n,nq", [(24, 19), (24, 18), (24, 15), (24, 13), (22, 19), (26, 19), (21, 19), (20, 14), (16, 16), (18, 18), (19, 19), (12, 11)])
+@pytest.mark.parametrize("n,nq", [(24, 19), (24, 18), (24, 15), (24, 13), (26, 16), (26, 19), (23, 19), (20, 14), (16, 11)])
 def test_waves_of_a_marginal(host, n, nq):
-    """A row of 64 outputs per work-group, and no more waves than 2^13 or one a row: a row's 16 waves are for few rows.
-    Nothing summed over: a thread per output."""
-    (name, status, launches, threads), = host("marginal", n, nq)
+    """Of the low qubits: a row of 64 outputs each, and no more waves than 2^13 (from 24 qubits on 2^15, from 26 on 2^16) or one a row."""
+    (_, status, launches, threads), = host("marginal", n, nq, 0)
     rows, summed = 1 << (nq - 6), 1 << (n - nq)
-    waves = max(1, min(16, summed, (1 << 13) // rows))
-    assert int(status) == 0 and int(launches) == 1
-    assert int(threads) == (1 << n if n == nq else 64 * rows * waves)
+    waves = max(1, min(16, summed, (1 << (13 if n < 24 else 15 if n < 26 else 16)) // rows))
+    assert int(status) == 0 and int(launches) == 1 and int(threads) == 64 * rows * waves
+
+
+@pytest.mark.parametrize("n,nq,high,threads", [(18, 18, 1, 1 << 18), (22, 19, 3, 1 << 19), (22, 18, 4, 1 << 18), (22, 17, 5, 64 << 16),
+                                               (23, 20, 3, 256 << 9), (22, 20, 2, 1 << 20), (22, 19, 0, 1 << 19), (16, 15, 1, 1 << 15), (21, 20, 1, 1 << 20), (22, 21, 1, 256 << 10)])
+def test_few_terms_in_cached_lines(host, n, nq, high, threads):
+    """Without the `high` lowest qubits: a thread per output while the state fits the L2s and at most four qubits are
+    summed over, else a wave a row or, from 2^20 outputs, a work-group per tile of 2^11."""
+    (_, status, launches, got), = host("marginal", n, nq, high)
+    assert int(status) == 0 and int(launches) == 1 and int(got) == threads
