@@ -376,7 +376,7 @@ hipError_t k1_small(void *S, int n, int dtype, const svp::K2Op *dev_ops, int nop
 // addresses (scalar loads), the 2^k outputs are stored after all inputs are
 // in registers.
 template <typename C, int K>
-__global__ void __launch_bounds__(128) kq_kernel(C *__restrict__ S, uint64_t ngroups, uint64_t group0, KqArg a, const C *__restrict__ U)
+__global__ void __launch_bounds__(128) kq_kernel(C *__restrict__ S, uint64_t ngroups, KqArg a, const C *__restrict__ U, uint64_t group0)
 {
     constexpr int D = 1 << K;
     const uint64_t g = (group0 + blockIdx.x) * 128 + threadIdx.x;
@@ -535,12 +535,12 @@ template <typename C> static hipError_t kq_launch(void *S, int n, const KqArg &a
     if (mfma && a.k == 6) return kq_mfma_launch<C, 6>((C *)S, ngroups, a, (const C *)U, st);
     return split_launch((ngroups + 127) / 128, 128, [&](uint64_t group0, unsigned groups) {
         switch (a.k) {
-        case 1: kq_kernel<C, 1><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
-        case 2: kq_kernel<C, 2><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
-        case 3: kq_kernel<C, 3><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
-        case 4: kq_kernel<C, 4><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
-        case 5: kq_kernel<C, 5><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
-        case 6: kq_kernel<C, 6><<<groups, 128, 0, st>>>((C *)S, ngroups, group0, a, (const C *)U); break;
+        case 1: kq_kernel<C, 1><<<groups, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U, group0); break;
+        case 2: kq_kernel<C, 2><<<groups, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U, group0); break;
+        case 3: kq_kernel<C, 3><<<groups, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U, group0); break;
+        case 4: kq_kernel<C, 4><<<groups, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U, group0); break;
+        case 5: kq_kernel<C, 5><<<groups, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U, group0); break;
+        case 6: kq_kernel<C, 6><<<groups, 128, 0, st>>>((C *)S, ngroups, a, (const C *)U, group0); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
