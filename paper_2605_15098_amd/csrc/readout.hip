@@ -761,18 +761,21 @@ bool shots_without_table(uint64_t M, uint64_t shots)
 }
 
 // Without a table, straight from the state or from an array of probabilities.
-// The array costs a write and a read of 8 M bytes, the state more per shot
-// (2^26 outcomes complex64, array / state: one shot 342 / 191, M / 512 503 / 404,
-// M / 256 657 / 613, M / 128 968 / 1032; 2^22 M / 512 52 / 50, M / 256 58 / 61; 2^20 M / 64
-// 44 / 44). In complex128 a lane's eight amplitudes fill a 128-byte line and a
+// The array costs a write and a read of 8 M bytes, and with the uniforms and the
+// outcomes in host memory some 28 us more, which only show after a kernel that
+// wrote 16 MiB or more; the state costs more per shot (complex64, arrays on the device,
+// array / state: 2^26 outcomes one shot 342 / 191, M / 256 657 / 613, M / 128 968 / 1032;
+// 2^24 M / 128 196 / 239; 2^22 M / 210 60 / 67, on the host 126 / 105, M / 105 74 / 89,
+// on the host 151 / 138; 2^21 M / 105 55 / 59, on the host 122 / 98; 2^20 M / 64 44 / 44).
+// In complex128 a lane's eight amplitudes fill a 128-byte line and a
 // wave's load touches 64 of them: beyond the caches that takes longer than the
 // array (2^22 50 / 90, 2^24 115 / 317, 2^26 454 / 977), within them less, for the
-// fewer shots the larger the state (2^17 M / 64 25 / 25; 2^20 one shot 27 / 25, M / 512
-// 31 / 29, M / 256 34 / 36; 2^21 one 40 / 34, M / 2048 40 / 38, M / 105 56 / 128).
+// fewer shots the larger the state (2^17 M / 64 25 / 25; 2^20 M / 512 31 / 29, M / 256
+// 34 / 36; 2^21 M / 700 41 / 45, on the host 96 / 76, M / 210 47 / 93, on the host 106 / 127).
 bool shots_from_state(int dtype, uint64_t M, uint64_t shots)
 {
-    if (dtype == 0) return shots < M / (M <= (1ull << 20) ? 64 : 256);
-    return M <= (1ull << 21) && shots < M / (M <= (1ull << 18) ? 64 : (M <= (1ull << 20) ? 512 : 2048));
+    if (dtype == 0) return shots < M / (M <= (1ull << 21) ? 64 : (M <= (1ull << 22) ? 96 : 128));
+    return M <= (1ull << 21) && shots < M / (M <= (1ull << 18) ? 64 : 512);
 }
 
 template <typename Src> static hipError_t shot_sums(const Src &src, uint64_t M, void *scratch, hipStream_t st)

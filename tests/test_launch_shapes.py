@@ -127,11 +127,12 @@ def test_failed_allocation_is_not_the_next_calls_error(host):
 
 @pytest.mark.parametrize("dtype,n,log_shots,permuted,how", [
     # complex128 straight from the state only within the caches
-    (1, 18, 11, 0, "state"), (1, 18, 12, 0, "table"), (1, 20, 0, 0, "state"), (1, 20, 11, 0, "array"), (1, 21, 9, 0, "state"),
-    (1, 21, 10, 0, "array"), (1, 22, 0, 0, "array"), (1, 26, 0, 0, "array"), (1, 26, 19, 0, "array"),
+    (1, 18, 11, 0, "state"), (1, 18, 12, 0, "table"), (1, 20, 0, 0, "state"), (1, 20, 11, 0, "array"), (1, 21, 11, 0, "state"),
+    (1, 21, 12, 0, "array"), (1, 22, 0, 0, "array"), (1, 26, 0, 0, "array"), (1, 26, 19, 0, "array"),
     (1, 26, 20, 0, "table"), (1, 26, -1, 0, "array"),
-    (0, 20, 13, 0, "state"), (0, 20, 14, 0, "table"), (0, 24, 15, 0, "state"), (0, 24, 16, 0, "array"), (0, 24, 17, 0, "array"),
-    (0, 24, 18, 0, "table"), (0, 25, 18, 1, "array"), (0, 25, 19, 1, "table"), (0, 26, 0, 0, "state"), (0, 26, -1, 0, "state"), (0, 26, 19, 0, "array"), (0, 26, 20, 0, "table"),
+    (0, 20, 13, 0, "state"), (0, 20, 14, 0, "table"), (0, 21, 14, 0, "state"), (0, 22, 15, 0, "state"), (0, 22, 16, 0, "table"),
+    (0, 24, 16, 0, "state"), (0, 24, 17, 0, "array"), (0, 24, 18, 0, "table"), (0, 25, 18, 1, "array"), (0, 25, 19, 1, "table"),
+    (0, 26, 0, 0, "state"), (0, 26, -1, 0, "state"), (0, 26, 18, 0, "state"), (0, 26, 19, 0, "array"), (0, 26, 20, 0, "table"),
     (0, 11, 0, 0, "state"), (0, 11, 0, 1, "table"), (0, 12, 0, 1, "array"), (1, 26, 0, 1, "array"), (0, 26, 20, 1, "table")])
 def test_how_shots_are_drawn(host, dtype, n, log_shots, permuted, how):
     """By the scratch: tile sums (M / 64 bytes), with the probabilities (8 M more), or those and the table (16 M)."""
