@@ -135,10 +135,11 @@ k1_pair_kernel(C *__restrict__ S, uint64_t npairs, uint64_t group0, int t, int c
 
 // Diagonal gates. Amplitudes with every bit of `ones` (at most two bits, lo
 // <= hi) set are multiplied by d1 when tsel < 0, else by d0 or d1 according
-// to bit tsel.
+// to bit tsel. (The first group as the last argument: 18 qubits complex128 3.28
+// us a gate, 3.30 as the third.)
 template <typename C>
 __global__ void __launch_bounds__(K1_BLOCK)
-k1_diag_kernel(C *__restrict__ S, uint64_t namps, uint64_t group0, int nones, int lo, int hi, int tsel, C d0, C d1)
+k1_diag_kernel(C *__restrict__ S, uint64_t namps, int nones, int lo, int hi, int tsel, C d0, C d1, uint64_t group0)
 {
     const uint64_t base = (group0 + blockIdx.x) * (K1_BLOCK * K1_PER) + threadIdx.x;
     uint64_t ones = 0;
@@ -175,9 +176,9 @@ template <typename T> static hipError_t k1_launch(void *Sv, int n, const svp::MG
         if (nb == 2 && bits[0] > bits[1]) { int x = bits[0]; bits[0] = bits[1]; bits[1] = x; }
         const uint64_t namps = 1ull << (n - nb);
         return split_launch(k1_groups(namps), K1_BLOCK, [&](uint64_t group0, unsigned groups) {
-            k1_diag_kernel<C><<<groups, K1_BLOCK, 0, st>>>(S, namps, group0, nb, nb > 0 ? bits[0] : 0,
+            k1_diag_kernel<C><<<groups, K1_BLOCK, 0, st>>>(S, namps, nb, nb > 0 ? bits[0] : 0,
                                                            nb > 1 ? bits[1] : 0, ptype ? -1 : g.t,
-                                                           mk<C>(u[0], u[1]), mk<C>(u[6], u[7]));
+                                                           mk<C>(u[0], u[1]), mk<C>(u[6], u[7]), group0);
             return hipGetLastError();
         });
     }
