@@ -306,6 +306,34 @@ __device__ __forceinline__ double fold_lanes(double s, uint32_t bits)
     return s;
 }
 
+// The lanes of R rows (a power of two) added over the lane bits `bits`: at each of
+// the lowest bits half of the rows stay on the lanes where it is clear and half
+// go to those where it is set, so R rows cost R - 1 exchanges and one for each bit
+// left instead of R a bit. The same pairs are added in the same order as by
+// fold_lanes. Leaves `live` values a lane, s[j] being row j * (R / live) + *row, and
+// clears in `bits` those that tell rows apart.
+template <int R> __device__ __forceinline__ uint32_t fold_rows(double (&s)[R], uint32_t &bits, uint32_t lane, uint32_t *row)
+{
+    uint32_t live = R;
+    *row = 0;
+#pragma unroll
+    for (int l = 0; (R >> l) > 1; ++l) {
+        if (bits == 0) break;
+        const int b = __builtin_ctz(bits);
+        const bool up = (lane >> b) & 1u;
+#pragma unroll
+        for (int j = 0; j < (R >> l) / 2; ++j) {
+            const double own = up ? s[2 * j + 1] : s[2 * j], other = up ? s[2 * j] : s[2 * j + 1];
+            s[j] = own + __shfl_xor(other, 1 << b, 64);
+        }
+        *row |= (uint32_t)up << l;
+        bits &= bits - 1;
+        live >>= 1;
+    }
+    for (uint32_t v = bits; v != 0; v &= v - 1) s[0] += __shfl_xor(s[0], (int)(v & -v), 64);
+    return live;
+}
+
 // Sum of the wave's terms o0 .. o0 + cnt - 1 (cnt a power of two) of the
 // summed bits, starting at storage address a (of term 0, this lane).
 template <typename C>
@@ -340,6 +368,34 @@ __device__ __forceinline__ double marg_terms(const C *__restrict__ S, uint64_t a
     return s;
 }
 
+// Sums of R rows' terms in ascending order, the first row's first at a, the others'
+// d[j] away: 8 loads in flight, of up to 2^2 terms (NS) from several rows, of more (NS 3) from one.
+template <int R, int NS, typename C>
+__device__ __forceinline__ void row_terms(double (&s)[R], const C *__restrict__ S, uint64_t a, const uint64_t (&d)[R], const MargArg &q)
+{
+    if constexpr (NS >= 3) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) s[j] = marg_terms(S, a ^ d[j], q, 0, 1ull << q.ns);
+    } else {
+        constexpr int T = 1 << NS, G = R < 8 / T ? R : 8 / T;
+        const uint64_t s0 = NS >= 1 ? q.sx[0] : 0ull, s1 = NS >= 2 ? q.sx[1] ^ q.sx[0] : 0ull;
+#pragma unroll
+        for (int g = 0; g < R; g += G) {
+            C v[G][T];
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[j][t] = S[a ^ d[g + j] ^ ((t & 1) ? s0 : 0ull) ^ ((t & 2) ? s1 : 0ull)];
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                s[g + j] = 0.0;
+#pragma unroll
+                for (int t = 0; t < T; ++t) s[g + j] += prob(v[j][t]);
+            }
+        }
+    }
+}
+
 // Few outputs: work-group (c, g) sums share g of the terms of value c of the
 // marginal's bits outside the lanes, its waves a part each; waves are added
 // in order. HBM bound: a one-qubit marginal of 25 qubits reads 256 MiB.
@@ -363,22 +419,41 @@ __global__ void __launch_bounds__(1024) marg_reduce_kernel(const C *__restrict__
     part[(uint64_t)blockIdx.y * M + m] = s;
 }
 
-// As many rows as waves: each wave sums a row by itself, four to a work-group. One
-// wave to a work-group costs the launch of each (16 of 22 qubits, all six lane bits
-// summed, 2^16 rows of 64 amplitudes: 39 us, four 26).
-template <typename C>
+// As many rows as waves, or more: a wave sums eight rows of up to four terms by
+// itself, or one of more, four waves to a work-group. A row of few terms is one
+// load, up to twelve exchanges of half a double and a store, one after the other: with one row a wave, 17
+// of 22 qubits without 1..5 (complex64, 2^16 rows of one term) take 26.2 us, a
+// thread per output 9.6, eight rows 6.4; 18 of 24 without the low six 107 / 80 /
+// 23; 19 of 24 without 2..6, two terms, 53 / 28 / 22. From eight terms on a row
+// fills the wave by itself, and eight rows leave too few waves (16 of 22 without 6..8 and three
+// lanes 5 to 19 % slower).
+template <typename C, int NS>
 __global__ void __launch_bounds__(256) marg_rows_kernel(const C *__restrict__ S, MargArg q, double *__restrict__ out)
 {
+    constexpr int LR = NS <= 2 ? 3 : 0, R = 1 << LR;
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t c = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t c = ((uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) << LR;
     if (c >> q.no) return;
-    const double s = fold_lanes(marg_terms(S, xor_masks(c, q.oa) ^ lane, q, 0, 1ull << q.ns), q.lane_sum);
-    if (lane & q.lane_sum) return;
+    double s[R];
+    const uint64_t a = xor_masks(c, q.oa) ^ lane;
+    uint64_t d[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) d[j] = ((j & 1) ? q.oa[0] : 0ull) ^ ((j & 2) ? q.oa[1] : 0ull) ^ ((j & 4) ? q.oa[2] : 0ull);
+    row_terms<R, NS>(s, S, a, d, q);
+    uint32_t bits = q.lane_sum, row;
+    const uint32_t live = fold_rows(s, bits, lane, &row);
+    if (lane & bits) return;
     uint64_t m = xor_masks(c, q.om);
 #pragma unroll
     for (int b = 0; b < 6; ++b)
         if ((lane >> b) & 1u) m |= q.lm[b];
-    out[m] = s;
+#pragma unroll
+    for (int k = 0; k < LR; ++k)
+        if ((row >> k) & 1u) m |= q.om[k];
+    const int step = LR - (31 - __builtin_clz(live));  // row bits that are on lanes
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j)
+        if (j < live) out[m | xor_masks(j << step, q.om)] = s[j];
 }
 
 // Adds the shares: a wave per output, its lanes in steps of 64, then across the lanes.
@@ -398,63 +473,48 @@ __global__ void __launch_bounds__(256) marg_finish_kernel(const double *__restri
 // it in index order, so both the reads and the writes cover whole runs also
 // where the layout is permuted. 28-qubit complex128, all qubits but the top
 // one in bit-reversed layout: 4958 us with a thread per output, which
-// fetched every 128-byte line for one amplitude at a time.
-template <typename C, int NS>
+// fetched every 128-byte line for one amplitude at a time. A wave folds eight
+// rows together, as above: 20 of 24 qubits without 2..5 (complex64) 24.9 us, row
+// by row 88, a thread per output 30; 20 of 25 without 3..7 43,
+// 145 and 58.
+template <typename C, int NS, int R>
 __global__ void __launch_bounds__(256) marg_tile_kernel(const C *__restrict__ S, MargArg q, uint64_t tile0, double *__restrict__ out)
 {
     __shared__ double tile[MARG_TILE];
+    constexpr int LR = R == 4 ? 2 : 3;
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t base = xor_masks(tile0 + blockIdx.x, q.oa) ^ lane, mbase = xor_masks(tile0 + blockIdx.x, q.om);
     uint32_t lpos = 0;
 #pragma unroll
     for (int b = 0; b < 6; ++b)
         if ((lane >> b) & 1u) lpos |= q.lp[b];
-    const uint32_t rounds = 1u << q.nt;
-    auto round_of = [&](uint32_t it, uint64_t *a, uint32_t *pos) {
-        *a = base;
-        *pos = lpos;
+    // a wave's R rows are bits 2 and up of the row's number, the wave its bits 0 and 1 (a tile has 2^5 rows or more)
+    uint64_t d[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) d[j] = ((j & 1) ? q.ta[2] : 0ull) ^ ((j & 2) ? q.ta[3] : 0ull) ^ ((j & 4) ? q.ta[4] : 0ull);
+    for (uint32_t it = wave; it < 1u << q.nt; it += 4 * R) {
+        uint64_t a = base;
+        uint32_t pos = lpos;
         for (uint32_t v = it; v != 0; v &= v - 1) {
             const int k = __builtin_ctz(v);
-            *a ^= q.ta[k];
-            *pos |= q.tp[k];
+            a ^= q.ta[k];
+            pos |= q.tp[k];
         }
-    };
-    auto put = [&](uint32_t pos, double s) {
-        s = fold_lanes(s, q.lane_sum);
-        if (!(lane & q.lane_sum)) tile[swz<float2>(pos)] = s;
-    };
-    if constexpr (NS <= 1) {
-        // one or two terms: four rounds' loads in flight
-        uint32_t it = wave;
-        for (; it + 12 < rounds; it += 16) {
-            C v[4][1 + NS];
-            uint32_t pos[4];
+        double s[R];
+        row_terms<R, NS>(s, S, a, d, q);
+        uint32_t bits = q.lane_sum, row;
+        const uint32_t live = fold_rows(s, bits, lane, &row);
+        if (!(lane & bits)) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint64_t a;
-                round_of(it + 4 * j, &a, &pos[j]);
-                v[j][0] = S[a];
-                if constexpr (NS == 1) v[j][1] = S[a ^ q.sx[0]];
-            }
+            for (int k = 0; k < LR; ++k)
+                if ((row >> k) & 1u) pos |= q.tp[2 + k];
+            const int step = LR - (31 - __builtin_clz(live));  // row bits that are on lanes
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                double s = prob(v[j][0]);
-                if constexpr (NS == 1) s += prob(v[j][1]);
-                put(pos[j], s);
+            for (uint32_t j = 0; j < R; ++j) {
+                const uint32_t r = j << step;
+                if (j < live)
+                    tile[swz<float2>(pos | ((r & 1) ? q.tp[2] : 0u) | ((r & 2) ? q.tp[3] : 0u) | ((r & 4) ? q.tp[4] : 0u))] = s[j];
             }
-        }
-        for (; it < rounds; it += 4) {
-            uint64_t a;
-            uint32_t pos;
-            round_of(it, &a, &pos);
-            put(pos, marg_terms(S, a, q, 0, 1ull << NS));
-        }
-    } else {
-        for (uint32_t it = wave; it < rounds; it += 4) {
-            uint64_t a;
-            uint32_t pos;
-            round_of(it, &a, &pos);
-            put(pos, marg_terms(S, a, q, 0, 1ull << q.ns));
         }
     }
     __syncthreads();
@@ -482,6 +542,18 @@ static BitList make_bits(const int *b, int cnt)
         if (b[k] != b[0] + k) bl.low = 0;
     }
     return bl;
+}
+
+// Eight rows folded together where two lane bits or more are summed. Else there is
+// next to nothing to fold, and four read faster from HBM (all lane bits asked for: 22
+// scattered ones of 23 qubits, complex64, 18.7 us, eight 20.4; 23 of 24, complex128,
+// 64 / 67).
+template <typename C, int R> static void marg_tiles(const C *S, const MargArg &a, uint64_t tile0, unsigned groups, double *out, hipStream_t st)
+{
+    if (a.ns == 0) marg_tile_kernel<C, 0, R><<<groups, 256, 0, st>>>(S, a, tile0, out);
+    else if (a.ns == 1) marg_tile_kernel<C, 1, R><<<groups, 256, 0, st>>>(S, a, tile0, out);
+    else if (a.ns == 2) marg_tile_kernel<C, 2, R><<<groups, 256, 0, st>>>(S, a, tile0, out);
+    else marg_tile_kernel<C, 3, R><<<groups, 256, 0, st>>>(S, a, tile0, out);
 }
 
 // How a marginal runs, unless a thread per output sums it (marg_by_threads). From
@@ -517,27 +589,9 @@ static MargPlan marg_plan(int n, int nq, int lane_q)
     return p;
 }
 
-// A thread per output: below 2^10 amplitudes; where nothing is summed of a state
-// below 2^20 (all 18 qubits reversed 16.6 us, a wave per 64 outputs 19.8); and for few
-// terms of a state within the L2s (32 MiB together; two terms: 16 MiB, 21 of 22
-// qubits 25 and tiles 10) whose lines of 128 bytes a wave uses up by itself: each
-// bit of a line is summed over or a low bit of the outputs' index (from 2^20
-// outputs on also a run of neighbouring qubits, whose address is a shift: others
-// cost an instruction or two a bit, 20 of 22 qubits 21 us and tiles 11). There the other kernels read 64 amplitudes at a time and, where
-// lane bits are summed, fold them for few outputs (threads / rows / tiles, complex64:
-// 19 of 22 qubits without the low three 10 / 25 / 36 us, 18 of 21 7 / 14 / 36; with
-// the lines spread over the outputs, 19 scattered ones of 22, 40 / 19 / 21; 19 of 24
-// without 3..7 26 / 31, 18 of 24 without the low six, 64 terms, 81 / 100).
-static bool marg_by_threads(int n, size_t amp, const int *qbits, int nq)
-{
-    if (n < 10) return true;
-    if (nq == n) return n < 20;
-    if (n - nq > 4 || (amp << n) > (n - nq == 1 ? 16ull : 32ull) << 20) return false;
-    const int line = amp == 8 ? 4 : 3;
-    for (int k = 1; k < nq; ++k)
-        if ((k >= 6 && qbits[k] < line) || (nq >= 20 && qbits[k] != qbits[0] + k)) return false;
-    return true;
-}
+// A thread per output: below 2^10 amplitudes, and where nothing is summed of a
+// state below 2^20 (all 18 qubits reversed, repeated in the caches, 3.9 us, by rows 4.9; 19 6.4 / 5.9).
+static bool marg_by_threads(int n, int nq) { return n < 10 || (nq == n && n < 20); }
 
 size_t marginal_scratch_bytes(int n, int nq)
 {
@@ -555,7 +609,7 @@ static hipError_t marginal_t(const C *S, int n, const int *qbits, int nq, const 
                              double *out, void *scratch, hipStream_t st)
 {
     const uint64_t M = 1ull << nq;
-    if (marg_by_threads(n, sizeof(C), qbits, nq)) {
+    if (marg_by_threads(n, nq)) {
         const BitList qb = make_bits(qbits, nq), ob = make_bits(obits, n - nq);
         marg_direct_kernel<C><<<grid_for(M, 256, 65535), 256, 0, st>>>(S, qb, ob, out);
         return hipGetLastError();
@@ -599,14 +653,18 @@ static hipError_t marginal_t(const C *S, int n, const int *qbits, int nq, const 
     }
     if (p.tiles) {
         return split_launch(1ull << a.no, 256, [&](uint64_t tile0, unsigned groups) {
-            if (a.ns == 0) marg_tile_kernel<C, 0><<<groups, 256, 0, st>>>(S, a, tile0, out);
-            else if (a.ns == 1) marg_tile_kernel<C, 1><<<groups, 256, 0, st>>>(S, a, tile0, out);
-            else marg_tile_kernel<C, 2><<<groups, 256, 0, st>>>(S, a, tile0, out);
+            if (__builtin_popcount(a.lane_sum) >= 2) marg_tiles<C, 8>(S, a, tile0, groups, out, st);
+            else marg_tiles<C, 4>(S, a, tile0, groups, out, st);
             return hipGetLastError();
         });
     }
     if (p.waves == 1 && p.shares == 1) {
-        marg_rows_kernel<C><<<((1u << a.no) + 3) / 4, 256, 0, st>>>(S, a, out);
+        // (fewer than eight rows: the ones too many have no bit of their own and repeat others)
+        const uint32_t waves = 1u << (a.ns <= 2 ? std::max(a.no - 3, 0) : a.no), groups = (waves + 3) / 4;
+        if (a.ns == 0) marg_rows_kernel<C, 0><<<groups, 256, 0, st>>>(S, a, out);
+        else if (a.ns == 1) marg_rows_kernel<C, 1><<<groups, 256, 0, st>>>(S, a, out);
+        else if (a.ns == 2) marg_rows_kernel<C, 2><<<groups, 256, 0, st>>>(S, a, out);
+        else marg_rows_kernel<C, 3><<<groups, 256, 0, st>>>(S, a, out);
         return hipGetLastError();
     }
     double *part = p.shares > 1 ? (double *)scratch : out;

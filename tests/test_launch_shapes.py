@@ -158,10 +158,11 @@ def test_waves_of_a_marginal(host, n, nq):
     assert int(status) == 0 and int(launches) == 1 and int(threads) == 64 * rows * waves
 
 
-@pytest.mark.parametrize("n,nq,high,threads", [(18, 18, 1, 1 << 18), (22, 19, 3, 1 << 19), (22, 18, 4, 1 << 18), (22, 17, 5, 64 << 16),
-                                               (23, 20, 3, 256 << 9), (22, 20, 2, 1 << 20), (22, 19, 0, 1 << 19), (16, 15, 1, 1 << 15), (21, 20, 1, 1 << 20), (22, 21, 1, 256 << 10)])
-def test_few_terms_in_cached_lines(host, n, nq, high, threads):
-    """Without the `high` lowest qubits: a thread per output while the state fits the L2s and at most four qubits are
-    summed over, else a wave a row or, from 2^20 outputs, a work-group per tile of 2^11."""
+@pytest.mark.parametrize("n,nq,high,threads", [(18, 18, 1, 1 << 18), (22, 19, 3, 64 << 13), (22, 18, 4, 64 << 13), (22, 17, 5, 64 << 13), (23, 18, 5, 64 << 14),
+                                               (23, 20, 3, 256 << 9), (22, 20, 2, 256 << 9), (22, 19, 0, 64 << 13), (16, 15, 1, 64 << 7), (21, 20, 1, 256 << 9),
+                                               (22, 21, 1, 256 << 10), (10, 8, 2, 64 << 2)])
+def test_few_terms(host, n, nq, high, threads):
+    """Without the `high` lowest qubits: a wave for eight rows of up to four terms or for one of more, a work-group
+    per tile of 2^11 from 2^20 outputs on, and a thread per output where nothing is summed of a state below 2^20."""
     (_, status, launches, got), = host("marginal", n, nq, high)
     assert int(status) == 0 and int(launches) == 1 and int(got) == threads
